@@ -33,12 +33,12 @@ PEAK_HBM = 8.0e12           # bytes/s
 # paper_2505_00097_amd/count_flops.py prints it (a CPU test keeps the two in
 # step). On grids with two phi planes the kernel variant drops the phi
 # derivatives that vanish identically there, and its own count applies.
-F_ALG = {(0, False): 5858, (0, True): 5037, (1, False): 5380, (1, True): 4553, (2, False): 5663,
-         (2, True): 4842}
+F_ALG = {(0, False): 5187, (0, True): 3923, (1, False): 4968, (1, True): 3684, (2, False): 5168,
+         (2, True): 3904}
 # the same for the 8th-order kernels (five ghost layers), with Kreiss-Oliger
 # dissipation as the production head-on numerics run them
-F_ALG8_KO = {(0, False): 11510, (0, True): 8220, (1, False): 11032, (1, True): 7736, (2, False): 11315,
-             (2, True): 8025}
+F_ALG8_KO = {(0, False): 9453, (0, True): 5924, (1, False): 9234, (1, True): 5685, (2, False): 9434,
+             (2, True): 5905}
 
 
 def two_planes(coord, N):
@@ -138,16 +138,16 @@ def roofline(kernel, flops_per_point, points, launch_s, traffic, probe=None):
     return out
 
 
-def kernel_name(coord, N, ko=False, nghosts=3, waves=1, tile=None):
-    """The right-hand-side kernel the library launches for this grid, tile
-    and mode: with row tiles (lx = 6) the one-wave kernel reads phase-1
-    stencils from an LDS stage (last template argument) at 4th order, and
-    at 8th order on two-phi-plane grids."""
+def kernel_name(coord, N, ko=False, nghosts=3, tile=None):
+    """The right-hand-side kernel the library launches for this grid and
+    tile: with the default tile (lx = 6) the one that brings its stencils
+    through LDS patches (last template argument; k_rhs_planes8 at 8th order
+    with more than two phi planes)."""
     ax = two_planes(coord, N)
     b = lambda v: "true" if v else "false"
-    if waves == 2:
-        return "k_rhs_pair<%d,%s,%s,%d>" % (coord, b(ax), b(ko), nghosts)
-    staged = tile is not None and tile[0] == 6 and (nghosts == 3 or ax)
+    staged = tile is not None and tile[0] == 6
+    if staged and nghosts == 5 and not ax:
+        return "k_rhs_planes8<%d,%s>" % (coord, b(ko))
     return "k_rhs_fused<%d,%s,%s,%d,%s>" % (coord, b(ax), b(ko), nghosts, b(staged))
 
 
@@ -486,8 +486,7 @@ def run_tiny(capi, wl, stream, steps, warmup):
     capi.set_initial_data_brill_lindquist(g.h, w["masses"], w["positions"], y, stream=stream)
     for _ in range(warmup):
         capi.rk4_step(g.h, y, ws, g.dt, eta=w["eta"], stream=stream)
-    # tile shape and waves per tile: on this grid's 16 tiles two waves per
-    # tile (each on its own SIMD) shorten the right-hand side
+    # tile shape by timing
     capi.grid_tune(g.h, y, g.state(), eta=w["eta"], stream=stream)
     ev = events(steps + 1)
     t0 = time.perf_counter()
@@ -690,7 +689,7 @@ def main():
 
     # the committed counters are those of the one-wave kernel
     waves = capi.grid_get_waves_per_tile(g.h)
-    traffic = measured_traffic(args.workload, tile) if waves == 1 else None
+    traffic = measured_traffic(args.workload, tile)
     out = {
         "metric": METRIC,
         "value": n_int * args.steps / elapsed,
@@ -714,7 +713,7 @@ def main():
                            "event pair per step",
                     "timed_chunks_ms_per_step": chunk_ms},
         "finite": finite,
-        "roofline": roofline(kernel_name(w["coord"], w["N"], waves=waves, tile=capi.grid_get_tile(g.h)),
+        "roofline": roofline(kernel_name(w["coord"], w["N"], tile=capi.grid_get_tile(g.h)),
                              f_alg(w["coord"], w["N"]), n_int, rhs_s,
                              traffic,
                              probe),

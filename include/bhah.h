@@ -295,39 +295,30 @@ int bhah_constraints(const bhah_grid* g, const double* y, double* H, double* M,
  * bhah_rk4_step, bhah_ssprk3_step, bhah_evolve): 64 points, 2^lx along i0,
  * 2^ly along i1, 64 >> (lx + ly) along i2, walked in bands of `band` tile
  * rows of i1. The extent along phi (i1 on SinhCylindrical grids, i2
- * otherwise) must be 1. Default (6, 0, 4). The shape changes speed only:
- * every point's arithmetic is the same, and with one wave per tile the
- * results are bitwise equal across shapes. With row tiles (lx = 6) the one-wave kernel brings
- * stencil rows shared by the tile's points into LDS with a few wide loads
- * (at 4th order; at 8th order on two-phi-plane grids without
- * dissipation). Setting a shape keeps the number of waves per tile
- * (below).                                                                  */
+ * otherwise) must be 1. Default (6, 0, 4). The shape changes speed only: the
+ * results are bitwise equal across shapes. With lx = 6 the kernel brings its
+ * stencils through LDS and is free to take the 64 points as a compact patch
+ * (16 along i0 by 4 along the other non-phi direction; band then counts rows
+ * of such patches): the fastest form. With any other lx each point reads its
+ * own stencil with tiles of exactly that shape. Setting a shape keeps the
+ * number of waves per tile (below).                                         */
 int bhah_grid_set_tile(bhah_grid* g, int lx, int ly, int band);
 int bhah_grid_get_tile(const bhah_grid* g, int* lx, int* ly, int* band);
 
-/* Waves per tile of this grid's right-hand-side kernel: 1 (default: one
- * wave computes all of a point's right-hand sides) or 2 (two waves of one
- * block share each point, one the metric part of Eqs. 7-15 with the Ricci
- * tensor of Eq. 12, the other the gauge part, exchanging intermediates
- * through LDS; each wave runs on its own SIMD). Two waves shorten a step on
- * grids with at most half as many tiles as the device has SIMDs; the
- * results agree with one wave to rounding (the sums are grouped
- * differently), not bit for bit. The two-wave kernel exists at 4th order
- * (nghosts = 3) without dissipation for every family and phi extent except
- * the general SinhSpherical one, and with dissipation for SinhCylindrical
- * grids of two phi planes; elsewhere the one-wave kernel runs whatever this
- * is set to. Any value other than 1 or 2 gets BHAH_EINVAL. The ensemble
- * engine and the server always use one wave per tile.                       */
+/* Waves per tile of this grid's right-hand-side kernel: 1 (default) or 2.
+ * The setting is kept and reported; every kernel runs a tile with two waves
+ * (one the metric part of Eqs. 7-15 with the Ricci tensor of Eq. 12, the
+ * other the gauge part, exchanging intermediates through LDS), so neither
+ * results nor speed depend on it. Any value other than 1 or 2 gets
+ * BHAH_EINVAL.                                                              */
 int bhah_grid_set_waves_per_tile(bhah_grid* g, int waves);
 int bhah_grid_get_waves_per_tile(const bhah_grid* g, int* waves);
 
 /* Time every allowed tile shape for this grid on state y (valid ghosts),
- * with one and with two waves per tile, writing right-hand sides into rhs
- * (state layout, caller-owned scratch), after a few warm-up launches, in
- * two passes; keep the first candidate within 2% of the fastest, one-wave
- * shapes before two-wave ones and larger extents along i0 first (so two
- * waves are chosen only when more than 2% faster than every one-wave
- * shape). Synchronises stream.                                              */
+ * writing right-hand sides into rhs (state layout, caller-owned scratch),
+ * after a few warm-up launches, in two passes; keep the first candidate
+ * within 2% of the fastest, larger extents along i0 first. The number of
+ * waves per tile becomes 1. Synchronises stream.                            */
 int bhah_grid_tune(bhah_grid* g, const bhah_gauge_params* gp, const double* y,
                    double* rhs, void* stream);
 
@@ -386,8 +377,8 @@ int bhah_batch_set_graph_steps(bhah_batch* b, int steps);
 int bhah_batch_set_integrator(bhah_batch* b, int integrator);
 
 /* Launch shape of the right-hand-side kernel: blocks_per_cu > 0 runs that
- * many persistent 64-lane blocks per compute unit striding over the work
- * list (default 4: one wave per SIMD); 0 launches one block per tile.       */
+ * many persistent two-wave blocks per compute unit striding over the work
+ * list (default 4: two waves per SIMD); 0 launches one block per tile.       */
 int bhah_batch_set_blocks_per_cu(bhah_batch* b, int blocks_per_cu);
 
 typedef struct {
@@ -422,7 +413,9 @@ int bhah_batch_set_launch_tuning(bhah_batch* b, int on);
 
 /* Tile choice for job j's size class: log2 extents along i0 and i1 (the
  * extent along i2 is 64 >> (lx + ly)) and band (tile rows of i1 walked
- * together). Defaults (6, 0, 4) before the class is tuned.                  */
+ * together). Defaults (6, 0, 4) before the class is tuned. The ensemble
+ * kernels bring every stencil through LDS on 16 x 4 patches (as the solo
+ * kernel with lx = 6), so of a choice only the band matters.                */
 int bhah_batch_get_tile(const bhah_batch* b, int j, int* lx, int* ly, int* band);
 
 void bhah_batch_destroy(bhah_batch* b);

@@ -129,7 +129,7 @@ int check_gauge(const bhah_gauge_params* gp, const char* who);
 // walked in bands of `band` tile rows of i1.
 struct TileCfg {
   int lx, ly, band;
-  int waves = 1;  // waves per 64-point tile of the solo kernel: 1 (rhs_fused.hip) or 2 (rhs_pair.hip)
+  int waves = 1;  // as set by bhah_grid_set_waves_per_tile (1 or 2); no kernel depends on it
 };
 
 // The stencil code reads the periodic direction (phi: i1 on SinhCylindrical
@@ -268,17 +268,14 @@ int launch_brill_lindquist(const GridDev& G, int n, const double* m, const doubl
 void launch_rhs_fused(const GridDev& G, const Gauge& ga, const double* y, double* aux, const StageArgs& st,
                       hipStream_t s, const TileCfg& cfg);
 TileMap make_tilemap(const GridDev& G, int lx, int ly, int band);
-// the right-hand side with two waves per tile (rhs_pair.hip); same
-// arguments and results as the one-wave kernel, to rounding; built for the
-// variants have_rhs_pair reports
-bool have_rhs_pair(const GridDev& G, bool ko);
-void launch_rhs_pair(const GridDev& G, const Gauge& ga, const double* y, double* aux, const StageArgs& st,
-                     hipStream_t s, const TileMap& T);
-// mix: the stages may combine two states (SSPRK3); RK4 stages never do.
+// the tile map of the kernels that bring their stencils through LDS patches
+// (rhs_stencil.h): 16 points along i0 by 4 along the other non-periodic
+// direction
+TileMap make_staged_tilemap(const GridDev& G, int band);
 // counts (device, one int per job; NULL: every job) and kk: step kk of a
 // graph launch runs only the jobs with kk < counts[job].
 void launch_rhs_batch(int variant, const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,
-                      const int* counts, int kk, const Gauge& ga, bool mix, int blocks, hipStream_t s);
+                      const int* counts, int kk, const Gauge& ga, int blocks, hipStream_t s);
 // last: the last stage of step kk (a job at its last active step then
 // fills all its ghosts)
 void launch_ghosts_batch(const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage, const int* counts,

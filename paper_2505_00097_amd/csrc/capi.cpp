@@ -377,15 +377,7 @@ int bhah_grid_tune(bhah_grid* g, const bhah_gauge_params* gp, const double* y, d
   }
   const StageArgs st{rhs, nullptr, nullptr, 0.0, nullptr, nullptr, 0.0};
   const SizeClass cls{g->params.coord, g->params.N[0], g->params.N[1], g->params.N[2]};
-  // every tile shape with one wave per tile, then the same shapes with two
-  // (the two-wave kernel wins only where the grid leaves SIMDs idle)
-  std::vector<TileCfg> cand = tile_candidates(cls);
-  const size_t n1 = have_rhs_pair(g->dev, gauge_of(*gp).ko()) ? cand.size() : 0;
-  for (size_t i = 0; i < n1; i++) {
-    TileCfg c = cand[i];
-    c.waves = 2;
-    cand.push_back(c);
-  }
+  const std::vector<TileCfg> cand = tile_candidates(cls);
   // a few launches first (clocks and caches settle), then every candidate
   // timed in two passes; each keeps its better pass
   for (int r = 0; r < 8; r++) launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, g->tile);

@@ -100,7 +100,7 @@ int Engine::set_jobs(const std::vector<EngineJob>& jobs) {
 }
 
 // Blocks of the right-hand-side kernel: blocks_per_cu_ per compute unit
-// (the kernel runs one wave per SIMD, so 4 fill a CU) striding over the work
+// (blocks of two waves, two waves per SIMD, so 4 fill a CU) striding over the work
 // list, or with blocks_per_cu_ == 0 one block per tile of the current
 // capacity; always a multiple of the XCD count.
 int Engine::rhs_grid() const {
@@ -149,7 +149,7 @@ void Engine::build_blob(const std::vector<TileCfg>& cfg, const std::vector<int>&
   std::vector<TileMap> maps(jobs_.size());
   int nt = 0, nc = 0;
   for (int j = 0; j < (int)jobs_.size(); j++)
-    maps[j] = make_tilemap(jobs_[j].g->dev, cfg[j].lx, cfg[j].ly, cfg[j].band);
+    maps[j] = make_staged_tilemap(jobs_[j].g->dev, cfg[j].band);
   for (int j : sel) {
     nt += maps[j].ntiles * repeat;
     const JobLists l = lists_of(j);
@@ -273,7 +273,7 @@ int Engine::time_class(const SizeClass& c, const TileCfg& cfg, hipStream_t s, do
     if (class_of(jobs_[j].g) == c) {
       only.push_back(j);
       cfgs[j] = cfg;
-      tiles += make_tilemap(jobs_[j].g->dev, cfg.lx, cfg.ly, cfg.band).ntiles;
+      tiles += make_staged_tilemap(jobs_[j].g->dev, cfg.band).ntiles;
     }
   // time the class at full occupancy: repeat its tiles until every
   // persistent block slot sees several
@@ -299,11 +299,11 @@ int Engine::time_class(const SizeClass& c, const TileCfg& cfg, hipStream_t s, do
   const int reps = 3;
   const int blocks = rhs_grid();
   for (int v = 0; v < NVAR; v++)
-    if (used[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), false, blocks, s);
+    if (used[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), blocks, s);
   (void)hipEventRecord(e0, s);
   for (int r = 0; r < reps; r++)
     for (int v = 0; v < NVAR; v++)
-      if (used[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), false, blocks, s);
+      if (used[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), blocks, s);
   (void)hipEventRecord(e1, s);
   rc = check_hip(hipEventSynchronize(e1), "tile timing");
   float ms = 0.f;
@@ -324,6 +324,7 @@ int Engine::tune_missing(hipStream_t s) {
     double best = 1e300;
     TileCfg bc{6, 0, 1};
     for (const TileCfg& cfg : tile_candidates(c)) {
+      if (cfg.lx != 6) continue;  // the ensemble kernels stage every tile: only the band matters
       double us = 0.0;
       const int rc = time_class(c, cfg, s, &us);
       if (rc) return rc;
@@ -362,8 +363,7 @@ int Engine::capture(int nsteps, hipStream_t s, hipGraphExec_t* out) {
     for (int stage = 0; stage < nst; stage++) {
       for (int f = 0; f < NVAR; f++)
         if (fam_present_[f])
-          launch_rhs_batch(f, dj, dh, dt, stage, dn, k, gauge_of(gp_), integrator_ == BHAH_SSPRK3, rhs_blocks_,
-                           cap_stream_);
+          launch_rhs_batch(f, dj, dh, dt, stage, dn, k, gauge_of(gp_), rhs_blocks_, cap_stream_);
       // outer points of radiation-boundary jobs, before their inner ghosts are copied
       if (fam_present_[NVAR]) launch_radiation_batch(dj, dh, dc, stage, dn, k, ghost_blocks_, cap_stream_);
       launch_ghosts_batch(dj, dh, dc, stage, dn, k, stage == nst - 1, ghost_blocks_, cap_stream_);

@@ -1,0 +1,960 @@
+// rhs_point.h -- the full BSSN + gauge right-hand side (Eqs. 7-15 with the
+// conformal Ricci tensor of Eq. 12, arXiv:2505.00097) of one 64-point tile by
+// two cooperating waves of one block, with the Runge-Kutta stage combination
+// as epilogue.
+//
+// Lane l of both waves holds the same point.
+//   metric wave: the stencils of h_ij; the inverse metric, Delta, the Ricci
+//     tensor and what d_k (Dbar_j beta^j) needs of gammabar; after the
+//     barrier Eqs. 7 and 8. It stores h_ij and a_ij.
+//   gauge wave: the stencils of W, alpha, vet^i, lambda^i and K and the
+//     advection of B^i and a_ij; after the barrier Eqs. 9, 10, 11, 13, 14, 15.
+//     It stores the other twelve.
+// What bounds it: the latency of a wave's own loads, LDS reads and arithmetic,
+// so the aim is two waves per SIMD, each within 256 registers and half of
+// 40 KB of LDS (four blocks, eight waves, per CU); on large grids the LDS and
+// vector memory pipes come next (44% and 35% busy on the 3-D grid). The split
+// keeps about 60 values per point in each wave; what the waves exchange and
+// the stencil stages share 80 LDS slots per point (slot v of lane l at
+// xs[v * 64 + l]). One wave per tile and SIMD with the algebra in coordinate
+// components took 19.2 us for a right-hand side on the 128 x 2 x 256 head-on
+// grid, 954 us on a 256 x 128 x 64 one and 2.44 ms there at 8th order with
+// dissipation; this form takes 14.0 us, 690 us and 1.58 ms.
+#pragma once
+
+#include "rhs_stencil.h"
+
+namespace bhah {
+
+enum {
+  // metric -> gauge
+  X_DEL = 0,   // 18 Delta^k_ij at X_DEL + 6 k + sy(i, j)
+  X_DU = 18,   // 3  Delta^k
+  X_PSI = 21,  // 3  psi_m = 1/2 gammabar^ab e_m h_ab = Delta^k_km
+  X_Q = 24,    // 3  v^m d_k d_m psi in frame scaling
+  // gauge -> metric
+  X_V = 27,    // 9  e_k vet^i at X_V + 3 k + i
+  X_L = 36,    // 9  e_k lambda^i at X_L + 3 k + i
+  X_Y = 45,    // 6  second-derivative terms of alpha and W in Eq. 8
+  X_U = 51,    // 3  2 alpha phi_k + alpha_k
+  X_A = 54,    // 6  advection (and dissipation) of a_ij
+  X_PARK = 60,   // the metric wave's park during its stencils, below the gauge wave's stencil stage
+  X_SLOTS = 80,
+  // results (12 per wave) take slots that neither wave reads any more
+  R_METRIC = X_V, R_GAUGE = X_PARK
+};
+
+// Stencil stages: the metric wave's takes slots 0.. (its exchange slots, which
+// it writes only after its stencils), the gauge wave's the last ones. The
+// metric wave parks e_k h_ij and the advection of h_ij in what is left.
+template <bool AX, int H>
+struct Stage {
+  static constexpr int PER = AX && H == 3 ? 2 : 1;  // gridfunctions per batch of loads on two-plane grids
+  static constexpr int N = AX ? PER * Patch<H>::MAIN : Patch<H>::MAIN + Patch<H>::PAIR;
+  static constexpr int SL = (N + 63) / 64, GAUGE = X_SLOTS - SL, LOW = X_V - SL;
+  static constexpr int CAP = LOW + GAUGE - X_PARK;  // park slots
+  static_assert(LOW >= 0 && GAUGE >= X_PARK, "stages");
+  static constexpr int park(int i) { return i < LOW ? SL + i : X_PARK + i - LOW; }
+};
+
+// what both waves derive from the point: frame, scales, upwind coefficients
+template <int H>
+struct Coefs {
+  double s1[3];  // e_k f = s1[k] * (den1 D f)
+  double ch[3], q[3], qg[3];  // advection and dissipation: ch A + q K (metric strength), qg (gauge strength)
+  double kw[3];
+  // f_kl = sc(k, l) * raw second difference
+  __device__ __forceinline__ double sc(int k, int l) const {
+    constexpr double r = FdW<H - 1>::den1 * FdW<H - 1>::den1 / FdW<H - 1>::den2;
+    return k == l ? s1[k] * s1[k] * r : s1[k] * s1[l];
+  }
+};
+template <bool KO, int H>
+__device__ __forceinline__ void make_coefs(const GridDev& G, const Gauge& ga, const double (&iS)[3],
+                                           const double (&v)[3], Coefs<H>& c) {
+  constexpr int R = H - 1;
+  using W = FdW<R>;
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    c.s1[k] = iS[k] * (G.inv_dx[k] * (1.0 / W::den1));
+    const double b = v[k] * c.s1[k];
+    c.ch[k] = 0.5 * b;
+    c.q[k] = c.qg[k] = UpW<R>::sk * fabs(b);
+    if constexpr (KO) {
+      c.kw[k] = G.inv_dx[k] * (1.0 / W::kden);
+      c.qg[k] = fma(ga.dg, c.kw[k], c.q[k]);
+      c.q[k] = fma(ga.dm, c.kw[k], c.q[k]);
+    }
+  }
+}
+
+template <int H>
+__device__ __forceinline__ double advect(const AxisSums (&s)[3], const double (&ch)[3], const double (&q)[3]) {
+  double a = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; k++) a = fma(ch[k], s[k].A, fma(q[k], s[k].K, a));
+  return a;
+}
+
+// ---- stencil drivers ---------------------------------------------------------
+// Runs over the gridfunctions list[0..N): for each, fn(t, axis sums
+// along the three directions, raw second differences dd[sy(k, l)]); dd is
+// formed for t in [F0, F1), first derivatives are used for t in [F0, F2).
+// Identically vanishing phi derivatives of two-plane
+// grids are literal zeros. The arithmetic is the same for both sources.
+// whether d_k d_l, kl = sy(k, l), vanishes identically (mixed with phi on two planes)
+template <bool AX, int PD>
+__device__ __forceinline__ constexpr bool zero_pair(int kl) {
+  return AX && (kl == sy(0, PD) || kl == sy(3 - PD, PD));
+}
+template <int R>
+__device__ __forceinline__ double acc_pair(int j, double acc, double p, double m) {
+  return j == 1 ? FdW<R>::d1[1] * (p - m) : fma(FdW<R>::d1[j], p - m, acc);
+}
+
+template <int C, bool AX, int H, int F0, int F1, int F2, int N, class FN>
+__device__ __forceinline__ void run_stencils(const StagedSrc<H>& S, const int (&list)[N], const FN& fn) {
+  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
+  using SS_ = StagedSrc<H>;
+  auto in_plane = [&](int slot, bool full, bool first, AxisSums(&s)[3], double (&dd)[6], double& c) BHAH_INLINE {
+    double v0[2 * H + 1], vE[2 * H + 1];
+#pragma unroll
+    for (int m = -H; m <= H; m++) {
+      v0[H + m] = S.main_at(slot, m, 0);
+      vE[H + m] = m == 0 ? v0[H] : S.main_at(slot, 0, m);
+    }
+    c = v0[H];
+    s[0] = axis_sums<R>(v0);
+    s[E] = axis_sums<R>(vE);
+    pin(s[0], first, full);
+    pin(s[E], first, full);
+    if (full) {
+      if constexpr (H == 5) BHAH_PHASE_BARRIER();
+      double e[2 * R + 1];
+      e[R] = 0.0;
+#pragma unroll
+      for (int m = -R; m <= R; m++)
+        if (m != 0) {
+          double r[2 * R + 1];
+          r[R] = 0.0;
+#pragma unroll
+          for (int n = -R; n <= R; n++)
+            if (n != 0) r[R + n] = S.main_at(slot, n, m);
+          e[R + m] = d1_sum<R>(r);
+          pin(e[R + m]);
+          if constexpr (H == 5) BHAH_PHASE_BARRIER();
+        }
+      dd[sy(0, E)] = d1_sum<R>(e);
+      pin(dd[sy(0, E)]);
+    }
+  };
+  if constexpr (AX) {
+    constexpr int PER = Stage<AX, H>::PER, NB = (N + PER - 1) / PER;
+    typename SS_::MainRegs m[PER];
+    double ph[PER];
+    auto issue = [&](int b) {
+#pragma unroll
+      for (int t = 0; t < PER; t++)
+        if (b * PER + t < N) {
+          S.issue_main(list[b * PER + t], m[t]);
+          ph[t] = S.column(list[b * PER + t], 1);
+        }
+    };
+    issue(0);
+    static_for<NB>([&](auto bc) BHAH_INLINE {
+      constexpr int b = decltype(bc)::value;
+      double o[PER];
+#pragma unroll
+      for (int t = 0; t < PER; t++)
+        if (b * PER + t < N) {
+          S.commit_main(m[t], t);
+          o[t] = ph[t];
+        }
+      if constexpr (b + 1 < NB) issue(b + 1);
+      BHAH_PHASE_BARRIER();
+      static_for<PER>([&](auto tc) BHAH_INLINE {
+        constexpr int t = decltype(tc)::value, tt = b * PER + t;
+        if constexpr (tt < N) {
+          AxisSums s[3];
+          double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
+          in_plane(t, tt >= F0 && tt < F1, tt >= F0 && tt < F2, s, dd, c);
+          s[PD] = axis_sums_two_planes<R>(c, o[t]);
+#pragma unroll
+          for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
+          fn(tt, s, dd);
+        }
+      });
+    });
+  } else {
+    constexpr int PB = SS_::PG::MAIN;  // the phi planes' place in the stage
+    // Loads run one gridfunction ahead of their use. At 8th order, where a
+    // gridfunction has four pairs of phi planes, one pair and then the next
+    // main patch: more in flight spills (3-D production step 6.0 instead of
+    // 5.2 ms); at 4th order deeper prefetch measures the same.
+    constexpr int PS = H == 3 ? 2 : 1;
+    typename SS_::MainRegs m;
+    typename SS_::PairRegs pr[PS];
+    double col[2 * H];  // phi offsets -H..-1, 1..H
+    auto issue = [&](auto tc) BHAH_INLINE {
+      constexpr int t = decltype(tc)::value;
+      if constexpr (t < N) {
+        S.issue_main(list[t], m);
+#pragma unroll
+        for (int o = 1; o <= H; o++)
+          if (o == H || !(t >= F0 && t < F1)) {
+            col[H - o] = S.column(list[t], -o);
+            col[H + o - 1] = S.column(list[t], o);
+          }
+      }
+    };
+    issue(std::integral_constant<int, 0>{});
+    if constexpr (F0 == 0) {
+#pragma unroll
+      for (int j = 1; j <= PS; j++) S.issue_pair(list[0], j, pr[j - 1]);
+    }
+    static_for<N>([&](auto tc) BHAH_INLINE {
+      constexpr int t = decltype(tc)::value;
+      constexpr bool full = t >= F0 && t < F1;
+      double vP[2 * H + 1];
+      S.commit_main(m, 0);
+#pragma unroll
+      for (int o = 1; o <= H; o++)
+        if (o == H || !full) {
+          vP[H - o] = col[H - o];
+          vP[H + o] = col[H + o - 1];
+        }
+      if constexpr (H == 3 || !full) issue(std::integral_constant<int, t + 1>{});
+      // the first pairs: a gridfunction early, at 8th order with their own main patch
+      if constexpr (H == 3 ? t + 1 == F0 : full && t > 0) {
+#pragma unroll
+        for (int j = 1; j <= PS; j++) S.issue_pair(list[H == 3 ? F0 : t], j, pr[j - 1]);
+      }
+      BHAH_PHASE_BARRIER();
+      AxisSums s[3];
+      double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
+      in_plane(0, full, t >= F0 && t < F2, s, dd, c);
+      vP[H] = c;
+      if constexpr (full) {
+        double a0 = 0.0, aE = 0.0;
+        static_for<R>([&](auto jc) BHAH_INLINE {
+          constexpr int j = decltype(jc)::value + 1;
+          S.commit_pair(pr[(j - 1) % PS], PB);
+          if constexpr (j + PS <= R) S.issue_pair(list[t], j + PS, pr[(j - 1) % PS]);
+          else if constexpr (H == 3 && t + 1 < F1) S.issue_pair(list[t + 1], j + PS - R, pr[(j - 1) % PS]);
+          if constexpr (H == 5 && j == R) issue(std::integral_constant<int, t + 1>{});
+          BHAH_PHASE_BARRIER();
+          double e0[2], eE[2];
+#pragma unroll
+          for (int side = 0; side < 2; side++) {
+            double r0[2 * R + 1], rE[2 * R + 1];
+            r0[R] = rE[R] = 0.0;
+#pragma unroll
+            for (int n = -R; n <= R; n++)
+              if (n != 0) {
+                r0[R + n] = S.pair_at(PB, side, n, 0);
+                rE[R + n] = S.pair_at(PB, side, 0, n);
+              }
+            e0[side] = d1_sum<R>(r0);
+            eE[side] = d1_sum<R>(rE);
+            vP[side ? H - j : H + j] = S.pair_at(PB, side, 0, 0);
+          }
+          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
+          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
+          pin(a0);
+          pin(aE);
+          BHAH_PHASE_BARRIER();
+        });
+        dd[sy(0, PD)] = a0;
+        dd[sy(E, PD)] = aE;
+      }
+      s[PD] = axis_sums<R>(vP);
+      pin(s[PD], t >= F0 && t < F2, full);
+#pragma unroll
+      for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
+      fn(t, s, dd);
+    });
+  }
+}
+
+template <int C, bool AX, int H, int F0, int F1, int F2, int N, class FN>
+__device__ __forceinline__ void run_stencils(const GatherSrc<H>& S, const int (&list)[N], const FN& fn) {
+  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
+  static_for<N>([&](auto tc) BHAH_INLINE {
+    constexpr int t = decltype(tc)::value;
+    const int g = list[t];
+    double v0[2 * H + 1], vE[2 * H + 1], vP[2 * H + 1];
+#pragma unroll
+    for (int m = -H; m <= H; m++) {
+      v0[H + m] = S.at(g, m, 0, 0);
+      vE[H + m] = m == 0 ? v0[H] : S.at(g, 0, m, 0);
+      if constexpr (!AX) vP[H + m] = m == 0 ? v0[H] : S.at(g, 0, 0, m);
+    }
+    if constexpr (AX) vP[H + 1] = S.at(g, 0, 0, 1);
+    AxisSums s[3];
+    double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (t >= F0 && t < F1) {
+      double x[4 * R * R];  // f at (n, m) along (i0, e)
+#pragma unroll
+      for (int m = -R; m <= R; m++)
+#pragma unroll
+        for (int n = -R; n <= R; n++)
+          if (m != 0 && n != 0) x[2 * R * xo<R>(m) + xo<R>(n)] = S.at(g, n, m, 0);
+      BHAH_PHASE_BARRIER();
+      double e[2 * R + 1];
+      e[R] = 0.0;
+#pragma unroll
+      for (int m = -R; m <= R; m++)
+        if (m != 0) {
+          double r[2 * R + 1];
+          r[R] = 0.0;
+#pragma unroll
+          for (int n = -R; n <= R; n++)
+            if (n != 0) r[R + n] = x[2 * R * xo<R>(m) + xo<R>(n)];
+          e[R + m] = d1_sum<R>(r);
+        }
+      dd[sy(0, E)] = d1_sum<R>(e);
+      pin(dd[sy(0, E)]);
+      if constexpr (!AX) {
+        double a0 = 0.0, aE = 0.0;
+#pragma unroll
+        for (int j = 1; j <= R; j++) {
+          double e0[2], eE[2];
+#pragma unroll
+          for (int side = 0; side < 2; side++) {
+            double r0[2 * R + 1], rE[2 * R + 1];
+            r0[R] = rE[R] = 0.0;
+#pragma unroll
+            for (int n = -R; n <= R; n++)
+              if (n != 0) {
+                r0[R + n] = S.at(g, n, 0, side ? -j : j);
+                rE[R + n] = S.at(g, 0, n, side ? -j : j);
+              }
+            e0[side] = d1_sum<R>(r0);
+            eE[side] = d1_sum<R>(rE);
+          }
+          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
+          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
+          pin(a0);
+          pin(aE);
+        }
+        dd[sy(0, PD)] = a0;
+        dd[sy(E, PD)] = aE;
+      }
+    }
+    BHAH_PHASE_BARRIER();
+    s[0] = axis_sums<R>(v0);
+    s[E] = axis_sums<R>(vE);
+    if constexpr (AX) s[PD] = axis_sums_two_planes<R>(v0[H], vP[H + 1]);
+    else s[PD] = axis_sums<R>(vP);
+#pragma unroll
+    for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
+    fn(t, s, dd);
+    BHAH_PHASE_BARRIER();
+  });
+}
+
+// ---- epilogue: the right-hand side or the Runge-Kutta stage combination -------
+// of the wave's twelve gridfunctions list[], results in park[(i) * 64].
+// Every base value is read before any result is stored. Within a stage the
+// arrays never overlap (RK4: base1 is y or Cacc, out1 is A, B or y; base2 and
+// out2 are Cacc at the same point; SSPRK3 mixes y with A or B into B or y),
+// but the compiler cannot know it and would otherwise put each load behind
+// the stores before it.
+// Row pairs: where all 64 lanes are live and lanes 2p, 2p+1 hold adjacent
+// points of one row, lane l takes points 2p and 2p+1, p = l mod 32, of
+// gridfunction list[2 i + l / 32], one 16-byte access for two gridfunctions
+// and two points: half the vector memory instructions of the per-lane form.
+typedef double bhah_d2 __attribute__((ext_vector_type(2), aligned(8)));
+
+__device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs& st, unsigned q, bool live,
+                                               const int (&list)[12], const double* __restrict__ park, int lane) {
+  const bool two = st.out2 != nullptr, mix = !two && st.base2 != nullptr, same = st.base2 == st.base1;
+  auto out1m = [&](double k, double x1, double x2) { return fma(st.c1, k, fma(st.m2, x2, st.m1 * x1)); };
+  const int p2 = 2 * (lane & 31), gs = lane >> 5;
+  const unsigned qa = (unsigned)__shfl((int)q, p2), qb = (unsigned)__shfl((int)q, p2 + 1);
+  if (__all(live && qb == qa + 1u)) {
+    const double* pk = park - lane + p2 + gs * 64;  // result 2 i + gs of point p2 at pk[128 i]
+    long long e[6];
+#pragma unroll
+    for (int i = 0; i < 6; i++) e[i] = (gs ? list[2 * i + 1] : list[2 * i]) * G.sgf + (long long)qa;
+    if (st.rhs) {
+#pragma unroll
+      for (int i = 0; i < 6; i++) *(bhah_d2*)(st.rhs + e[i]) = bhah_d2{pk[128 * i], pk[128 * i + 1]};
+      return;
+    }
+    bhah_d2 b1[6], b2[6];
+#pragma unroll
+    for (int i = 0; i < 6; i++) b1[i] = *(const bhah_d2*)(st.base1 + e[i]);
+    if ((two || mix) && !same) {
+#pragma unroll
+      for (int i = 0; i < 6; i++) b2[i] = *(const bhah_d2*)(st.base2 + e[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 6; i++) b2[i] = b1[i];
+    }
+    BHAH_PHASE_BARRIER();
+    if (mix) {
+#pragma unroll
+      for (int i = 0; i < 6; i++)
+        *(bhah_d2*)(st.out1 + e[i]) =
+            bhah_d2{out1m(pk[128 * i], b1[i].x, b2[i].x), out1m(pk[128 * i + 1], b1[i].y, b2[i].y)};
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < 6; i++)
+      *(bhah_d2*)(st.out1 + e[i]) =
+          bhah_d2{fma(st.c1, pk[128 * i], b1[i].x), fma(st.c1, pk[128 * i + 1], b1[i].y)};
+    if (two) {
+#pragma unroll
+      for (int i = 0; i < 6; i++)
+        *(bhah_d2*)(st.out2 + e[i]) =
+            bhah_d2{fma(st.c2, pk[128 * i], b2[i].x), fma(st.c2, pk[128 * i + 1], b2[i].y)};
+    }
+    return;
+  }
+  if (!live) return;
+  if (st.rhs) {
+#pragma unroll
+    for (int i = 0; i < 12; i++) st.rhs[list[i] * G.sgf + q] = park[i * 64];
+    return;
+  }
+  double b1[12], b2[12];
+#pragma unroll
+  for (int i = 0; i < 12; i++) b1[i] = st.base1[list[i] * G.sgf + q];
+  if ((two || mix) && !same) {
+#pragma unroll
+    for (int i = 0; i < 12; i++) b2[i] = st.base2[list[i] * G.sgf + q];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 12; i++) b2[i] = b1[i];
+  }
+  BHAH_PHASE_BARRIER();
+  if (mix) {
+#pragma unroll
+    for (int i = 0; i < 12; i++) st.out1[list[i] * G.sgf + q] = out1m(park[i * 64], b1[i], b2[i]);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 12; i++) st.out1[list[i] * G.sgf + q] = fma(st.c1, park[i * 64], b1[i]);
+  if (two) {
+#pragma unroll
+    for (int i = 0; i < 12; i++) st.out2[list[i] * G.sgf + q] = fma(st.c2, park[i * 64], b2[i]);
+  }
+}
+
+// the point of a lane and the tile it belongs to
+struct TilePoint {
+  int t0, t1, t2, i0, i1, i2;
+  unsigned q;
+  bool live;
+};
+
+template <class SRC, int C, bool AX, int H>
+__device__ __forceinline__ SRC make_source(const double* y, const GridDev& G, const TilePoint& p, int lane,
+                                           double* lds) {
+  constexpr bool cyl = C == BHAH_SINH_CYLINDRICAL;
+  if constexpr (SRC::STG) {
+    SRC S;
+    if (cyl) S.init(y, G, 1, p.t0, p.t2, p.i0, p.i2, p.t1, lane, lds, AX);
+    else S.init(y, G, 2, p.t0, p.t1, p.i0, p.i1, p.t2, lane, lds, AX);
+    return S;
+  } else {
+    return SRC{PtT<H>(y, G, C, p.i0, p.i1, p.i2), cyl ? 1 : 2};
+  }
+}
+
+// ---- metric wave ---------------------------------------------------------------
+template <int C, bool AX, bool KO, int H, class SRC>
+__device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
+                                            const StageArgs& st, const TilePoint& p, double* __restrict__ aux,
+                                            double* __restrict__ xs0, int lane) {
+  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2;
+  double* xs = xs0 + lane;
+  auto put = [&](int v, double x) { xs[v * 64] = x; };
+  auto get = [&](int v) { return xs[v * 64]; };
+  auto at = [&](int g) { return gf_ld(y, G.sgf, g, p.q * 8u, 0); };
+  const SRC S = make_source<SRC, C, AX, H>(y, G, p, lane, xs0);
+  using ST = Stage<AX, H>;
+  double gU[6], Pc[6], ck[6], late[24];  // late: what the park cannot take
+  auto keep = [&](int i, double x) {
+    if (SRC::STG && i < ST::CAP) put(ST::park(i), x);
+    else late[i] = x;
+  };
+  auto kept = [&](int i) { return SRC::STG && i < ST::CAP ? get(ST::park(i)) : late[i]; };
+  {
+    Coefs<H> c;
+    double w[6], gd[6];
+    {
+      double h[6], v[3];
+#pragma unroll
+      for (int a = 0; a < 6; a++) h[a] = at(G_HDD00 + a);
+#pragma unroll
+      for (int i = 0; i < 3; i++) v[i] = at(G_VETU0 + i);
+      const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
+      metric_inverse(h, gU);
+      make_coefs<KO, H>(G, ga, F.iS, v, c);
+    }
+    doubled(gU, gd);
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+#pragma unroll
+      for (int l = k; l < 3; l++) w[sy(k, l)] = gd[sy(k, l)] * c.sc(k, l);
+#pragma unroll
+    for (int a = 0; a < 6; a++) { Pc[a] = 0.0; ck[a] = 0.0; }
+    constexpr int list[6] = {G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
+    //   Pc_ij = gammabar^kl h_ij,kl,  ck_kl = gammabar^ab h_ab,kl (unscaled)
+    run_stencils<C, AX, H, 0, 6, 6>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+#pragma unroll
+      for (int k = 0; k < 3; k++)
+        if (!(AX && k == PD)) keep(3 * a + k, c.s1[k] * s[k].d1);
+      keep(18 + a, advect<H>(s, c.ch, c.q));
+#pragma unroll
+      for (int kl = 0; kl < 6; kl++) {
+        Pc[a] = fma(w[kl], dd[kl], Pc[a]);
+        ck[kl] = fma(gd[a], dd[kl], ck[kl]);
+        if (!zero_pair<AX, PD>(kl)) pin(ck[kl]);
+      }
+      pin(Pc[a]);
+    });
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+#pragma unroll
+      for (int l = k; l < 3; l++) ck[sy(k, l)] *= c.sc(k, l);
+  }
+  BHAH_PHASE_BARRIER();
+  double h[6], v[3], adv[6], hk[3][6];
+#pragma unroll
+  for (int a = 0; a < 6; a++) {
+    h[a] = at(G_HDD00 + a);
+    adv[a] = kept(18 + a);
+#pragma unroll
+    for (int k = 0; k < 3; k++) hk[k][a] = AX && k == PD ? 0.0 : kept(3 * a + k);
+  }
+#pragma unroll
+  for (int i = 0; i < 3; i++) v[i] = at(G_VETU0 + i);
+  const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
+  BHAH_PHASE_BARRIER();
+  // psi = 1/2 ln det(gammabar/gammahat): psi_m = 1/2 gammabar^ab h_ab,m and
+  // v^m psi_km = 1/2 (v^m gammabar^ab h_ab,km - (gammabar^-1 v^m h_m gammabar^-1)^ab h_ab,k)
+  {
+    double gd[6], hb[6], M[3][3], N[6], Nd[6];
+    doubled(gU, gd);
+#pragma unroll
+    for (int m = 0; m < 3; m++) put(X_PSI + m, 0.5 * dot6(gd, hk[m]));
+#pragma unroll
+    for (int c = 0; c < 6; c++) hb[c] = fma(v[2], hk[2][c], fma(v[1], hk[1][c], v[0] * hk[0][c]));
+    raise_first(gU, hb, M);
+    raise_second(gU, M, N);
+    doubled(N, Nd);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      double s = v[0] * ck[sy(k, 0)];
+      s = fma(v[1], ck[sy(k, 1)], s);
+      s = fma(v[2], ck[sy(k, 2)], s);
+      put(X_Q + k, 0.5 * (s - dot6(Nd, hk[k])));
+    }
+  }
+  BHAH_PHASE_BARRIER();
+  double D[3][6];  // Dhat_k h_ij
+  cov_deriv<C, 6>(F, h, hk, D);
+  double Rc[6];
+  {
+    const Lower L = lower_terms<C>(F, gU);
+    add_lower<C, 6>(F, L, gU, h, hk, D, Pc);
+#pragma unroll
+    for (int c = 0; c < 6; c++) Rc[c] = -0.5 * Pc[c];
+  }
+  BHAH_PHASE_BARRIER();
+  double DU[3];
+  {
+    double gd[6];
+    doubled(gU, gd);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      double Dk[6];
+#pragma unroll
+      for (int c = 0; c < 6; c++) Dk[c] = 0.0;
+#pragma unroll
+      for (int l = 0; l < 3; l++) {
+        double low[6];
+        delta_lower(D, l, low);
+#pragma unroll
+        for (int c = 0; c < 6; c++) Dk[c] = fma(gU[sy(k, l)], low[c], Dk[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < 6; c++) put(X_DEL + 6 * k + c, Dk[c]);
+      DU[k] = dot6(gd, Dk);
+      put(X_DU + k, DU[k]);
+    }
+  }
+  BHAH_PHASE_BARRIER();
+  add_ricci_delta(gU, D, DU, [&](int k, int c) { return get(X_DEL + 6 * k + c); }, Rc);
+  double a6[6];
+#pragma unroll
+  for (int c = 0; c < 6; c++) a6[c] = at(G_ADD00 + c);
+  const double alpha = at(G_ALPHA), W = at(G_CF), K = at(G_TRK);
+  __syncthreads();
+
+  // ---- Lambdabar part of the Ricci tensor, Eq. 8's X_ij -------------------
+  {
+    double lam[3], lk[3][3], Dl[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) lam[i] = at(G_LAMU0 + i);
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+#pragma unroll
+      for (int i = 0; i < 3; i++) lk[k][i] = AX && k == PD ? 0.0 : get(X_L + 3 * k + i);
+    cov_deriv<C, 3>(F, lam, lk, Dl);
+    add_ricci_lambda(h, Dl, Rc);
+  }
+  if (aux && p.live) {
+#pragma unroll
+    for (int c = 0; c < 6; c++) aux[c * G.sgf + p.q] = Rc[c];
+    // Q_k = (d_k Gammabar^j_jm) beta^m in logical coordinates: beta^m d_k d_m
+    // of ln(S_0 S_1 S_2) + psi
+    const double* t0 = G.tab0 + p.i0 * TAB_W;
+    const double r1 = t0[1] * t0[4], l0 = t0[2] * t0[5];  // r'/r, r''/r'
+    const double n = C == BHAH_SINH_CYLINDRICAL ? 1.0 : 2.0;
+    double dl[3] = {t0[3] * t0[5] - l0 * l0 + n * (t0[2] * t0[4] - r1 * r1), 0.0, 0.0};
+    if constexpr (C == BHAH_SINH_CYLINDRICAL) {
+      const double* t2 = G.tab2 + p.i2 * TAB_W;
+      const double l2 = t2[2] * t2[5];
+      dl[2] = t2[3] * t2[5] - l2 * l2;
+    } else {
+      const double* t1 = G.tab1 + p.i1 * TAB_W;
+      dl[1] = -(t1[2] * t1[2]);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+      aux[(6 + k) * G.sgf + p.q] = v[k] * F.iS[k] * dl[k] + get(X_Q + k) / F.iS[k];
+  }
+  BHAH_PHASE_BARRIER();
+  double X[6], L[3][3], Dv[3][3], div = 0.0;
+#pragma unroll
+  for (int c = 0; c < 6; c++) X[c] = fma(alpha, Rc[c], get(X_Y + c));
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    const double u = get(X_U + k);
+#pragma unroll
+    for (int c = 0; c < 6; c++) X[c] = fma(get(X_DEL + 6 * k + c), u, X[c]);
+  }
+  {
+    double vk[3][3];
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+#pragma unroll
+      for (int i = 0; i < 3; i++) vk[k][i] = AX && k == PD ? 0.0 : get(X_V + 3 * k + i);
+    cov_deriv<C, 3>(F, v, vk, Dv);
+    lie_matrix<C>(F, v, vk, Dv, L);
+#pragma unroll
+    for (int k = 0; k < 3; k++) div = fma(get(X_PSI + k), v[k], div + Dv[k][k]);
+  }
+  double AUD[3][3], gd[6];
+  raise_first(gU, a6, AUD);
+  doubled(gU, gd);
+  const double trX3 = (1.0 / 3.0) * dot6(gd, X), W2 = W * W;
+  const double trA = AUD[0][0] + AUD[1][1] + AUD[2][2];
+  const double fA = fma(alpha, K, -(2.0 / 3.0) * div), fh = (2.0 / 3.0) * fma(alpha, trA, -div);
+  double ra[6], rh[6];
+#pragma unroll
+  for (int i = 0; i < 3; i++)
+#pragma unroll
+    for (int j = i; j < 3; j++) {
+      const int c = sy(i, j);
+      const double gb = i == j ? 1.0 + h[c] : h[c];
+      // Eq. 8
+      double AA = a6[sy(i, 0)] * AUD[0][j];
+      AA = fma(a6[sy(i, 1)], AUD[1][j], AA);
+      AA = fma(a6[sy(i, 2)], AUD[2][j], AA);
+      double r = fma(fA, a6[c], get(X_A + c));
+      r = fma(-2.0 * alpha, AA, r);
+      r = fma(W2, fma(-gb, trX3, X[c]), r);
+      add_lie(L, a6, i, j, r);
+      ra[c] = r;
+      // Eq. 7
+      r = fma(fh, gb, adv[c]) + (Dv[i][j] + Dv[j][i]);
+      r = fma(-2.0 * alpha, a6[c], r);
+      add_lie(L, h, i, j, r);
+      rh[c] = r;
+    }
+  BHAH_PHASE_BARRIER();
+#pragma unroll
+  for (int c = 0; c < 6; c++) {
+    put(R_METRIC + c, ra[c]);
+    put(R_METRIC + 6 + c, rh[c]);
+  }
+  constexpr int out[12] = {0, 1, 2, 3, 4, 5, G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
+  stage_epilogue(G, st, p.q, p.live, out, xs + R_METRIC * 64, lane);
+}
+
+// ---- gauge wave ------------------------------------------------------------------
+template <int C, bool AX, bool KO, int H, class SRC>
+__device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
+                                           const StageArgs& st, const TilePoint& p, double* __restrict__ xs0,
+                                           int lane) {
+  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2;
+  double* xs = xs0 + lane;
+  auto put = [&](int v, double x) { xs[v * 64] = x; };
+  auto get = [&](int v) { return xs[v * 64]; };
+  auto at = [&](int g) { return gf_ld(y, G.sgf, g, p.q * 8u, 0); };
+  const SRC S = make_source<SRC, C, AX, H>(y, G, p, lane, xs0 + Stage<AX, H>::GAUGE * 64);
+  double gU[6], Y[6], Za = 0.0, Bv[3], Bd[3], ak[3], phi[3], Kk[3];
+  double advW = 0.0, advAl = 0.0, advK = 0.0, advV[3], advL[3], advB[3], koL[3];
+#pragma unroll
+  for (int i = 0; i < 3; i++) { Bv[i] = 0.0; Bd[i] = 0.0; koL[i] = 0.0; }
+  const double alpha = at(G_ALPHA), W = at(G_CF);
+  {
+    Coefs<H> c;
+    double w[6];
+    {
+      double h[6], v[3];
+#pragma unroll
+      for (int a = 0; a < 6; a++) h[a] = at(G_HDD00 + a);
+#pragma unroll
+      for (int i = 0; i < 3; i++) v[i] = at(G_VETU0 + i);
+      const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
+      metric_inverse(h, gU);
+      make_coefs<KO, H>(G, ga, F.iS, v, c);
+    }
+    doubled(gU, w);
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+#pragma unroll
+      for (int l = k; l < 3; l++) w[sy(k, l)] *= c.sc(k, l);
+    const double iW = 1.0 / W, aW = alpha * iW;
+    // the gridfunctions with second derivatives come while few results wait in registers
+    constexpr int list[18] = {0, 1, 2, 3, 4, 5, G_VETU0, G_VETU0 + 1, G_VETU0 + 2, G_CF, G_ALPHA,
+                              G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2, G_TRK, G_BETU0, G_BETU0 + 1, G_BETU0 + 2};
+    run_stencils<C, AX, H, 6, 11, 15>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+      const bool gauge = (t >= 6 && t < 9) || t == 10 || t >= 15;
+      const double adv = gauge ? advect<H>(s, c.ch, c.qg) : advect<H>(s, c.ch, c.q);
+      double d[3];
+#pragma unroll
+      for (int k = 0; k < 3; k++) d[k] = AX && k == PD ? 0.0 : c.s1[k] * s[k].d1;
+      if (t < 6) {  // a_ij
+        put(X_A + t, adv);
+      } else if (t < 9) {  // vet^i
+        const int i = t - 6;
+        advV[i] = adv;
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+          if (!(AX && k == PD)) put(X_V + 3 * k + i, d[k]);
+#pragma unroll
+        for (int kl = 0; kl < 6; kl++) Bv[i] = fma(w[kl], dd[kl], Bv[i]);
+#pragma unroll
+        for (int k = 0; k < 3; k++) Bd[k] = fma(c.sc(k, i), dd[sy(k, i)], Bd[k]);
+        pin(Bv[i]);
+        pin(advV[i]);
+        pin(Bd[0]);
+        pin(Bd[3 - PD]);
+      } else if (t == 9) {  // W
+        advW = adv;
+#pragma unroll
+        for (int k = 0; k < 3; k++) phi[k] = (-0.5 * iW) * d[k];
+#pragma unroll
+        for (int kl = 0; kl < 6; kl++) {
+          Y[kl] = aW * dd[kl];
+          if (!zero_pair<AX, PD>(kl)) pin(Y[kl]);
+        }
+        pin(advW);
+      } else if (t == 10) {  // alpha
+        advAl = adv;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+          ak[k] = d[k];
+#pragma unroll
+          for (int l = k; l < 3; l++) {
+            const int kl = sy(k, l);
+            Y[kl] = (Y[kl] - dd[kl]) * c.sc(k, l);
+            Za = fma(w[kl], dd[kl], Za);
+            if (!zero_pair<AX, PD>(kl)) pin(Y[kl]);
+          }
+        }
+        pin(Za);
+        pin(advAl);
+      } else if (t < 14) {  // lambda^i
+        const int i = t - 11;
+        advL[i] = adv;
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+          if (!(AX && k == PD)) put(X_L + 3 * k + i, d[k]);
+        if constexpr (KO) {  // kept apart: B^i takes 3/4 of lambda^i's undissipated right-hand side
+          double o = 0.0;
+#pragma unroll
+          for (int k = 0; k < 3; k++) o = fma(c.kw[k], s[k].K, o);
+          koL[i] = ga.dm * o;
+          pin(koL[i]);
+        }
+        pin(advL[i]);
+      } else if (t == 14) {  // K
+        advK = adv;
+#pragma unroll
+        for (int k = 0; k < 3; k++) Kk[k] = d[k];
+        pin(advK);
+      } else {  // B^i
+        advB[t - 15] = adv;
+        pin(advB[t - 15]);
+      }
+    });
+  }
+  BHAH_PHASE_BARRIER();
+  double v[3], lam[3], bet[3];
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    v[i] = at(G_VETU0 + i);
+    lam[i] = at(G_LAMU0 + i);
+    bet[i] = at(G_BETU0 + i);
+  }
+  const double K = at(G_TRK);
+  const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
+  BHAH_PHASE_BARRIER();
+  {
+    // alpha W_ij/W - alpha_ij + its lower terms + 2 (alpha_i phi_j + alpha_j phi_i);
+    // the terms alpha W_i W_j / W^2 and 4 alpha phi_i phi_j of Eq. 8 cancel
+    double f[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      const double u = fma(2.0 * alpha, phi[k], ak[k]);
+      f[k] = -u;
+      put(X_U + k, u);
+    }
+    add_hessian_lower<C>(F, f, Y);
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+      for (int j = i; j < 3; j++) put(X_Y + sy(i, j), fma(2.0, fma(ak[i], phi[j], ak[j] * phi[i]), Y[sy(i, j)]));
+  }
+  double a6[6];
+#pragma unroll
+  for (int c = 0; c < 6; c++) a6[c] = at(G_ADD00 + c);
+  // gammabar^jk Dhat_j Dhat_k beta^i
+  double vk[3][3], Dv[3][3];
+#pragma unroll
+  for (int k = 0; k < 3; k++)
+#pragma unroll
+    for (int i = 0; i < 3; i++) vk[k][i] = AX && k == PD ? 0.0 : get(X_V + 3 * k + i);
+  cov_deriv<C, 3>(F, v, vk, Dv);
+  const Lower Lw = lower_terms<C>(F, gU);
+  add_lower<C, 3>(F, Lw, gU, v, vk, Dv, Bv);
+  // d_k (Dhat_j beta^j)
+  const double a = F.a, b = F.b;
+  if constexpr (C == BHAH_SINH_CYLINDRICAL) {
+    Bd[0] = fma(-a, vk[1][1], fma(-F.s0, vk[0][0], Bd[0]));
+    Bd[2] = fma(-F.s2, vk[2][2], Bd[2]);
+#pragma unroll
+    for (int k = 0; k < 3; k++) Bd[k] = fma(a, vk[k][0], Bd[k]);
+    Bd[0] = fma(-(a * a), v[0], Bd[0]);
+  } else {
+    Bd[0] = fma(-a, vk[1][1] + vk[2][2], fma(-F.s0, vk[0][0], Bd[0]));
+    Bd[1] = fma(-b, vk[2][2], Bd[1]);
+#pragma unroll
+    for (int k = 0; k < 3; k++) Bd[k] = fma(b, vk[k][1], fma(a + a, vk[k][0], Bd[k]));
+    Bd[0] = fma(-a, fma(a + a, v[0], b * v[1]), Bd[0]);
+    Bd[1] = fma(-fma(a, a, b * b), v[1], Bd[1]);
+  }
+  __syncthreads();
+
+  double L[3][3], psi[3], DU[3], div = 0.0;
+  lie_matrix<C>(F, v, vk, Dv, L);
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    psi[k] = get(X_PSI + k);
+    DU[k] = get(X_DU + k);
+    div = fma(psi[k], v[k], div + Dv[k][k]);
+  }
+  double AUU[6], AA;
+  {
+    double AUD[3][3], w[6];
+    raise_first(gU, a6, AUD);
+    raise_second(gU, AUD, AUU);
+    doubled(AUU, w);
+    AA = dot6(w, a6);
+  }
+  double rl[3];
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    double t = 0.0;
+#pragma unroll
+    for (int j = 0; j < 3; j++)
+#pragma unroll
+      for (int k = j; k < 3; k++)
+        t = fma((j == k ? 1.0 : 2.0) * AUU[sy(j, k)], get(X_DEL + 6 * i + sy(j, k)), t);
+    rl[i] = fma(2.0 * alpha, t, Bv[i]);
+  }
+  double q[3];
+#pragma unroll
+  for (int k = 0; k < 3; k++) q[k] = get(X_Q + k);
+  BHAH_PHASE_BARRIER();
+  // Eq. 10 (K), Eq. 9 (W), Eq. 13 (alpha)
+  double rK;
+  {
+    double lap = Za, dd = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+      lap = fma(Lw.n[i] - DU[i], ak[i], lap);
+      double u = gU[sy(i, 0)] * ak[0];
+      u = fma(gU[sy(i, 1)], ak[1], u);
+      u = fma(gU[sy(i, 2)], ak[2], u);
+      dd = fma(u, phi[i], dd);
+    }
+    const double aK = alpha * K;
+    rK = fma((1.0 / 3.0) * aK, K, advK);
+    rK = fma(alpha, AA, rK);
+    rK = fma(-(W * W), fma(2.0, dd, lap), rK);
+    put(R_GAUGE + 8, rK);
+    put(R_GAUGE + 4, fma(-(1.0 / 3.0) * W, div - aK, advW));
+    put(R_GAUGE + 0, fma(-2.0, aK, advAl));
+  }
+  // Eq. 11 (Lambdabar), Eqs. 14-15 (shift, B)
+  double z[3];  // 1/3 d_j (Dbar_k beta^k) - 4/3 alpha K_j, to be raised
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    // d_k (Dbar_j beta^j) = d_k (Dhat_j beta^j) + v^m psi_km + (v_k^m - sigma_km v^m) psi_m
+    double s = Bd[k] + q[k];
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      double g = k == m ? vk[k][k] : L[k][m];
+      if (k == m && k == 0) g = fma(-F.s0, v[0], g);
+      if (C == BHAH_SINH_CYLINDRICAL && k == m && k == 2) g = fma(-F.s2, v[2], g);
+      s = fma(g, psi[m], s);
+    }
+    z[k] = (1.0 / 3.0) * fma(-4.0 * alpha, Kk[k], s);
+  }
+  double bS[3];  // v^k e_k ln S_i
+  bS[0] = v[0] * F.s0;
+  bS[1] = v[0] * a;
+  bS[2] = C == BHAH_SINH_CYLINDRICAL ? v[2] * F.s2 : fma(v[1], b, bS[1]);
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    double r = fma((2.0 / 3.0) * div, DU[i], rl[i]);
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+      r = fma(gU[sy(i, j)], z[j], r);
+      r = fma(-2.0 * AUU[sy(i, j)], fma(-6.0 * alpha, phi[j], ak[j]), r);
+      r = fma(-lam[j], L[j][i], r);
+    }
+    r += advL[i];
+    put(R_GAUGE + 5 + i, r);
+    put(R_GAUGE + 1 + i, fma(0.75, KO ? r - koL[i] : r, advB[i]) - fma(bet[i], bS[i], ga.eta * bet[i]));
+    put(R_GAUGE + 9 + i, fma(-v[i], bS[i], bet[i]) + advV[i]);
+  }
+  constexpr int out[12] = {G_ALPHA, G_BETU0, G_BETU0 + 1, G_BETU0 + 2, G_CF, G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2, G_TRK,
+                           G_VETU0, G_VETU0 + 1, G_VETU0 + 2};
+  stage_epilogue(G, st, p.q, p.live, out, xs + R_GAUGE * 64, lane);
+}
+
+// One tile by the block's two waves. Every lane takes part (lanes past the
+// grid compute a point on it and store nothing).
+template <int C, bool AX, bool KO, int H, class SRC>
+__device__ __forceinline__ void rhs_tile(const GridDev& G, const TileMap& T, int w, const Gauge& ga,
+                                         const double* __restrict__ y, const StageArgs& st, double* __restrict__ aux,
+                                         double* __restrict__ xs) {
+  const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  TilePoint p;
+  p.live = tile_point<H>(G, T, w, lane, p.t0, p.t1, p.t2, p.i0, p.i1, p.i2);
+  p.q = (unsigned)(p.i0 + G.s1 * p.i1 + G.s2 * p.i2);
+  if (wave == 0) metric_wave<C, AX, KO, H, SRC>(G, ga, y, st, p, aux, xs, lane);
+  else gauge_wave<C, AX, KO, H, SRC>(G, ga, y, st, p, xs, lane);
+}
+
+}  // namespace bhah

@@ -1,195 +1,281 @@
-// rhs_stencil.h -- the stencil building blocks shared by the right-hand-side
-// kernels (one wave per tile in rhs_fused.hip, two waves per tile in
-// rhs_pair.hip): upwinded advection and Kreiss-Oliger sums, the stencil
-// gathers, the batched advection of several gridfunctions, and the tile walk.
+// rhs_stencil.h -- the stencil side of the right-hand-side kernel
+// (rhs_fused.hip): the stencil sums of one gridfunction, where its values
+// come from (LDS patches of a tile, or per-lane loads), and the tile walk.
 #pragma once
 
-#include "rhs_common.h"
+#include <type_traits>
+#include <utility>
+
+#include "rhs_frame.h"
 
 namespace bhah {
 
-// Upwinded advection beta^k d_k f of a rescaled gridfunction (Sec. 3: shift
-// advection terms use the stencil shifted one point upwind). With
-// sigma = sign(vet^k) and f(m) = f at offset m*sigma along k:
-//   beta^k U_k f = |beta^k|/(den1 dxx^k) sum_{m != 1} up_m (f(m) - f(1)),
-// m = -(R-1)..R+1; at 4th order
-//   |beta^k|/(12 dxx^k) [3 (f(1) - f(-1)) + 10 (f(1) - f(0))
-//                        - 6 (f(2) - f(1)) + (f(3) - f(1))].
-template <int H>
-struct UpwindT {
-  unsigned vu[3][H];  // per-lane byte offsets of q + m s, m = 1..H (upwind side)
-  unsigned vd[3][H];  // q - m s (downwind side; beyond R - 1 for dissipation only)
-  unsigned v0;
-  double w[3];        // |beta^k| / (den1 dxx^k)
-};
-
-// the upwinded sum for f(m), m = -(R-1)..R+1 in upwind orientation; at 4th
-// order in the grouping written above
-template <int R, class F>
-__device__ __forceinline__ double upwind_f(const F& f) {
-  if constexpr (R == 2) {
-    const double fp = f(1), fm = f(-1), f2 = f(2), f0 = f(0), f3 = f(3);
-    return 3.0 * (fp - fm) + 10.0 * (fp - f0) - 6.0 * (f2 - fp) + (f3 - fp);
-  } else {
-    const double f1 = f(1);
-    double a = FdW<R>::up[0] * (f(1 - R) - f1);
-#pragma unroll
-    for (int m = 2 - R; m <= R + 1; m++)
-      if (m != 1) a += FdW<R>::up[m + R - 1] * (f(m) - f1);
-    return a;
-  }
-}
-
-// upwinded stencil sum from centred values v[R + m] = f(m) and the value fu
-// at (R+1) sigma; up selects the side (sigma = +1)
-template <int R>
-__device__ __forceinline__ double upwind_sum(const double (&v)[2 * R + 1], double fu, bool up) {
-  auto f = [&](int m) { return m == R + 1 ? fu : (up ? v[R + m] : v[R - m]); };
-  return upwind_f<R>(f);
-}
-
-// Kreiss-Oliger dissipation (Sec. 4.1): the difference of order 2(R+1)
-// along each logical direction, weighted by eps/(kden dxx^k); at 4th order
-// delta^6 f = f(3) + f(-3) - 6 (f(2) + f(-2)) + 15 (f(1) + f(-1)) - 20 f(0)
-// over 64 dxx^k. Symmetric in the two sides, so the upwind-ordered stencil
-// values serve as they are. fp[j], fm[j] are f(+-j), j = 1..R+1; the sums
-// are taken as differences from f(0) (exact zero on constants, rounding
-// of the size of the differences).
-template <int R>
-__device__ __forceinline__ double ko_sum(const double (&fp)[R + 2], const double (&fm)[R + 2], double f0) {
-  double a = FdW<R>::ko[R + 1] * ((fp[R + 1] - f0) + (fm[R + 1] - f0));
-#pragma unroll
-  for (int j = R; j >= 1; j--) a += FdW<R>::ko[j] * ((fp[j] - f0) + (fm[j] - f0));
-  return a;
-}
-// the same from centred values v (offsets -R..R) and the two outermost
-template <int R>
-__device__ __forceinline__ double ko_v(const double (&v)[2 * R + 1], double fu, double fd) {
-  double fp[R + 2], fm[R + 2];
-#pragma unroll
-  for (int j = 1; j <= R; j++) { fp[j] = v[R + j]; fm[j] = v[R - j]; }
-  fp[R + 1] = fu;
-  fm[R + 1] = fd;
-  fp[0] = fm[0] = v[R];
-  return ko_sum<R>(fp, fm, v[R]);
-}
-
 #define BHAH_PHASE_BARRIER() __builtin_amdgcn_sched_barrier(0)
 
-// Two-plane phi (AX): with exactly two interior phi planes the wrapped odd
-// offsets land on the other plane and the even ones on the point's own, so
-// a phi stencil reads two values, every centred phi first derivative and
-// every mixed derivative involving phi vanishes identically (the grouped
-// differences of equal values), and the upwinded phi stencil reduces to the
-// two planes. The arithmetic on the values read is unchanged.
+// Keeps arithmetic where it is written: a scheduling barrier holds loads and
+// stores, but arithmetic on loaded values would still sink to its last use
+// and keep every operand in a register until there (at 8th order all 64
+// values of a mixed pair). No instruction is emitted.
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
 
-// axis gather along K; along phi on a two-plane grid only the two planes are
-// read
-template <int K, int PD, bool AX, class PT>
-__device__ __forceinline__ void gather_axis_ax(const PT& P, int g, double (&v)[2 * PT::R + 1]) {
-  if constexpr (AX && K == PD) {
-    const double c = P.at(g, 0, 0, 0), o = P.template ax<K>(g, 1);
+// Upwinded advection beta^k d_k f (Sec. 3: the centred stencil shifted one
+// point upwind) as its antisymmetric and symmetric parts. With
+// D_j = f_j - f_-j and S_j = (f_j - f_0) + (f_-j - f_0), for either sign of
+// the shift component v,
+//   den1 v U f = (v/2) sum_j ua[j] D_j + sk |v| sum_j ko[j] S_j,  j = 1..R+1,
+// where sum_j ko[j] S_j is the difference of order 2R+2 that the
+// Kreiss-Oliger term uses: its strength adds to sk |v|, so dissipation costs
+// no stencil arithmetic of its own, and no value is selected by the sign of
+// the shift. At 4th order (up = -3, -10, 18, -6, 1): D: 21, -6, 1 (halves),
+// S: (f_3 + f_-3) - 6 (f_2 + f_-2) + 15 (f_1 + f_-1) - 20 f_0, sk = 1/2.
+// D_j and S_j also give the first and second derivatives.
+template <int R>
+struct UpW;
+template <>
+struct UpW<2> {
+  static constexpr double ua[4] = {0.0, 21.0, -6.0, 1.0}, sk = 0.5;
+};
+template <>
+struct UpW<4> {
+  static constexpr double ua[6] = {0.0, 1470.0, -480.0, 145.0, -30.0, 3.0}, sk = 1.5;
+};
+
+// f(0), f(1), .., f(N - 1) with the index as a compile-time constant (loops of
+// this size are not always unrolled by the compiler, and a loop left over
+// would index registers at run time)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_(const F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(const F& f) {
+  static_for_(f, std::make_integer_sequence<int, N>{});
+}
+#define BHAH_INLINE __attribute__((always_inline))
+
+// raw sums of one gridfunction along one direction: den1 D f, den2 D2 f and
+// the two parts of the upwinded sum (A: sum ua D_j, K: sum ko S_j)
+struct AxisSums {
+  double d1, d2, A, K;
+};
+// (first, second: whether d1 and d2 are used at all)
+__device__ __forceinline__ void pin(AxisSums& s, bool first, bool second) {
+  if (first) pin(s.d1);
+  if (second) pin(s.d2);
+  pin(s.A);
+  pin(s.K);
+}
+template <int R>
+__device__ __forceinline__ AxisSums axis_sums(const double (&v)[2 * R + 3]) {
+  constexpr int H = R + 1;
+  double D[H + 1], S[H + 1];
 #pragma unroll
-    for (int t = 0; t < 2 * PT::R + 1; t++) v[t] = ((t - PT::R) & 1) ? o : c;
-  } else {
-    gather_axis<K>(P, g, v);
+  for (int j = 1; j <= H; j++) {
+    D[j] = v[H + j] - v[H - j];
+    S[j] = (v[H + j] - v[H]) + (v[H - j] - v[H]);
   }
+  AxisSums s;
+  s.d1 = FdW<R>::d1[R] * D[R];
+  s.d2 = FdW<R>::d2[R] * S[R];
+#pragma unroll
+  for (int j = R - 1; j >= 1; j--) {
+    s.d1 = fma(FdW<R>::d1[j], D[j], s.d1);
+    s.d2 = fma(FdW<R>::d2[j], S[j], s.d2);
+  }
+  s.A = UpW<R>::ua[H] * D[H];
+  s.K = FdW<R>::ko[H] * S[H];
+#pragma unroll
+  for (int j = R; j >= 1; j--) {
+    s.A = fma(UpW<R>::ua[j], D[j], s.A);
+    s.K = fma(FdW<R>::ko[j], S[j], s.K);
+  }
+  return s;
+}
+// The same along phi on a grid with two phi planes: odd offsets land on the
+// other plane (value o), even ones on the point's own (c), so D_j = 0 and the
+// odd S_j are all 2 (o - c).
+template <int R>
+__device__ __forceinline__ AxisSums axis_sums_two_planes(double c, double o) {
+  double kd2 = 0.0, kk = 0.0;
+#pragma unroll
+  for (int j = 1; j <= R; j += 2) kd2 += 2.0 * FdW<R>::d2[j];
+#pragma unroll
+  for (int j = 1; j <= R + 1; j += 2) kk += 2.0 * FdW<R>::ko[j];
+  const double x = o - c;
+  return AxisSums{0.0, kd2 * x, 0.0, kk * x};
+}
+// den1 D f from values v[R + m] = f(m), m = -R..R (v[R] is not used)
+template <int R>
+__device__ __forceinline__ double d1_sum(const double (&v)[2 * R + 1]) {
+  double a = FdW<R>::d1[R] * (v[2 * R] - v[0]);
+#pragma unroll
+  for (int j = R - 1; j >= 1; j--) a = fma(FdW<R>::d1[j], v[R + j] - v[R - j], a);
+  return a;
 }
 
-// compile-time dispatch of the gathers on a (compile-time after unrolling)
-// direction index
-template <int PD, bool AX, class PT>
-__device__ __forceinline__ void gather_axis_k(const PT& P, int g, int k, double (&v)[2 * PT::R + 1]) {
-  if (k == 0) gather_axis_ax<0, PD, AX>(P, g, v);
-  else if (k == 1) gather_axis_ax<1, PD, AX>(P, g, v);
-  else gather_axis_ax<2, PD, AX>(P, g, v);
-}
-// value R+1 points upwind along k (the last point of the shifted stencil),
-// or, with the offsets of the other side, R+1 points downwind; on a
-// two-plane grid R+1 is odd, the other plane
-template <int PD, bool AX, class PT>
-__device__ __forceinline__ double upwind_far(const PT& P, int g, int k, const unsigned (&vo)[3][PT::H],
-                                             const double (&v)[2 * PT::R + 1]) {
-  if (AX && k == PD) return v[PT::R - 1];
-  return gf_ld(P.y, P.sgf, g, vo[k][PT::H - 1], 0);
-}
-template <class PT>
-__device__ __forceinline__ void gather_cross_kl(const PT& P, int g, int k, int l, double (&v)[4 * PT::R * PT::R]) {
-  if (k == 0 && l == 1) gather_cross<0, 1>(P, g, v);
-  else if (k == 0) gather_cross<0, 2>(P, g, v);
-  else gather_cross<1, 2>(P, g, v);
-}
+// ---- where stencil values come from ----------------------------------------
+// A tile is a patch of EX points along i0 and EE along the other
+// non-periodic direction e (i2 on SinhCylindrical grids, i1 otherwise) on one
+// phi plane: 16 x 4. For one gridfunction at a time the wave brings the
+// patch with its halo into LDS with 16-byte loads and takes every stencil
+// value along i0 and e and of the mixed pair (0, e) from there. On grids with
+// more than two phi planes the planes at phi offsets +-j follow in pairs, for
+// the mixed pairs (0, phi) and (e, phi); values at phi offsets +-(R+1), and
+// all phi offsets of gridfunctions without second derivatives, are read per
+// lane. The CU's vector memory path takes about the same time for every load
+// instruction whatever its width (16 cycles measured for 64 lanes), so what
+// counts is the number of instructions: a 16 x 4 patch with its halo at 4th
+// order is 22 x 10 values, two loads, where a row of 64 points would be 7 x
+// 70, four, and per-lane gathers 30 to 70.
+constexpr int TLX = 4, TEX = 1 << TLX, TEE = 64 >> TLX;
+// row length and 16-byte pieces of the main patch (halo H) and of one pair of
+// phi planes (halo R each)
+template <int H>
+struct Patch {
+  static constexpr int R = H - 1;
+  static constexpr int RL = TEX + 2 * H, RE = TEE + 2 * H, NP = RL * RE / 2, NR = (NP + 63) / 64;
+  static constexpr int QL = TEX + 2 * R, QE = TEE + 2 * R, QN = QL * QE, QP = QN, QR = (QP + 63) / 64;
+  static constexpr int MAIN = 2 * NP, PAIR = 2 * QN;  // doubles
+};
 
-// upwinded advection of N gridfunctions in one batch of loads; with KO also
-// their dissipation (strength eps[t], weights kw[k] = 1/(kden dxx^k))
-template <int N, int PD, bool AX, bool KO, class PT>
-__device__ __forceinline__ void advect_batch(const PT& P, const int (&gl)[N], const UpwindT<PT::H>& U,
-                                             double (&out)[N], const double (&eps)[N], const double (&kw)[3]) {
-  constexpr int H = PT::H, R = PT::R;
-  constexpr int ND = KO ? H : R - 1;  // downwind points read
-  double f0[N], fu[N][3][H + 1], fd[N][3][ND + 1];
+// All accessors give f at offsets (d0, de) on the point's phi plane or on the
+// plane at phi offset +-j, and the phi column of the point.
+template <int H>
+struct StagedSrc {
+  static constexpr bool STG = true;
+  using PG = Patch<H>;
+  static constexpr int R = H - 1;
+  const double* y;
+  long long sgf;
+  double* lds;         // the wave's stage: main patches, then a pair of phi planes
+  unsigned voff[PG::NR], qoff[PG::QR];  // per-lane byte offsets of the lane's pieces
+  int lane;
+  unsigned vlane;      // per-lane byte offset of the point, phi index removed
+  int sw[2 * H + 1];   // byte offsets of the (wrapped) phi planes at offsets -H..H, wave-uniform
+  unsigned org;        // byte offset of the patch origin (halo H), phi index removed, wave-uniform
+  int c0, q0;          // the point's place in the main patch and in a phi-plane patch
+
+  // tile origin (it, et), point (i0, ie), phi index ip; sE, sP strides
+  __device__ __forceinline__ void init(const double* y_, const GridDev& G, int pd, int it, int et, int i0, int ie,
+                                       int ip, int lane_, double* lds_, bool two_planes) {
+    y = y_;
+    lane = lane_;
+    sgf = G.sgf;
+    lds = lds_;
+    const int sP = pd == 1 ? G.s1 : G.s2, sE = pd == 1 ? G.s2 : G.s1, nP = pd == 1 ? G.N1 : G.N2;
+    const int id = ip - H;
 #pragma unroll
-  for (int t = 0; t < N; t++) {
-    const int g = gl[t];
-    f0[t] = gf_ld(P.y, P.sgf, g, U.v0, 0);
+    for (int o = -H; o <= H; o++) {
+      int x = id + o;
+      if (two_planes) {
+        x = (x + 2 * H) & 1;
+      } else if constexpr (H == 3) {  // nP >= 2: two corrections each way suffice
+        x += x < 0 ? nP : 0;
+        x += x < 0 ? nP : 0;
+        x -= x >= nP ? nP : 0;
+        x -= x >= nP ? nP : 0;
+      } else {
+        x %= nP;
+        x += x < 0 ? nP : 0;
+      }
+      sw[o + H] = (H + x) * sP * 8;
+    }
+    org = (unsigned)((it - H) + sE * (et - H)) * 8u;
+    vlane = (unsigned)(i0 + sE * ie) * 8u;
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-      fu[t][k][1] = gf_ld(P.y, P.sgf, g, U.vu[k][0], 0);
-      if (AX && k == PD) {  // two phi planes: odd offsets are the other plane, even ones this one
+    for (int r = 0; r < PG::NR; r++) {
+      const int p = piece<PG::NP>(r), row = p / (PG::RL / 2), col = 2 * (p - row * (PG::RL / 2));
+      voff[r] = (unsigned)(col + row * sE) * 8u;
+    }
+    if (!two_planes) {
 #pragma unroll
-        for (int m = 2; m <= H; m++) fu[t][k][m] = (m & 1) ? fu[t][k][1] : f0[t];
-#pragma unroll
-        for (int m = 1; m <= ND; m++) fd[t][k][m] = (m & 1) ? fu[t][k][1] : f0[t];
-      } else {  // in the order q - s, q + 2s .. q + Hs, then further downwind
-        if constexpr (ND >= 1) fd[t][k][1] = gf_ld(P.y, P.sgf, g, U.vd[k][0], 0);
-#pragma unroll
-        for (int m = 2; m <= H; m++) fu[t][k][m] = gf_ld(P.y, P.sgf, g, U.vu[k][m - 1], 0);
-#pragma unroll
-        for (int m = 2; m <= ND; m++) fd[t][k][m] = gf_ld(P.y, P.sgf, g, U.vd[k][m - 1], 0);
+      for (int r = 0; r < PG::QR; r++) {
+        int p = piece<PG::QP>(r);
+        if (far_plane(r)) p -= PG::QN / 2;
+        const int row = p / (PG::QL / 2), col = 2 * (p - row * (PG::QL / 2));
+        qoff[r] = (unsigned)((col + 1) + (row + 1) * sE) * 8u;  // halo R = H - 1
       }
     }
+    c0 = (ie - et + H) * PG::RL + (i0 - it + H);
+    q0 = (ie - et + R) * PG::QL + (i0 - it + R);
   }
-  BHAH_PHASE_BARRIER();
-#pragma unroll
-  for (int t = 0; t < N; t++) {
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; k++) {
-      // f(m) for m = -(R-1)..R+1 in upwind orientation
-      auto f = [&](int m) { return m == 0 ? f0[t] : (m > 0 ? fu[t][k][m] : fd[t][k][-m]); };
-      s += U.w[k] * upwind_f<R>(f);
-    }
-    if constexpr (KO) {
-      double d = 0.0;
-#pragma unroll
-      for (int k = 0; k < 3; k++) {
-        double fp[R + 2], fm[R + 2];
-#pragma unroll
-        for (int j = 0; j <= H; j++) {
-          fp[j] = j == 0 ? f0[t] : fu[t][k][j];
-          fm[j] = j == 0 ? f0[t] : fd[t][k][j];
-        }
-        d += kw[k] * ko_sum<R>(fp, fm, f0[t]);
-      }
-      s += eps[t] * d;
-    }
-    out[t] = s;
+  // the lane's r-th 16-byte piece of N; past the last one it repeats it, so
+  // that every lane loads and stores in bounds
+  template <int N>
+  __device__ __forceinline__ int piece(int r) const {
+    return (r + 1) * 64 <= N ? r * 64 + lane : min(r * 64 + lane, N - 1);
   }
-}
+  // whether it lies on the second plane (phi offset -j) of a pair
+  __device__ __forceinline__ bool far_plane(int r) const {
+    constexpr int half = PG::QN / 2;
+    return (r + 1) * 64 <= half ? false : (r * 64 >= half ? true : r * 64 + lane >= half);
+  }
+  struct MainRegs {
+    double lo[PG::NR], hi[PG::NR];
+  };
+  struct PairRegs {
+    double lo[PG::QR], hi[PG::QR];
+  };
+  __device__ __forceinline__ void issue_main(int g, MainRegs& m) const {
+#pragma unroll
+    for (int r = 0; r < PG::NR; r++) gf_ld2(y, sgf, g, voff[r], (int)org + sw[H], m.lo[r], m.hi[r]);
+  }
+  __device__ __forceinline__ void commit_main(const MainRegs& m, int slot) const {
+#pragma unroll
+    for (int r = 0; r < PG::NR; r++) {
+      lds[slot * PG::MAIN + 2 * piece<PG::NP>(r)] = m.lo[r];
+      lds[slot * PG::MAIN + 2 * piece<PG::NP>(r) + 1] = m.hi[r];
+    }
+  }
+  __device__ __forceinline__ void issue_pair(int g, int j, PairRegs& m) const {
+#pragma unroll
+    for (int r = 0; r < PG::QR; r++)
+      gf_ld2(y, sgf, g, qoff[r] + (unsigned)(far_plane(r) ? sw[H - j] : sw[H + j]), (int)org, m.lo[r], m.hi[r]);
+  }
+  __device__ __forceinline__ void commit_pair(const PairRegs& m, int base) const {
+#pragma unroll
+    for (int r = 0; r < PG::QR; r++) {
+      lds[base + 2 * piece<PG::QP>(r)] = m.lo[r];
+      lds[base + 2 * piece<PG::QP>(r) + 1] = m.hi[r];
+    }
+  }
+  __device__ __forceinline__ double main_at(int slot, int d0, int de) const {
+    return lds[slot * PG::MAIN + c0 + de * PG::RL + d0];
+  }
+  __device__ __forceinline__ double pair_at(int base, int side, int d0, int de) const {
+    return lds[base + side * PG::QN + q0 + de * PG::QL + d0];
+  }
+  // value in the point's phi column
+  __device__ __forceinline__ double column(int g, int m) const { return gf_ld(y, sgf, g, vlane, sw[H + m]); }
+};
+
+// per-lane loads (tile shapes other than the staged patch)
+template <int H>
+struct GatherSrc {
+  static constexpr bool STG = false;
+  PtT<H> P;
+  int pd;
+  __device__ __forceinline__ double at(int g, int d0, int de, int dp) const {
+    return pd == 1 ? P.at(g, d0, dp, de) : P.at(g, d0, de, dp);
+  }
+};
 
 // Tiles: 64 points, 2^lx along i0 times 2^ly along i1 times 64 >> (lx + ly)
 // along i2; the tile grid is walked in bands of `band` tile rows of i1, and
-// within a band by i0 tile column, then i2, then i1 (fastest), so the tiles
-// that run at the same time form a compact block of one column whose
-// stencils overlap. The hardware hands consecutive workgroup ids to the XCDs
-// in turn; block ids are remapped so that every XCD works through one
-// contiguous range of the walk (its L2 then holds a compact part of the
-// grid). On the 3-D grid the column-first order moves a third (4th order)
-// to a quarter (8th order) of the HBM bytes of an i0-fastest order, at the
-// same speed.
+// within a band by i2, then i1, then i0 (fastest), so that tiles that share
+// cache lines along i0 run at the same time. The hardware hands consecutive
+// workgroup ids to the XCDs in turn; block ids are remapped so that every XCD
+// works through one contiguous range of the walk (its L2 then holds a compact
+// part of the grid). The lines matter more than the bytes: in columns of 64
+// points the 3-D RK4 stage reads 2.4 GB instead of 4.2 GB through the L2s, but
+// every column edge leaves lines that two tiles complete far apart in time
+// (1.16x the write requests), and the step takes 3.90 ms instead of 3.66 ms
+// (head-on 0.934 instead of 0.902 ms per 10 steps).
+// (t0, t1, t2) is the tile's first point; (i0, i1, i2) the lane's, moved onto
+// the grid where the tile runs past it (false is returned for such lanes).
 template <int H>
-__device__ __forceinline__ bool tile_point(const GridDev& G, const TileMap& T, int w, int lane, int& i0,
-                                           int& i1, int& i2) {
+__device__ __forceinline__ bool tile_point(const GridDev& G, const TileMap& T, int w, int lane, int& t0, int& t1,
+                                           int& t2, int& i0, int& i1, int& i2) {
   const int full = T.band * T.tz * T.tx;  // tiles in one full band
   const int nb = (T.ty + T.band - 1) / T.band;
   int bi = w / full;
@@ -197,15 +283,19 @@ __device__ __forceinline__ bool tile_point(const GridDev& G, const TileMap& T, i
   const int start = bi * T.band;
   const int hgt = min(T.band, T.ty - start);
   const int idx = w - start * T.tz * T.tx;
-  const int xt = idx / (hgt * T.tz);
-  const int r = idx - xt * hgt * T.tz;
+  const int r = idx / T.tx;
+  const int xt = idx - r * T.tx;
   const int j2 = r / hgt;
   const int j1 = start + (r - j2 * hgt);
   const int ex = 1 << T.lx, ey = 1 << T.ly;
-  i0 = H + xt * ex + (lane & (ex - 1));
-  i1 = H + j1 * ey + ((lane >> T.lx) & (ey - 1));
-  i2 = H + (j2 << (6 - T.lx - T.ly)) + (lane >> (T.lx + T.ly));
-  return i0 < H + G.N0 && i1 < H + G.N1 && i2 < H + G.N2;
+  t0 = H + xt * ex;
+  t1 = H + j1 * ey;
+  t2 = H + (j2 << (6 - T.lx - T.ly));
+  const int a = t0 + (lane & (ex - 1)), b = t1 + ((lane >> T.lx) & (ey - 1)), c = t2 + (lane >> (T.lx + T.ly));
+  i0 = min(a, H + G.N0 - 1);
+  i1 = min(b, H + G.N1 - 1);
+  i2 = min(c, H + G.N2 - 1);
+  return a == i0 && b == i1 && c == i2;
 }
 
 // logical position in the walk of the tile a block works on; with G_blocks a
