@@ -3,10 +3,10 @@
 Each source is compiled with hipcc for gfx950; the right-hand-side and
 constraint units also get -fno-signed-zeros -ffinite-math-only so that
 structurally zero reference-metric terms fold away (no reassociation is
-enabled). The right-hand-side unit fuses multiply-adds only where the source
-writes them in one expression (-ffp-contract=on), so that every kernel that
-inlines the same code rounds alike whatever the compiler makes of its
-surroundings; it is compiled in parts (one kernel variant each), in parallel.
+enabled). They fuse multiply-adds only where the source writes them in one
+expression (-ffp-contract=on), so that every kernel that inlines the same code
+rounds alike whatever the compiler makes of its surroundings, and are compiled
+in parts (one kernel variant each), in parallel.
 """
 import concurrent.futures as cf
 import os
@@ -21,9 +21,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function"]
 ARCH = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 DEVICE = ARCH + ["-ffp-contract=fast"]
+STENCIL = ARCH + ["-ffp-contract=on", "-fno-signed-zeros", "-ffinite-math-only"]
 SOURCES = {
-    "rhs_fused.hip": ARCH + ["-ffp-contract=on", "-fno-signed-zeros", "-ffinite-math-only"],
-    "hamiltonian.hip": DEVICE + ["-fno-signed-zeros", "-ffinite-math-only"],
+    "rhs_fused.hip": STENCIL,
+    "hamiltonian.hip": STENCIL,
     "misc.hip": DEVICE,
     "probe.hip": DEVICE,
     "grid.cpp": [],
@@ -32,7 +33,7 @@ SOURCES = {
     "batch.cpp": [],
     "server.cpp": [],
 }
-PARTS = {"rhs_fused.hip": 12}  # compiled once per part, -DBHAH_PART=0 ..
+PARTS = {"rhs_fused.hip": 12, "hamiltonian.hip": 12}  # compiled once per part, -DBHAH_PART=0 ..
 
 
 def _compile(name, extra, part, verbose):

@@ -48,310 +48,13 @@ enum {
 // it writes only after its stencils), the gauge wave's the last ones. The
 // metric wave parks e_k h_ij and the advection of h_ij in what is left.
 template <bool AX, int H>
-struct Stage {
-  static constexpr int PER = AX && H == 3 ? 2 : 1;  // gridfunctions per batch of loads on two-plane grids
-  static constexpr int N = AX ? PER * Patch<H>::MAIN : Patch<H>::MAIN + Patch<H>::PAIR;
-  static constexpr int SL = (N + 63) / 64, GAUGE = X_SLOTS - SL, LOW = X_V - SL;
+struct Stage : StageSize<AX, H> {
+  using StageSize<AX, H>::SL;
+  static constexpr int GAUGE = X_SLOTS - SL, LOW = X_V - SL;
   static constexpr int CAP = LOW + GAUGE - X_PARK;  // park slots
   static_assert(LOW >= 0 && GAUGE >= X_PARK, "stages");
   static constexpr int park(int i) { return i < LOW ? SL + i : X_PARK + i - LOW; }
 };
-
-// what both waves derive from the point: frame, scales, upwind coefficients
-template <int H>
-struct Coefs {
-  double s1[3];  // e_k f = s1[k] * (den1 D f)
-  double ch[3], q[3], qg[3];  // advection and dissipation: ch A + q K (metric strength), qg (gauge strength)
-  double kw[3];
-  // f_kl = sc(k, l) * raw second difference
-  __device__ __forceinline__ double sc(int k, int l) const {
-    constexpr double r = FdW<H - 1>::den1 * FdW<H - 1>::den1 / FdW<H - 1>::den2;
-    return k == l ? s1[k] * s1[k] * r : s1[k] * s1[l];
-  }
-};
-template <bool KO, int H>
-__device__ __forceinline__ void make_coefs(const GridDev& G, const Gauge& ga, const double (&iS)[3],
-                                           const double (&v)[3], Coefs<H>& c) {
-  constexpr int R = H - 1;
-  using W = FdW<R>;
-#pragma unroll
-  for (int k = 0; k < 3; k++) {
-    c.s1[k] = iS[k] * (G.inv_dx[k] * (1.0 / W::den1));
-    const double b = v[k] * c.s1[k];
-    c.ch[k] = 0.5 * b;
-    c.q[k] = c.qg[k] = UpW<R>::sk * fabs(b);
-    if constexpr (KO) {
-      c.kw[k] = G.inv_dx[k] * (1.0 / W::kden);
-      c.qg[k] = fma(ga.dg, c.kw[k], c.q[k]);
-      c.q[k] = fma(ga.dm, c.kw[k], c.q[k]);
-    }
-  }
-}
-
-template <int H>
-__device__ __forceinline__ double advect(const AxisSums (&s)[3], const double (&ch)[3], const double (&q)[3]) {
-  double a = 0.0;
-#pragma unroll
-  for (int k = 0; k < 3; k++) a = fma(ch[k], s[k].A, fma(q[k], s[k].K, a));
-  return a;
-}
-
-// ---- stencil drivers ---------------------------------------------------------
-// Runs over the gridfunctions list[0..N): for each, fn(t, axis sums
-// along the three directions, raw second differences dd[sy(k, l)]); dd is
-// formed for t in [F0, F1), first derivatives are used for t in [F0, F2).
-// Identically vanishing phi derivatives of two-plane
-// grids are literal zeros. The arithmetic is the same for both sources.
-// whether d_k d_l, kl = sy(k, l), vanishes identically (mixed with phi on two planes)
-template <bool AX, int PD>
-__device__ __forceinline__ constexpr bool zero_pair(int kl) {
-  return AX && (kl == sy(0, PD) || kl == sy(3 - PD, PD));
-}
-template <int R>
-__device__ __forceinline__ double acc_pair(int j, double acc, double p, double m) {
-  return j == 1 ? FdW<R>::d1[1] * (p - m) : fma(FdW<R>::d1[j], p - m, acc);
-}
-
-template <int C, bool AX, int H, int F0, int F1, int F2, int N, class FN>
-__device__ __forceinline__ void run_stencils(const StagedSrc<H>& S, const int (&list)[N], const FN& fn) {
-  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
-  using SS_ = StagedSrc<H>;
-  auto in_plane = [&](int slot, bool full, bool first, AxisSums(&s)[3], double (&dd)[6], double& c) BHAH_INLINE {
-    double v0[2 * H + 1], vE[2 * H + 1];
-#pragma unroll
-    for (int m = -H; m <= H; m++) {
-      v0[H + m] = S.main_at(slot, m, 0);
-      vE[H + m] = m == 0 ? v0[H] : S.main_at(slot, 0, m);
-    }
-    c = v0[H];
-    s[0] = axis_sums<R>(v0);
-    s[E] = axis_sums<R>(vE);
-    pin(s[0], first, full);
-    pin(s[E], first, full);
-    if (full) {
-      if constexpr (H == 5) BHAH_PHASE_BARRIER();
-      double e[2 * R + 1];
-      e[R] = 0.0;
-#pragma unroll
-      for (int m = -R; m <= R; m++)
-        if (m != 0) {
-          double r[2 * R + 1];
-          r[R] = 0.0;
-#pragma unroll
-          for (int n = -R; n <= R; n++)
-            if (n != 0) r[R + n] = S.main_at(slot, n, m);
-          e[R + m] = d1_sum<R>(r);
-          pin(e[R + m]);
-          if constexpr (H == 5) BHAH_PHASE_BARRIER();
-        }
-      dd[sy(0, E)] = d1_sum<R>(e);
-      pin(dd[sy(0, E)]);
-    }
-  };
-  if constexpr (AX) {
-    constexpr int PER = Stage<AX, H>::PER, NB = (N + PER - 1) / PER;
-    typename SS_::MainRegs m[PER];
-    double ph[PER];
-    auto issue = [&](int b) {
-#pragma unroll
-      for (int t = 0; t < PER; t++)
-        if (b * PER + t < N) {
-          S.issue_main(list[b * PER + t], m[t]);
-          ph[t] = S.column(list[b * PER + t], 1);
-        }
-    };
-    issue(0);
-    static_for<NB>([&](auto bc) BHAH_INLINE {
-      constexpr int b = decltype(bc)::value;
-      double o[PER];
-#pragma unroll
-      for (int t = 0; t < PER; t++)
-        if (b * PER + t < N) {
-          S.commit_main(m[t], t);
-          o[t] = ph[t];
-        }
-      if constexpr (b + 1 < NB) issue(b + 1);
-      BHAH_PHASE_BARRIER();
-      static_for<PER>([&](auto tc) BHAH_INLINE {
-        constexpr int t = decltype(tc)::value, tt = b * PER + t;
-        if constexpr (tt < N) {
-          AxisSums s[3];
-          double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
-          in_plane(t, tt >= F0 && tt < F1, tt >= F0 && tt < F2, s, dd, c);
-          s[PD] = axis_sums_two_planes<R>(c, o[t]);
-#pragma unroll
-          for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
-          fn(tt, s, dd);
-        }
-      });
-    });
-  } else {
-    constexpr int PB = SS_::PG::MAIN;  // the phi planes' place in the stage
-    // Loads run one gridfunction ahead of their use. At 8th order, where a
-    // gridfunction has four pairs of phi planes, one pair and then the next
-    // main patch: more in flight spills (3-D production step 6.0 instead of
-    // 5.2 ms); at 4th order deeper prefetch measures the same.
-    constexpr int PS = H == 3 ? 2 : 1;
-    typename SS_::MainRegs m;
-    typename SS_::PairRegs pr[PS];
-    double col[2 * H];  // phi offsets -H..-1, 1..H
-    auto issue = [&](auto tc) BHAH_INLINE {
-      constexpr int t = decltype(tc)::value;
-      if constexpr (t < N) {
-        S.issue_main(list[t], m);
-#pragma unroll
-        for (int o = 1; o <= H; o++)
-          if (o == H || !(t >= F0 && t < F1)) {
-            col[H - o] = S.column(list[t], -o);
-            col[H + o - 1] = S.column(list[t], o);
-          }
-      }
-    };
-    issue(std::integral_constant<int, 0>{});
-    if constexpr (F0 == 0) {
-#pragma unroll
-      for (int j = 1; j <= PS; j++) S.issue_pair(list[0], j, pr[j - 1]);
-    }
-    static_for<N>([&](auto tc) BHAH_INLINE {
-      constexpr int t = decltype(tc)::value;
-      constexpr bool full = t >= F0 && t < F1;
-      double vP[2 * H + 1];
-      S.commit_main(m, 0);
-#pragma unroll
-      for (int o = 1; o <= H; o++)
-        if (o == H || !full) {
-          vP[H - o] = col[H - o];
-          vP[H + o] = col[H + o - 1];
-        }
-      if constexpr (H == 3 || !full) issue(std::integral_constant<int, t + 1>{});
-      // the first pairs: a gridfunction early, at 8th order with their own main patch
-      if constexpr (H == 3 ? t + 1 == F0 : full && t > 0) {
-#pragma unroll
-        for (int j = 1; j <= PS; j++) S.issue_pair(list[H == 3 ? F0 : t], j, pr[j - 1]);
-      }
-      BHAH_PHASE_BARRIER();
-      AxisSums s[3];
-      double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
-      in_plane(0, full, t >= F0 && t < F2, s, dd, c);
-      vP[H] = c;
-      if constexpr (full) {
-        double a0 = 0.0, aE = 0.0;
-        static_for<R>([&](auto jc) BHAH_INLINE {
-          constexpr int j = decltype(jc)::value + 1;
-          S.commit_pair(pr[(j - 1) % PS], PB);
-          if constexpr (j + PS <= R) S.issue_pair(list[t], j + PS, pr[(j - 1) % PS]);
-          else if constexpr (H == 3 && t + 1 < F1) S.issue_pair(list[t + 1], j + PS - R, pr[(j - 1) % PS]);
-          if constexpr (H == 5 && j == R) issue(std::integral_constant<int, t + 1>{});
-          BHAH_PHASE_BARRIER();
-          double e0[2], eE[2];
-#pragma unroll
-          for (int side = 0; side < 2; side++) {
-            double r0[2 * R + 1], rE[2 * R + 1];
-            r0[R] = rE[R] = 0.0;
-#pragma unroll
-            for (int n = -R; n <= R; n++)
-              if (n != 0) {
-                r0[R + n] = S.pair_at(PB, side, n, 0);
-                rE[R + n] = S.pair_at(PB, side, 0, n);
-              }
-            e0[side] = d1_sum<R>(r0);
-            eE[side] = d1_sum<R>(rE);
-            vP[side ? H - j : H + j] = S.pair_at(PB, side, 0, 0);
-          }
-          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
-          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
-          pin(a0);
-          pin(aE);
-          BHAH_PHASE_BARRIER();
-        });
-        dd[sy(0, PD)] = a0;
-        dd[sy(E, PD)] = aE;
-      }
-      s[PD] = axis_sums<R>(vP);
-      pin(s[PD], t >= F0 && t < F2, full);
-#pragma unroll
-      for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
-      fn(t, s, dd);
-    });
-  }
-}
-
-template <int C, bool AX, int H, int F0, int F1, int F2, int N, class FN>
-__device__ __forceinline__ void run_stencils(const GatherSrc<H>& S, const int (&list)[N], const FN& fn) {
-  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
-  static_for<N>([&](auto tc) BHAH_INLINE {
-    constexpr int t = decltype(tc)::value;
-    const int g = list[t];
-    double v0[2 * H + 1], vE[2 * H + 1], vP[2 * H + 1];
-#pragma unroll
-    for (int m = -H; m <= H; m++) {
-      v0[H + m] = S.at(g, m, 0, 0);
-      vE[H + m] = m == 0 ? v0[H] : S.at(g, 0, m, 0);
-      if constexpr (!AX) vP[H + m] = m == 0 ? v0[H] : S.at(g, 0, 0, m);
-    }
-    if constexpr (AX) vP[H + 1] = S.at(g, 0, 0, 1);
-    AxisSums s[3];
-    double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (t >= F0 && t < F1) {
-      double x[4 * R * R];  // f at (n, m) along (i0, e)
-#pragma unroll
-      for (int m = -R; m <= R; m++)
-#pragma unroll
-        for (int n = -R; n <= R; n++)
-          if (m != 0 && n != 0) x[2 * R * xo<R>(m) + xo<R>(n)] = S.at(g, n, m, 0);
-      BHAH_PHASE_BARRIER();
-      double e[2 * R + 1];
-      e[R] = 0.0;
-#pragma unroll
-      for (int m = -R; m <= R; m++)
-        if (m != 0) {
-          double r[2 * R + 1];
-          r[R] = 0.0;
-#pragma unroll
-          for (int n = -R; n <= R; n++)
-            if (n != 0) r[R + n] = x[2 * R * xo<R>(m) + xo<R>(n)];
-          e[R + m] = d1_sum<R>(r);
-        }
-      dd[sy(0, E)] = d1_sum<R>(e);
-      pin(dd[sy(0, E)]);
-      if constexpr (!AX) {
-        double a0 = 0.0, aE = 0.0;
-#pragma unroll
-        for (int j = 1; j <= R; j++) {
-          double e0[2], eE[2];
-#pragma unroll
-          for (int side = 0; side < 2; side++) {
-            double r0[2 * R + 1], rE[2 * R + 1];
-            r0[R] = rE[R] = 0.0;
-#pragma unroll
-            for (int n = -R; n <= R; n++)
-              if (n != 0) {
-                r0[R + n] = S.at(g, n, 0, side ? -j : j);
-                rE[R + n] = S.at(g, 0, n, side ? -j : j);
-              }
-            e0[side] = d1_sum<R>(r0);
-            eE[side] = d1_sum<R>(rE);
-          }
-          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
-          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
-          pin(a0);
-          pin(aE);
-        }
-        dd[sy(0, PD)] = a0;
-        dd[sy(E, PD)] = aE;
-      }
-    }
-    BHAH_PHASE_BARRIER();
-    s[0] = axis_sums<R>(v0);
-    s[E] = axis_sums<R>(vE);
-    if constexpr (AX) s[PD] = axis_sums_two_planes<R>(v0[H], vP[H + 1]);
-    else s[PD] = axis_sums<R>(vP);
-#pragma unroll
-    for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
-    fn(t, s, dd);
-    BHAH_PHASE_BARRIER();
-  });
-}
 
 // ---- epilogue: the right-hand side or the Runge-Kutta stage combination -------
 // of the wave's twelve gridfunctions list[], results in park[(i) * 64].
@@ -442,27 +145,6 @@ __device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs
   }
 }
 
-// the point of a lane and the tile it belongs to
-struct TilePoint {
-  int t0, t1, t2, i0, i1, i2;
-  unsigned q;
-  bool live;
-};
-
-template <class SRC, int C, bool AX, int H>
-__device__ __forceinline__ SRC make_source(const double* y, const GridDev& G, const TilePoint& p, int lane,
-                                           double* lds) {
-  constexpr bool cyl = C == BHAH_SINH_CYLINDRICAL;
-  if constexpr (SRC::STG) {
-    SRC S;
-    if (cyl) S.init(y, G, 1, p.t0, p.t2, p.i0, p.i2, p.t1, lane, lds, AX);
-    else S.init(y, G, 2, p.t0, p.t1, p.i0, p.i1, p.t2, lane, lds, AX);
-    return S;
-  } else {
-    return SRC{PtT<H>(y, G, C, p.i0, p.i1, p.i2), cyl ? 1 : 2};
-  }
-}
-
 // ---- metric wave ---------------------------------------------------------------
 template <int C, bool AX, bool KO, int H, class SRC>
 __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
@@ -503,7 +185,7 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
     for (int a = 0; a < 6; a++) { Pc[a] = 0.0; ck[a] = 0.0; }
     constexpr int list[6] = {G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
     //   Pc_ij = gammabar^kl h_ij,kl,  ck_kl = gammabar^ab h_ab,kl (unscaled)
-    run_stencils<C, AX, H, 0, 6, 6>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+    run_stencils<C, AX, H, 0, 6, 6, true>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
 #pragma unroll
       for (int k = 0; k < 3; k++)
         if (!(AX && k == PD)) keep(3 * a + k, c.s1[k] * s[k].d1);
@@ -725,7 +407,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
     // the gridfunctions with second derivatives come while few results wait in registers
     constexpr int list[18] = {0, 1, 2, 3, 4, 5, G_VETU0, G_VETU0 + 1, G_VETU0 + 2, G_CF, G_ALPHA,
                               G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2, G_TRK, G_BETU0, G_BETU0 + 1, G_BETU0 + 2};
-    run_stencils<C, AX, H, 6, 11, 15>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+    run_stencils<C, AX, H, 6, 11, 15, true>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
       const bool gauge = (t >= 6 && t < 9) || t == 10 || t >= 15;
       const double adv = gauge ? advect<H>(s, c.ch, c.qg) : advect<H>(s, c.ch, c.q);
       double d[3];

@@ -1,6 +1,7 @@
-// rhs_stencil.h -- the stencil side of the right-hand-side kernel
-// (rhs_fused.hip): the stencil sums of one gridfunction, where its values
-// come from (LDS patches of a tile, or per-lane loads), and the tile walk.
+// rhs_stencil.h -- the stencil side of the right-hand side (rhs_point.h) and
+// the constraints (hamiltonian.hip): the stencil sums of one gridfunction,
+// where its values come from (LDS patches of a tile, or per-lane loads), the
+// loops over gridfunctions, and the tile walk.
 #pragma once
 
 #include <type_traits>
@@ -58,12 +59,15 @@ __device__ __forceinline__ void static_for(const F& f) {
 struct AxisSums {
   double d1, d2, A, K;
 };
-// (first, second: whether d1 and d2 are used at all)
+// (first, second, ADV: whether d1, d2, and A and K are used at all)
+template <bool ADV>
 __device__ __forceinline__ void pin(AxisSums& s, bool first, bool second) {
   if (first) pin(s.d1);
   if (second) pin(s.d2);
-  pin(s.A);
-  pin(s.K);
+  if constexpr (ADV) {
+    pin(s.A);
+    pin(s.K);
+  }
 }
 template <int R>
 __device__ __forceinline__ AxisSums axis_sums(const double (&v)[2 * R + 3]) {
@@ -301,5 +305,333 @@ __device__ __forceinline__ bool tile_point(const GridDev& G, const TileMap& T, i
 // logical position in the walk of the tile a block works on; with G_blocks a
 // multiple of the XCD count, block b runs on XCD b % nxcd
 __device__ __forceinline__ int xcd_remap(int b, int per) { return (b % BHAH_NXCD) * per + b / BHAH_NXCD; }
+
+// a wave's stencil stage: PER main patches on grids with two phi planes (a
+// batch of gridfunctions), else one main patch and a pair of phi planes
+template <bool AX, int H>
+struct StageSize {
+  static constexpr int PER = AX && H == 3 ? 2 : 1;
+  static constexpr int N = AX ? PER * Patch<H>::MAIN : Patch<H>::MAIN + Patch<H>::PAIR;  // doubles
+  static constexpr int SL = (N + 63) / 64;                                              // slots of 64
+};
+
+// scales of the derivatives and upwind coefficients at a point
+template <int H>
+struct Coefs {
+  double s1[3];  // e_k f = s1[k] * (den1 D f)
+  double ch[3], q[3], qg[3];  // advection and dissipation: ch A + q K (metric strength), qg (gauge strength)
+  double kw[3];
+  // f_kl = sc(k, l) * raw second difference
+  __device__ __forceinline__ double sc(int k, int l) const {
+    constexpr double r = FdW<H - 1>::den1 * FdW<H - 1>::den1 / FdW<H - 1>::den2;
+    return k == l ? s1[k] * s1[k] * r : s1[k] * s1[l];
+  }
+};
+template <bool KO, int H>
+__device__ __forceinline__ void make_coefs(const GridDev& G, const Gauge& ga, const double (&iS)[3],
+                                           const double (&v)[3], Coefs<H>& c) {
+  constexpr int R = H - 1;
+  using W = FdW<R>;
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    c.s1[k] = iS[k] * (G.inv_dx[k] * (1.0 / W::den1));
+    const double b = v[k] * c.s1[k];
+    c.ch[k] = 0.5 * b;
+    c.q[k] = c.qg[k] = UpW<R>::sk * fabs(b);
+    if constexpr (KO) {
+      c.kw[k] = G.inv_dx[k] * (1.0 / W::kden);
+      c.qg[k] = fma(ga.dg, c.kw[k], c.q[k]);
+      c.q[k] = fma(ga.dm, c.kw[k], c.q[k]);
+    }
+  }
+}
+
+template <int H>
+__device__ __forceinline__ double advect(const AxisSums (&s)[3], const double (&ch)[3], const double (&q)[3]) {
+  double a = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; k++) a = fma(ch[k], s[k].A, fma(q[k], s[k].K, a));
+  return a;
+}
+
+// ---- stencil drivers ---------------------------------------------------------
+// Runs over the gridfunctions list[0..N): for each, fn(t, axis sums
+// along the three directions, raw second differences dd[sy(k, l)]); dd is
+// formed for t in [F0, F1), first derivatives are used for t in [F0, F2), the
+// upwinded sums where ADV.
+// Identically vanishing phi derivatives of two-plane
+// grids are literal zeros. The arithmetic is the same for both sources.
+// whether d_k d_l, kl = sy(k, l), vanishes identically (mixed with phi on two planes)
+template <bool AX, int PD>
+__device__ __forceinline__ constexpr bool zero_pair(int kl) {
+  return AX && (kl == sy(0, PD) || kl == sy(3 - PD, PD));
+}
+template <int R>
+__device__ __forceinline__ double acc_pair(int j, double acc, double p, double m) {
+  return j == 1 ? FdW<R>::d1[1] * (p - m) : fma(FdW<R>::d1[j], p - m, acc);
+}
+
+template <int C, bool AX, int H, int F0, int F1, int F2, bool ADV, int N, class FN>
+__device__ __forceinline__ void run_stencils(const StagedSrc<H>& S, const int (&list)[N], const FN& fn) {
+  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
+  using SS_ = StagedSrc<H>;
+  auto in_plane = [&](int slot, bool full, bool first, AxisSums(&s)[3], double (&dd)[6], double& c) BHAH_INLINE {
+    double v0[2 * H + 1], vE[2 * H + 1];
+#pragma unroll
+    for (int m = -H; m <= H; m++) {
+      v0[H + m] = S.main_at(slot, m, 0);
+      vE[H + m] = m == 0 ? v0[H] : S.main_at(slot, 0, m);
+    }
+    c = v0[H];
+    s[0] = axis_sums<R>(v0);
+    s[E] = axis_sums<R>(vE);
+    pin<ADV>(s[0], first, full);
+    pin<ADV>(s[E], first, full);
+    if (full) {
+      if constexpr (H == 5) BHAH_PHASE_BARRIER();
+      double e[2 * R + 1];
+      e[R] = 0.0;
+#pragma unroll
+      for (int m = -R; m <= R; m++)
+        if (m != 0) {
+          double r[2 * R + 1];
+          r[R] = 0.0;
+#pragma unroll
+          for (int n = -R; n <= R; n++)
+            if (n != 0) r[R + n] = S.main_at(slot, n, m);
+          e[R + m] = d1_sum<R>(r);
+          pin(e[R + m]);
+          if constexpr (H == 5) BHAH_PHASE_BARRIER();
+        }
+      dd[sy(0, E)] = d1_sum<R>(e);
+      pin(dd[sy(0, E)]);
+    }
+  };
+  if constexpr (AX) {
+    constexpr int PER = StageSize<AX, H>::PER, NB = (N + PER - 1) / PER;
+    typename SS_::MainRegs m[PER];
+    double ph[PER];
+    auto issue = [&](int b) {
+#pragma unroll
+      for (int t = 0; t < PER; t++)
+        if (b * PER + t < N) {
+          S.issue_main(list[b * PER + t], m[t]);
+          ph[t] = S.column(list[b * PER + t], 1);
+        }
+    };
+    issue(0);
+    static_for<NB>([&](auto bc) BHAH_INLINE {
+      constexpr int b = decltype(bc)::value;
+      double o[PER];
+#pragma unroll
+      for (int t = 0; t < PER; t++)
+        if (b * PER + t < N) {
+          S.commit_main(m[t], t);
+          o[t] = ph[t];
+        }
+      if constexpr (b + 1 < NB) issue(b + 1);
+      BHAH_PHASE_BARRIER();
+      static_for<PER>([&](auto tc) BHAH_INLINE {
+        constexpr int t = decltype(tc)::value, tt = b * PER + t;
+        if constexpr (tt < N) {
+          AxisSums s[3];
+          double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
+          in_plane(t, tt >= F0 && tt < F1, tt >= F0 && tt < F2, s, dd, c);
+          s[PD] = axis_sums_two_planes<R>(c, o[t]);
+#pragma unroll
+          for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
+          fn(tt, s, dd);
+        }
+      });
+    });
+  } else {
+    constexpr int PB = SS_::PG::MAIN;  // the phi planes' place in the stage
+    // Loads run one gridfunction ahead of their use. At 8th order, where a
+    // gridfunction has four pairs of phi planes, one pair and then the next
+    // main patch: more in flight spills (3-D production step 6.0 instead of
+    // 5.2 ms); at 4th order deeper prefetch measures the same.
+    constexpr int PS = H == 3 ? 2 : 1;
+    typename SS_::MainRegs m;
+    typename SS_::PairRegs pr[PS];
+    double col[2 * H];  // phi offsets -H..-1, 1..H
+    auto issue = [&](auto tc) BHAH_INLINE {
+      constexpr int t = decltype(tc)::value;
+      if constexpr (t < N) {
+        S.issue_main(list[t], m);
+#pragma unroll
+        for (int o = 1; o <= H; o++)
+          if (o == H ? ADV : !(t >= F0 && t < F1)) {
+            col[H - o] = S.column(list[t], -o);
+            col[H + o - 1] = S.column(list[t], o);
+          }
+      }
+    };
+    issue(std::integral_constant<int, 0>{});
+    if constexpr (F0 == 0) {
+#pragma unroll
+      for (int j = 1; j <= PS; j++) S.issue_pair(list[0], j, pr[j - 1]);
+    }
+    static_for<N>([&](auto tc) BHAH_INLINE {
+      constexpr int t = decltype(tc)::value;
+      constexpr bool full = t >= F0 && t < F1;
+      double vP[2 * H + 1];
+      vP[0] = vP[2 * H] = 0.0;
+      S.commit_main(m, 0);
+#pragma unroll
+      for (int o = 1; o <= H; o++)
+        if (o == H ? ADV : !full) {
+          vP[H - o] = col[H - o];
+          vP[H + o] = col[H + o - 1];
+        }
+      if constexpr (H == 3 || !full) issue(std::integral_constant<int, t + 1>{});
+      // the first pairs: a gridfunction early, at 8th order with their own main patch
+      if constexpr (H == 3 ? t + 1 == F0 : full && t > 0) {
+#pragma unroll
+        for (int j = 1; j <= PS; j++) S.issue_pair(list[H == 3 ? F0 : t], j, pr[j - 1]);
+      }
+      BHAH_PHASE_BARRIER();
+      AxisSums s[3];
+      double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
+      in_plane(0, full, t >= F0 && t < F2, s, dd, c);
+      vP[H] = c;
+      if constexpr (full) {
+        double a0 = 0.0, aE = 0.0;
+        static_for<R>([&](auto jc) BHAH_INLINE {
+          constexpr int j = decltype(jc)::value + 1;
+          S.commit_pair(pr[(j - 1) % PS], PB);
+          if constexpr (j + PS <= R) S.issue_pair(list[t], j + PS, pr[(j - 1) % PS]);
+          else if constexpr (H == 3 && t + 1 < F1) S.issue_pair(list[t + 1], j + PS - R, pr[(j - 1) % PS]);
+          if constexpr (H == 5 && j == R) issue(std::integral_constant<int, t + 1>{});
+          BHAH_PHASE_BARRIER();
+          double e0[2], eE[2];
+#pragma unroll
+          for (int side = 0; side < 2; side++) {
+            double r0[2 * R + 1], rE[2 * R + 1];
+            r0[R] = rE[R] = 0.0;
+#pragma unroll
+            for (int n = -R; n <= R; n++)
+              if (n != 0) {
+                r0[R + n] = S.pair_at(PB, side, n, 0);
+                rE[R + n] = S.pair_at(PB, side, 0, n);
+              }
+            e0[side] = d1_sum<R>(r0);
+            eE[side] = d1_sum<R>(rE);
+            vP[side ? H - j : H + j] = S.pair_at(PB, side, 0, 0);
+          }
+          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
+          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
+          pin(a0);
+          pin(aE);
+          BHAH_PHASE_BARRIER();
+        });
+        dd[sy(0, PD)] = a0;
+        dd[sy(E, PD)] = aE;
+      }
+      s[PD] = axis_sums<R>(vP);
+      pin<ADV>(s[PD], t >= F0 && t < F2, full);
+#pragma unroll
+      for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
+      fn(t, s, dd);
+    });
+  }
+}
+
+template <int C, bool AX, int H, int F0, int F1, int F2, bool ADV, int N, class FN>
+__device__ __forceinline__ void run_stencils(const GatherSrc<H>& S, const int (&list)[N], const FN& fn) {
+  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
+  static_for<N>([&](auto tc) BHAH_INLINE {
+    constexpr int t = decltype(tc)::value;
+    const int g = list[t];
+    double v0[2 * H + 1], vE[2 * H + 1], vP[2 * H + 1];
+#pragma unroll
+    for (int m = -H; m <= H; m++) {
+      v0[H + m] = S.at(g, m, 0, 0);
+      vE[H + m] = m == 0 ? v0[H] : S.at(g, 0, m, 0);
+      if constexpr (!AX) vP[H + m] = m == 0 ? v0[H] : S.at(g, 0, 0, m);
+    }
+    if constexpr (AX) vP[H + 1] = S.at(g, 0, 0, 1);
+    AxisSums s[3];
+    double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (t >= F0 && t < F1) {
+      double x[4 * R * R];  // f at (n, m) along (i0, e)
+#pragma unroll
+      for (int m = -R; m <= R; m++)
+#pragma unroll
+        for (int n = -R; n <= R; n++)
+          if (m != 0 && n != 0) x[2 * R * xo<R>(m) + xo<R>(n)] = S.at(g, n, m, 0);
+      BHAH_PHASE_BARRIER();
+      double e[2 * R + 1];
+      e[R] = 0.0;
+#pragma unroll
+      for (int m = -R; m <= R; m++)
+        if (m != 0) {
+          double r[2 * R + 1];
+          r[R] = 0.0;
+#pragma unroll
+          for (int n = -R; n <= R; n++)
+            if (n != 0) r[R + n] = x[2 * R * xo<R>(m) + xo<R>(n)];
+          e[R + m] = d1_sum<R>(r);
+        }
+      dd[sy(0, E)] = d1_sum<R>(e);
+      pin(dd[sy(0, E)]);
+      if constexpr (!AX) {
+        double a0 = 0.0, aE = 0.0;
+#pragma unroll
+        for (int j = 1; j <= R; j++) {
+          double e0[2], eE[2];
+#pragma unroll
+          for (int side = 0; side < 2; side++) {
+            double r0[2 * R + 1], rE[2 * R + 1];
+            r0[R] = rE[R] = 0.0;
+#pragma unroll
+            for (int n = -R; n <= R; n++)
+              if (n != 0) {
+                r0[R + n] = S.at(g, n, 0, side ? -j : j);
+                rE[R + n] = S.at(g, 0, n, side ? -j : j);
+              }
+            e0[side] = d1_sum<R>(r0);
+            eE[side] = d1_sum<R>(rE);
+          }
+          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
+          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
+          pin(a0);
+          pin(aE);
+        }
+        dd[sy(0, PD)] = a0;
+        dd[sy(E, PD)] = aE;
+      }
+    }
+    BHAH_PHASE_BARRIER();
+    s[0] = axis_sums<R>(v0);
+    s[E] = axis_sums<R>(vE);
+    if constexpr (AX) s[PD] = axis_sums_two_planes<R>(v0[H], vP[H + 1]);
+    else s[PD] = axis_sums<R>(vP);
+#pragma unroll
+    for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
+    fn(t, s, dd);
+    BHAH_PHASE_BARRIER();
+  });
+}
+
+// the point of a lane and the tile it belongs to
+struct TilePoint {
+  int t0, t1, t2, i0, i1, i2;
+  unsigned q;
+  bool live;
+};
+
+template <class SRC, int C, bool AX, int H>
+__device__ __forceinline__ SRC make_source(const double* y, const GridDev& G, const TilePoint& p, int lane,
+                                           double* lds) {
+  constexpr bool cyl = C == BHAH_SINH_CYLINDRICAL;
+  if constexpr (SRC::STG) {
+    SRC S;
+    if (cyl) S.init(y, G, 1, p.t0, p.t2, p.i0, p.i2, p.t1, lane, lds, AX);
+    else S.init(y, G, 2, p.t0, p.t1, p.i0, p.i1, p.t2, lane, lds, AX);
+    return S;
+  } else {
+    return SRC{PtT<H>(y, G, C, p.i0, p.i1, p.i2), cyl ? 1 : 2};
+  }
+}
 
 }  // namespace bhah
