@@ -99,20 +99,35 @@ struct HostGhosts {
   std::vector<double> w;
 };
 
-// RK stage epilogue of the right-hand-side kernel: with rhs != nullptr the
-// right-hand side k is stored; otherwise out1 = base1 + c1 k and, if out2 is
-// set, out2 = base2 + c2 k, gridfunction by gridfunction. With base2 set but
-// no out2 the stage mixes two states: out1 = m1 base1 + m2 base2 + c1 k.
+// Stage epilogue of the right-hand-side kernel: with rhs != nullptr the
+// right-hand side k is stored; otherwise out is, gridfunction by
+// gridfunction,
+//   base4 set: base1 + ((base2 - base1) + 2 (base3 - base1) + (base4 - base1))/3
+//              + c k   (the last RK4 stage: y, A, B, C)
+//   base2 set: m1 base1 + m2 base2 + c k   (SSPRK3)
+//   else     : base1 + c k
 struct StageArgs {
   double* rhs;
   const double* base1;
-  double* out1;
-  double c1;
+  double* out;
+  double c;
   const double* base2;
-  double* out2;
-  double c2;
   double m1, m2;
+  const double* base3;
+  const double* base4;
 };
+// the three combinations (explicit multiply-adds: every kernel rounds alike)
+__host__ __device__ __forceinline__ double combine_plain(const StageArgs& st, double k, double b1) {
+  return fma(st.c, k, b1);
+}
+__host__ __device__ __forceinline__ double combine_mix(const StageArgs& st, double k, double b1, double b2) {
+  return fma(st.c, k, fma(st.m2, b2, st.m1 * b1));
+}
+__host__ __device__ __forceinline__ double combine_rk4(const StageArgs& st, double k, double b1, double b2, double b3,
+                                                       double b4) {
+  const double d = fma(2.0, b3 - b1, (b2 - b1) + (b4 - b1));
+  return fma(st.c, k, fma(1.0 / 3.0, d, b1));
+}
 
 // Gauge and dissipation parameters as the right-hand-side kernel takes them:
 // eta of Eq. 15, Kreiss-Oliger strengths for gauge and metric variables.
@@ -289,7 +304,7 @@ void launch_radiation_batch(const BatchJob* jobs, const BatchHdr* hdr, const int
 void launch_constraints(const GridDev& G, const double* y, double* H, double* Mo, double* Co, hipStream_t s);
 
 // The four stages of one classical RK4 step on state y with workspace ws
-// (three state-sized arrays A, B, Cacc): inputs, stage combinations and the
+// (three state-sized arrays A, B, C): inputs, stage combinations and the
 // array whose ghosts are filled after each stage.
 void rk4_stages(double dt, double* y, double* ws, long long n, StageArgs st[4], const double* in[4],
                 double* gdst[4]);

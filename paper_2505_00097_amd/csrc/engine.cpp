@@ -207,7 +207,7 @@ void Engine::build_blob(const std::vector<TileCfg>& cfg, const std::vector<int>&
       b.in[k] = in[k];
       b.gdst[k] = gd[k];
     }
-    b.st[4] = StageArgs{e.ws, nullptr, nullptr, 0.0, nullptr, nullptr, 0.0};
+    b.st[4] = StageArgs{e.ws, nullptr, nullptr, 0.0, nullptr, 0.0, 0.0, nullptr, nullptr};
     b.in[4] = e.y;
     b.gdst[4] = nullptr;
   }

@@ -207,15 +207,10 @@ __device__ __forceinline__ void radiation_point(const GridDev& G, const RadDev& 
 #pragma unroll
   for (int j = 0; j < GF_PER; j++) {
     const long long e = (g0 + j) * G.sgf + q;
-    if (st.rhs) {
-      st.rhs[e] = k[j];
-    } else if (st.out2 == nullptr && st.base2 != nullptr) {
-      st.out1[e] = st.m1 * st.base1[e] + st.m2 * st.base2[e] + st.c1 * k[j];
-    } else {
-      const double b1 = st.base1[e], b2 = st.out2 ? st.base2[e] : 0.0;
-      st.out1[e] = b1 + st.c1 * k[j];
-      if (st.out2) st.out2[e] = b2 + st.c2 * k[j];
-    }
+    if (st.rhs) st.rhs[e] = k[j];
+    else if (st.base4) st.out[e] = combine_rk4(st, k[j], st.base1[e], st.base2[e], st.base3[e], st.base4[e]);
+    else if (st.base2) st.out[e] = combine_mix(st, k[j], st.base1[e], st.base2[e]);
+    else st.out[e] = combine_plain(st, k[j], st.base1[e]);
   }
 }
 

@@ -59,20 +59,69 @@ struct Stage : StageSize<AX, H> {
 // ---- epilogue: the right-hand side or the Runge-Kutta stage combination -------
 // of the wave's twelve gridfunctions list[], results in park[(i) * 64].
 // Every base value is read before any result is stored. Within a stage the
-// arrays never overlap (RK4: base1 is y or Cacc, out1 is A, B or y; base2 and
-// out2 are Cacc at the same point; SSPRK3 mixes y with A or B into B or y),
-// but the compiler cannot know it and would otherwise put each load behind
-// the stores before it.
+// arrays never overlap but at the same point (RK4: y, A, B, C into A, B, C or
+// y; SSPRK3 mixes y with A or B into B or y), but the compiler cannot know it
+// and would otherwise put each load behind the stores before it.
 // Row pairs: where all 64 lanes are live and lanes 2p, 2p+1 hold adjacent
 // points of one row, lane l takes points 2p and 2p+1, p = l mod 32, of
 // gridfunction list[2 i + l / 32], one 16-byte access for two gridfunctions
 // and two points: half the vector memory instructions of the per-lane form.
 typedef double bhah_d2 __attribute__((ext_vector_type(2), aligned(8)));
 
+// V: double (per lane, twelve results) or bhah_d2 (row pairs, six); e(i) is
+// the element of result i, res(i) its value
+template <class V, int N, class E, class RES>
+__device__ __forceinline__ void store_stage(const StageArgs& st, const E& e, const RES& res) {
+  auto each = [](const V& k, auto f) {
+    if constexpr (std::is_same_v<V, double>) return f(k, 0);
+    else return V{f(k.x, 0), f(k.y, 1)};
+  };
+  auto el = [](const V& v, int h) {
+    if constexpr (std::is_same_v<V, double>) return v;
+    else return h ? v.y : v.x;
+  };
+  auto ld = [&](const double* b, V(&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i++) x[i] = *(const V*)(b + e(i));
+  };
+  if (st.rhs) {
+#pragma unroll
+    for (int i = 0; i < N; i++) *(V*)(st.rhs + e(i)) = res(i);
+    return;
+  }
+  V b1[N];
+  ld(st.base1, b1);
+  if (st.base4) {
+    V b2[N], b3[N], b4[N];
+    ld(st.base2, b2);
+    ld(st.base3, b3);
+    ld(st.base4, b4);
+    BHAH_PHASE_BARRIER();
+#pragma unroll
+    for (int i = 0; i < N; i++)
+      *(V*)(st.out + e(i)) = each(res(i), [&](double k, int h) {
+        return combine_rk4(st, k, el(b1[i], h), el(b2[i], h), el(b3[i], h), el(b4[i], h));
+      });
+    return;
+  }
+  if (st.base2) {
+    V b2[N];
+    ld(st.base2, b2);
+    BHAH_PHASE_BARRIER();
+#pragma unroll
+    for (int i = 0; i < N; i++)
+      *(V*)(st.out + e(i)) =
+          each(res(i), [&](double k, int h) { return combine_mix(st, k, el(b1[i], h), el(b2[i], h)); });
+    return;
+  }
+  BHAH_PHASE_BARRIER();
+#pragma unroll
+  for (int i = 0; i < N; i++)
+    *(V*)(st.out + e(i)) = each(res(i), [&](double k, int h) { return combine_plain(st, k, el(b1[i], h)); });
+}
+
 __device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs& st, unsigned q, bool live,
                                                const int (&list)[12], const double* __restrict__ park, int lane) {
-  const bool two = st.out2 != nullptr, mix = !two && st.base2 != nullptr, same = st.base2 == st.base1;
-  auto out1m = [&](double k, double x1, double x2) { return fma(st.c1, k, fma(st.m2, x2, st.m1 * x1)); };
   const int p2 = 2 * (lane & 31), gs = lane >> 5;
   const unsigned qa = (unsigned)__shfl((int)q, p2), qb = (unsigned)__shfl((int)q, p2 + 1);
   if (__all(live && qb == qa + 1u)) {
@@ -80,69 +129,12 @@ __device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs
     long long e[6];
 #pragma unroll
     for (int i = 0; i < 6; i++) e[i] = (gs ? list[2 * i + 1] : list[2 * i]) * G.sgf + (long long)qa;
-    if (st.rhs) {
-#pragma unroll
-      for (int i = 0; i < 6; i++) *(bhah_d2*)(st.rhs + e[i]) = bhah_d2{pk[128 * i], pk[128 * i + 1]};
-      return;
-    }
-    bhah_d2 b1[6], b2[6];
-#pragma unroll
-    for (int i = 0; i < 6; i++) b1[i] = *(const bhah_d2*)(st.base1 + e[i]);
-    if ((two || mix) && !same) {
-#pragma unroll
-      for (int i = 0; i < 6; i++) b2[i] = *(const bhah_d2*)(st.base2 + e[i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 6; i++) b2[i] = b1[i];
-    }
-    BHAH_PHASE_BARRIER();
-    if (mix) {
-#pragma unroll
-      for (int i = 0; i < 6; i++)
-        *(bhah_d2*)(st.out1 + e[i]) =
-            bhah_d2{out1m(pk[128 * i], b1[i].x, b2[i].x), out1m(pk[128 * i + 1], b1[i].y, b2[i].y)};
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < 6; i++)
-      *(bhah_d2*)(st.out1 + e[i]) =
-          bhah_d2{fma(st.c1, pk[128 * i], b1[i].x), fma(st.c1, pk[128 * i + 1], b1[i].y)};
-    if (two) {
-#pragma unroll
-      for (int i = 0; i < 6; i++)
-        *(bhah_d2*)(st.out2 + e[i]) =
-            bhah_d2{fma(st.c2, pk[128 * i], b2[i].x), fma(st.c2, pk[128 * i + 1], b2[i].y)};
-    }
+    store_stage<bhah_d2, 6>(st, [&](int i) { return e[i]; },
+                            [&](int i) { return bhah_d2{pk[128 * i], pk[128 * i + 1]}; });
     return;
   }
   if (!live) return;
-  if (st.rhs) {
-#pragma unroll
-    for (int i = 0; i < 12; i++) st.rhs[list[i] * G.sgf + q] = park[i * 64];
-    return;
-  }
-  double b1[12], b2[12];
-#pragma unroll
-  for (int i = 0; i < 12; i++) b1[i] = st.base1[list[i] * G.sgf + q];
-  if ((two || mix) && !same) {
-#pragma unroll
-    for (int i = 0; i < 12; i++) b2[i] = st.base2[list[i] * G.sgf + q];
-  } else {
-#pragma unroll
-    for (int i = 0; i < 12; i++) b2[i] = b1[i];
-  }
-  BHAH_PHASE_BARRIER();
-  if (mix) {
-#pragma unroll
-    for (int i = 0; i < 12; i++) st.out1[list[i] * G.sgf + q] = out1m(park[i * 64], b1[i], b2[i]);
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 12; i++) st.out1[list[i] * G.sgf + q] = fma(st.c1, park[i * 64], b1[i]);
-  if (two) {
-#pragma unroll
-    for (int i = 0; i < 12; i++) st.out2[list[i] * G.sgf + q] = fma(st.c2, park[i * 64], b2[i]);
-  }
+  store_stage<double, 12>(st, [&](int i) { return list[i] * G.sgf + q; }, [&](int i) { return park[i * 64]; });
 }
 
 // ---- metric wave ---------------------------------------------------------------
