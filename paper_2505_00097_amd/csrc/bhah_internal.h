@@ -9,7 +9,12 @@
 
 #include "../../include/bhah.h"
 
+struct bhah_grid;
+
 namespace bhah {
+
+// patch of the kernels that stage their stencils: points along i0 and along e
+constexpr int PATCH_LX = 4, PATCH_X = 1 << PATCH_LX, PATCH_E = 64 >> PATCH_LX;
 
 constexpr int NG = 3;     // ghost layers of the 4th-order grids (5 for 8th order)
 constexpr int NGF = 24;   // evolved gridfunctions
@@ -79,6 +84,19 @@ struct GhostDev {
   const double* w;      // [n_terms]
 };
 
+// Ghosts that the right-hand-side kernel writes itself: those of a stage whose
+// sources all lie in one 16 x 4 patch, grouped by patch (patch number
+// (phi index * ne + e index) * nx + i0 index). A ghost is four words: dst;
+// parity | terms << 3 (1 or 3) or parity | 32 | terms << 8; then up to
+// three source lanes (6 bits each) and as many weights (signed bytes), or the
+// offset of its (lane, weight) pairs in `terms`.
+struct PushDev {
+  const int* start;  // [patches + 1]; nullptr: none
+  const int* rec;    // [4 * ghosts]
+  const int* terms;  // [2 * terms]
+  int nx, ne;        // patches along i0 and e
+};
+
 // Pure-outer ghost points evolved by the radiation condition: flat index,
 // packed stencil starts (s0 + 2R) | (s2 + 2R) << 4 of the (2R+1)-point
 // logical derivatives along xx0 and xx2 (s in -2R..0, R = N_G - 1), and per
@@ -92,12 +110,27 @@ struct RadDev {
   const double* coef;  // [n][3]
   int R;              // stencil radius N_G - 1
   const double* w;    // [2R+1][2R+1]: row s + 2R holds the weights of nodes s..s+2R
+  // inner ghosts that copy outer point t (in a stage): pairs (index, parity)
+  // copy[2 k], k = copy_start[t] .. copy_start[t + 1] - 1
+  const int* copy_start;
+  const int* copy;
 };
 // host copy of a ghost list in the GhostDev layout
 struct HostGhosts {
   std::vector<int> dst, start, par, src;
   std::vector<double> w;
 };
+// host copy of the pushed ghosts, and the ghosts of the stage that are not
+struct HostPush {
+  std::vector<int> start, rec, terms;
+  int nx = 0, ne = 0;
+  HostGhosts left;
+};
+// The pushed ghosts of a stage list (dst, start, par, src, w) of grid g; a
+// source that is not an interior point makes its ghost one of the left ones,
+// as does a source outside the patch of the others.
+HostPush build_push(const bhah_grid* g, const std::vector<int>& dst, const std::vector<int>& start,
+                    const std::vector<int>& par, const std::vector<int>& src, const std::vector<double>& w);
 
 // Stage epilogue of the right-hand-side kernel: with rhs != nullptr the
 // right-hand side k is stored; otherwise out is, gridfunction by
@@ -259,10 +292,11 @@ struct bhah_grid {
   // as one-hop parity copies (all of them; those with an interior phi index)
   std::vector<int> rad_q, rad_shift;
   std::vector<double> rad_coef, rad_w;
+  std::vector<int> rad_copy_start, rad_copy;  // inner ghosts that copy an outer point (RadDev::copy)
   bhah::HostGhosts inner_full, inner_stage;
   bhah::RadDev rad{};
   bhah::GhostDev ghost_inner{}, ghost_inner_stage{};
-  int* d_rad_i = nullptr;     // q | shift
+  int* d_rad_i = nullptr;     // q | shift | copy_start | copy
   double* d_rad_c = nullptr;
   int* d_inner_ints[2] = {nullptr, nullptr};
   double* d_inner_w[2] = {nullptr, nullptr};
@@ -272,6 +306,14 @@ struct bhah_grid {
   double* d_w;
   int* d_rints;     // the same for the stage ghost list
   double* d_rw;
+  // stage ghosts written by the right-hand-side kernel, and the list of the
+  // others (on radiation grids without those that the radiation kernel copies)
+  bhah::HostPush push;
+  bhah::PushDev push_dev{};
+  bhah::GhostDev ghost_left{};
+  int* d_push = nullptr;      // start | rec | terms
+  int* d_left_ints = nullptr;
+  double* d_left_w = nullptr;
   long long n_int_block;
 };
 
@@ -280,8 +322,20 @@ namespace bhah {
 void launch_ghosts(const GhostDev& gh, double* y, long long sgf, hipStream_t s);
 int launch_brill_lindquist(const GridDev& G, int n, const double* m, const double* pos, int lapse_kind,
                            double* y, hipStream_t s);
+// push: ghosts of st.out to write beside the interior (where rhs_pushes)
 void launch_rhs_fused(const GridDev& G, const Gauge& ga, const double* y, double* aux, const StageArgs& st,
-                      hipStream_t s, const TileCfg& cfg);
+                      hipStream_t s, const TileCfg& cfg, const PushDev& push = PushDev{});
+// whether a tile choice runs the staged kernel
+inline bool rhs_staged(int coord, const TileCfg& c) { return c.lx == 6 || !tile_fits_periodic(coord, c); }
+// Whether the solo kernel writes the stage ghosts itself: the staged forms
+// but the 8th-order general one, which has no registers for it (3-D
+// production step 5.06 -> 5.23 ms). The ensemble kernels do not either: with
+// tiles enough to fill the card the ghost kernel costs 33 us of a 370 us stage
+// for 16 jobs, and border tiles that write their ghosts make the step 1% longer.
+inline bool rhs_pushes(const GridDev& G, const TileCfg& c) {
+  const bool two = (G.coord == BHAH_SINH_CYLINDRICAL ? G.N1 : G.N2) == 2;
+  return rhs_staged(G.coord, c) && (two || G.ng == NG);
+}
 TileMap make_tilemap(const GridDev& G, int lx, int ly, int band);
 // the tile map of the kernels that bring their stencils through LDS patches
 // (rhs_stencil.h): 16 points along i0 by 4 along the other non-periodic
@@ -297,8 +351,10 @@ void launch_ghosts_batch(const BatchJob* jobs, const BatchHdr* hdr, const int2* 
                          int kk, bool last, int blocks, hipStream_t s);
 void launch_hamiltonian(const GridDev& G, const double* y, double* H, hipStream_t s);
 // radiation condition at the pure-outer points of one stage: the right-hand
-// side of `in` combined as in st (same semantics as the RHS kernel)
-void launch_radiation(const GridDev& G, const RadDev& R, const double* in, const StageArgs& st, hipStream_t s);
+// side of `in` combined as in st (same semantics as the RHS kernel); with
+// copy also the inner ghosts that copy an outer point
+void launch_radiation(const GridDev& G, const RadDev& R, const double* in, const StageArgs& st, bool copy,
+                      hipStream_t s);
 void launch_radiation_batch(const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,
                             const int* counts, int kk, int blocks, hipStream_t s);
 void launch_constraints(const GridDev& G, const double* y, double* H, double* Mo, double* Co, hipStream_t s);

@@ -80,7 +80,7 @@ static void free_device(bhah_grid* g) {
     if (g->d_tab[d]) (void)hipFree(g->d_tab[d]);
   for (void* p : {(void*)g->d_ints, (void*)g->d_w, (void*)g->d_rints, (void*)g->d_rw, (void*)g->d_rad_i,
                   (void*)g->d_rad_c, (void*)g->d_inner_ints[0], (void*)g->d_inner_w[0], (void*)g->d_inner_ints[1],
-                  (void*)g->d_inner_w[1]})
+                  (void*)g->d_inner_w[1], (void*)g->d_push, (void*)g->d_left_ints, (void*)g->d_left_w})
     if (p) (void)hipFree(p);
 }
 
@@ -109,21 +109,43 @@ static hipError_t upload_ghosts(const std::vector<int>& dst, const std::vector<i
   return e;
 }
 
+// Upload the ghosts that the right-hand-side kernel writes and the list of the
+// stage's other ghosts.
+static hipError_t upload_push(bhah_grid* g) {
+  const HostPush& P = g->push;
+  // records first: they are read as 16-byte words
+  std::vector<int> packed(P.rec);
+  packed.insert(packed.end(), P.terms.begin(), P.terms.end());
+  packed.insert(packed.end(), P.start.begin(), P.start.end());
+  hipError_t e = hipMalloc((void**)&g->d_push, packed.size() * sizeof(int));
+  if (e == hipSuccess) e = hipMemcpy(g->d_push, packed.data(), packed.size() * sizeof(int), hipMemcpyHostToDevice);
+  const int* terms = g->d_push + P.rec.size();
+  g->push_dev = PushDev{terms + P.terms.size(), g->d_push, terms, P.nx, P.ne};
+  if (e == hipSuccess)
+    e = upload_ghosts(P.left.dst, P.left.start, P.left.par, P.left.src, P.left.w, &g->d_left_ints, &g->d_left_w,
+                      &g->ghost_left);
+  return e;
+}
+
 // Upload the radiation lists: the outer points (q | shift packed, 3
-// coefficients each) and the two inner-copy lists.
+// coefficients each, their copies) and the two inner-copy lists.
 static hipError_t upload_radiation(bhah_grid* g) {
   const size_t n = g->rad_q.size();
   std::vector<int> packed(g->rad_q);
   packed.insert(packed.end(), g->rad_shift.begin(), g->rad_shift.end());
+  packed.insert(packed.end(), g->rad_copy_start.begin(), g->rad_copy_start.end());
+  packed.insert(packed.end(), g->rad_copy.begin(), g->rad_copy.end());
   // coefficients [n][3], then the stencil weight table
   const size_t nw = g->rad_w.size();
   std::vector<double> coef(g->rad_coef);
   coef.insert(coef.end(), g->rad_w.begin(), g->rad_w.end());
-  hipError_t e = hipMalloc((void**)&g->d_rad_i, (n ? 2 * n : 1) * sizeof(int));
+  hipError_t e = hipMalloc((void**)&g->d_rad_i, packed.size() * sizeof(int));
   if (e == hipSuccess) e = hipMalloc((void**)&g->d_rad_c, (3 * n + nw) * sizeof(double));
-  if (e == hipSuccess && n) e = hipMemcpy(g->d_rad_i, packed.data(), 2 * n * sizeof(int), hipMemcpyHostToDevice);
+  if (e == hipSuccess)
+    e = hipMemcpy(g->d_rad_i, packed.data(), packed.size() * sizeof(int), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(g->d_rad_c, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice);
-  g->rad = RadDev{(int)n, g->d_rad_i, g->d_rad_i + n, g->d_rad_c, g->params.nghosts - 1, g->d_rad_c + 3 * n};
+  g->rad = RadDev{(int)n, g->d_rad_i, g->d_rad_i + n, g->d_rad_c, g->params.nghosts - 1, g->d_rad_c + 3 * n,
+                  g->d_rad_i + 2 * n, g->d_rad_i + 3 * n + 1};
   const HostGhosts* L[2] = {&g->inner_full, &g->inner_stage};
   GhostDev* D[2] = {&g->ghost_inner, &g->ghost_inner_stage};
   for (int k = 0; k < 2 && e == hipSuccess; k++)
@@ -133,18 +155,20 @@ static hipError_t upload_radiation(bhah_grid* g) {
 }
 
 // One stage of a time integrator: the interior right-hand side combined as in
-// st, with the radiation boundary also at the pure-outer points, then the
-// ghost fill of the stage's result (all ghosts after the last stage, those
-// with an interior phi index before: the stencils never read phi ghosts).
+// st, with the radiation boundary also at the pure-outer points, and the ghosts
+// of the stage's result: all of them after the last stage; before, those with
+// an interior phi index (the stencils never read phi ghosts). Where the
+// right-hand-side kernel writes these itself (rhs_pushes), the radiation kernel
+// adds the copies of its points and the ghost kernel the few in ghost_left.
 static int run_stage(const bhah_grid* g, const Gauge& ga, const double* in, const StageArgs& st, double* gdst,
                      bool last, hipStream_t s) {
-  launch_rhs_fused(g->dev, ga, in, nullptr, st, s, g->tile);
-  if (g->params.bc_kind == BHAH_BC_RADIATION) {
-    launch_radiation(g->dev, g->rad, in, st, s);
-    launch_ghosts(last ? g->ghost_inner : g->ghost_inner_stage, gdst, g->dev.sgf, s);
-  } else {
-    launch_ghosts(last ? g->ghost : g->ghost_stage, gdst, g->dev.sgf, s);
-  }
+  const bool rad = g->params.bc_kind == BHAH_BC_RADIATION;
+  const bool push = !last && rhs_pushes(g->dev, g->tile);
+  launch_rhs_fused(g->dev, ga, in, nullptr, st, s, g->tile, push ? g->push_dev : PushDev{});
+  if (rad) launch_radiation(g->dev, g->rad, in, st, push, s);
+  if (push) launch_ghosts(g->ghost_left, gdst, g->dev.sgf, s);
+  else if (rad) launch_ghosts(last ? g->ghost_inner : g->ghost_inner_stage, gdst, g->dev.sgf, s);
+  else launch_ghosts(last ? g->ghost : g->ghost_stage, gdst, g->dev.sgf, s);
   return check_launch("stage launch");
 }
 
@@ -178,6 +202,7 @@ int bhah_grid_create(const bhah_grid_params* params, bhah_grid** out) {
     e = upload_ghosts(g->g_dst, g->g_start, g->g_par, g->g_src, g->g_w, &g->d_ints, &g->d_w, &g->ghost);
   if (e == hipSuccess)
     e = upload_ghosts(g->r_dst, g->r_start, g->r_par, g->r_src, g->r_w, &g->d_rints, &g->d_rw, &g->ghost_stage);
+  if (e == hipSuccess) e = upload_push(g);
   if (e == hipSuccess && params->bc_kind == BHAH_BC_RADIATION) e = upload_radiation(g);
   if (e != hipSuccess) {
     const int code = e == hipErrorOutOfMemory ? BHAH_ENOMEM : BHAH_EDEVICE;
@@ -259,7 +284,7 @@ int bhah_bssn_rhs(const bhah_grid* g, const bhah_gauge_params* gp, const double*
   if (int rc = check_gauge(gp, "bhah_bssn_rhs")) return rc;
   StageArgs st{rhs, nullptr, nullptr, 0.0, nullptr, 0.0, 0.0, nullptr, nullptr};
   launch_rhs_fused(g->dev, gauge_of(*gp), y, aux, st, (hipStream_t)stream, g->tile);
-  if (g->params.bc_kind == BHAH_BC_RADIATION) launch_radiation(g->dev, g->rad, y, st, (hipStream_t)stream);
+  if (g->params.bc_kind == BHAH_BC_RADIATION) launch_radiation(g->dev, g->rad, y, st, false, (hipStream_t)stream);
   return check_launch("bhah_bssn_rhs");
 }
 

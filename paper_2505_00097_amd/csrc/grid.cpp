@@ -110,6 +110,74 @@ std::vector<double> one_sided_weights(int R) {
 
 }  // namespace
 
+HostPush build_push(const bhah_grid* g, const std::vector<int>& dst, const std::vector<int>& start,
+                    const std::vector<int>& par, const std::vector<int>& src, const std::vector<double>& w) {
+  HostPush P;
+  const Classifier& c = g->classify;
+  const int pd = c.coord == BHAH_SINH_CYLINDRICAL ? 1 : 2, ed = 3 - pd;
+  P.nx = (c.N[0] + PATCH_X - 1) / PATCH_X;
+  P.ne = (c.N[ed] + PATCH_E - 1) / PATCH_E;
+  // patch and lane of an interior point (patch -1 for any other)
+  auto place = [&](int q, int& lane) {
+    const int i[3] = {q % c.n[0] - c.ng, (q / c.n[0]) % c.n[1] - c.ng, q / (c.n[0] * c.n[1]) - c.ng};
+    for (int d = 0; d < 3; d++)
+      if (i[d] < 0 || i[d] >= c.N[d]) return -1;
+    lane = i[0] % PATCH_X + PATCH_X * (i[ed] % PATCH_E);
+    return (i[pd] * P.ne + i[ed] / PATCH_E) * P.nx + i[0] / PATCH_X;
+  };
+  const size_t n = dst.size();
+  std::vector<int> patch(n);
+  P.start.assign((size_t)P.nx * P.ne * c.N[pd] + 1, 0);
+  for (size_t t = 0; t < n; t++) {
+    int lane;
+    patch[t] = place(src[start[t]], lane);
+    for (int k = start[t] + 1; k < start[t + 1] && patch[t] >= 0; k++)
+      if (place(src[k], lane) != patch[t]) patch[t] = -1;
+    if (patch[t] >= 0) {
+      P.start[patch[t] + 1]++;
+    } else {
+      P.left.dst.push_back(dst[t]);
+      P.left.start.push_back((int)P.left.src.size());
+      P.left.par.push_back(par[t]);
+      for (int k = start[t]; k < start[t + 1]; k++) {
+        P.left.src.push_back(src[k]);
+        P.left.w.push_back(w[k]);
+      }
+    }
+  }
+  P.left.start.push_back((int)P.left.src.size());
+  for (size_t k = 1; k < P.start.size(); k++) P.start[k] += P.start[k - 1];
+  std::vector<int> at(P.start.begin(), P.start.end() - 1);
+  P.rec.assign(4 * (size_t)P.start.back(), 0);
+  for (size_t t = 0; t < n; t++) {
+    if (patch[t] < 0) continue;
+    int* r = &P.rec[4 * (size_t)at[patch[t]]++];
+    const int m = start[t + 1] - start[t];
+    r[0] = dst[t];
+    bool small = m == 1 ? w[start[t]] == 1.0 : m == 3;
+    for (int k = start[t]; k < start[t + 1]; k++) small = small && std::fabs(w[k]) <= 127.0;
+    if (small) {
+      r[1] = par[t] | m << 3;
+      for (int k = 0; k < m; k++) {
+        int lane = 0;
+        place(src[start[t] + k], lane);
+        r[2] |= lane << (6 * k);
+        r[3] |= ((int)w[start[t] + k] & 0xff) << (8 * k);
+      }
+    } else {
+      r[1] = par[t] | 32 | m << 8;
+      r[2] = (int)(P.terms.size() / 2);
+      for (int k = start[t]; k < start[t + 1]; k++) {
+        int lane = 0;
+        place(src[k], lane);
+        P.terms.push_back(lane);
+        P.terms.push_back((int)w[k]);
+      }
+    }
+  }
+  return P;
+}
+
 int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
   const int coord = p->coord;
   if (coord < 0 || coord > 2) return fail(BHAH_EINVAL, "coord must be 0, 1 or 2");
@@ -371,6 +439,31 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
         }
     for (HostGhosts* L : {&g->inner_full, &g->inner_stage}) L->start.push_back((int)L->src.size());
   }
+
+  // ---- stage ghosts written by the right-hand-side kernel ------------------
+  if (p->bc_kind != BHAH_BC_RADIATION) {
+    g->push = build_push(g, g->r_dst, g->r_start, g->r_par, g->r_src, g->r_w);
+    return BHAH_OK;
+  }
+  const HostGhosts& L = g->inner_stage;
+  g->push = build_push(g, L.dst, L.start, L.par, L.src, L.w);
+  // what is left copies outer points: grouped by its source for the radiation kernel
+  HostGhosts& left = g->push.left;
+  std::unordered_map<int, int> outer;
+  for (size_t t = 0; t < g->rad_q.size(); t++) outer[g->rad_q[t]] = (int)t;
+  std::vector<int>& cs = g->rad_copy_start;
+  cs.assign(g->rad_q.size() + 1, 0);
+  for (int q : left.src) cs[outer.at(q) + 1]++;
+  for (size_t k = 1; k < cs.size(); k++) cs[k] += cs[k - 1];
+  std::vector<int> at(cs.begin(), cs.end() - 1);
+  g->rad_copy.assign(2 * left.src.size(), 0);
+  for (size_t t = 0; t < left.src.size(); t++) {
+    const int k = at[outer.at(left.src[t])]++;
+    g->rad_copy[2 * k] = left.dst[t];
+    g->rad_copy[2 * k + 1] = left.par[t];
+  }
+  left = HostGhosts{};
+  left.start.push_back(0);
   return BHAH_OK;
 }
 

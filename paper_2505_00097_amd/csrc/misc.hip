@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(64) k_brill_lindquist(GridDev G, Punctures P, 
 // kernel does it.
 template <int RS>
 __device__ __forceinline__ void radiation_point(const GridDev& G, const RadDev& R, int t,
-                                                const double* __restrict__ in, const StageArgs& st, int g0) {
+                                                const double* __restrict__ in, const StageArgs& st, int g0, bool copy) {
   constexpr int W = 2 * RS + 1;  // RS: the stencil radius R.R
   const long long q = R.q[t];
   const int sh = R.shift[t];
@@ -207,25 +207,37 @@ __device__ __forceinline__ void radiation_point(const GridDev& G, const RadDev& 
 #pragma unroll
   for (int j = 0; j < GF_PER; j++) {
     const long long e = (g0 + j) * G.sgf + q;
-    if (st.rhs) st.rhs[e] = k[j];
-    else if (st.base4) st.out[e] = combine_rk4(st, k[j], st.base1[e], st.base2[e], st.base3[e], st.base4[e]);
-    else if (st.base2) st.out[e] = combine_mix(st, k[j], st.base1[e], st.base2[e]);
-    else st.out[e] = combine_plain(st, k[j], st.base1[e]);
+    if (st.rhs) {
+      st.rhs[e] = k[j];
+      continue;
+    }
+    if (st.base4) k[j] = combine_rk4(st, k[j], st.base1[e], st.base2[e], st.base3[e], st.base4[e]);
+    else if (st.base2) k[j] = combine_mix(st, k[j], st.base1[e], st.base2[e]);
+    else k[j] = combine_plain(st, k[j], st.base1[e]);
+    st.out[e] = k[j];
+  }
+  if (copy) {
+    for (int c = R.copy_start[t]; c < R.copy_start[t + 1]; c++) {
+      const int dst = R.copy[2 * c], par = R.copy[2 * c + 1];
+#pragma unroll
+      for (int j = 0; j < GF_PER; j++) st.out[(g0 + j) * G.sgf + dst] = gf_flip(g0 + j, par) ? -k[j] : k[j];
+    }
   }
 }
 
 template <int RS>
 __global__ void __launch_bounds__(256) k_radiation(GridDev G, RadDev R, const double* __restrict__ in,
-                                                   StageArgs st) {
+                                                   StageArgs st, bool copy) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < R.n) radiation_point<RS>(G, R, t, in, st, (int)blockIdx.y * GF_PER);
+  if (t < R.n) radiation_point<RS>(G, R, t, in, st, (int)blockIdx.y * GF_PER, copy);
 }
 
-void launch_radiation(const GridDev& G, const RadDev& R, const double* in, const StageArgs& st, hipStream_t s) {
+void launch_radiation(const GridDev& G, const RadDev& R, const double* in, const StageArgs& st, bool copy,
+                      hipStream_t s) {
   if (R.n == 0) return;
   const dim3 grid((R.n + 255) / 256, NGF / GF_PER);
-  if (R.R == 4) hipLaunchKernelGGL(k_radiation<4>, grid, dim3(256), 0, s, G, R, in, st);
-  else hipLaunchKernelGGL(k_radiation<2>, grid, dim3(256), 0, s, G, R, in, st);
+  if (R.R == 4) hipLaunchKernelGGL(k_radiation<4>, grid, dim3(256), 0, s, G, R, in, st, copy);
+  else hipLaunchKernelGGL(k_radiation<2>, grid, dim3(256), 0, s, G, R, in, st, copy);
 }
 
 // Ensemble form: blocks stride over the (job, chunk of 256 radiation points)
@@ -244,8 +256,8 @@ __global__ void __launch_bounds__(256) k_radiation_batch(const BatchJob* __restr
     const BatchJob* J = jobs + wk.x;
     const int t = wk.y * 256 + (int)threadIdx.x;
     if (t < J->rad.n) {
-      if (J->rad.R == 4) radiation_point<4>(J->G, J->rad, t, J->in[stage], J->st[stage], g0);
-      else radiation_point<2>(J->G, J->rad, t, J->in[stage], J->st[stage], g0);
+      if (J->rad.R == 4) radiation_point<4>(J->G, J->rad, t, J->in[stage], J->st[stage], g0, false);
+      else radiation_point<2>(J->G, J->rad, t, J->in[stage], J->st[stage], g0, false);
     }
   }
 }

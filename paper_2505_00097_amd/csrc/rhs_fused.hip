@@ -19,24 +19,26 @@ namespace bhah {
 // points); otherwise from per-lane loads, for the other tile shapes.
 template <int C, bool AX, bool KO, int H, bool STG>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(BHAH_RHS_WAVES, BHAH_RHS_WAVES)))
-k_rhs_fused(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageArgs st, double* __restrict__ aux) {
+k_rhs_fused(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageArgs st, PushDev P,
+            double* __restrict__ aux) {
   const int per = (T.ntiles + BHAH_NXCD - 1) / BHAH_NXCD;
   const int w = xcd_remap((int)blockIdx.x, per);
   if (w >= T.ntiles) return;
   __shared__ __attribute__((aligned(16))) double xs[X_SLOTS * 64];
   using SRC = std::conditional_t<STG, StagedSrc<H>, GatherSrc<H>>;
-  rhs_tile<C, AX, KO, H, SRC>(G, T, w, ga, y, st, aux, xs);
+  rhs_tile<C, AX, KO, H, SRC, STG>(G, T, w, ga, y, st, P, aux, xs);
 }
 
 // the staged form at 8th order on grids with more than two phi planes
 template <int C, bool KO>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(BHAH_RHS_WAVES, BHAH_RHS_WAVES)))
-k_rhs_planes8(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageArgs st, double* __restrict__ aux) {
+k_rhs_planes8(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageArgs st,
+              double* __restrict__ aux) {
   const int per = (T.ntiles + BHAH_NXCD - 1) / BHAH_NXCD;
   const int w = xcd_remap((int)blockIdx.x, per);
   if (w >= T.ntiles) return;
   __shared__ __attribute__((aligned(16))) double xs[X_SLOTS * 64];
-  rhs_tile<C, false, KO, 5, StagedSrc<5>>(G, T, w, ga, y, st, aux, xs);
+  rhs_tile<C, false, KO, 5, StagedSrc<5>, false>(G, T, w, ga, y, st, PushDev{}, aux, xs);
 }
 
 // Persistent form for ensembles: a fixed grid of blocks (a multiple of the
@@ -60,22 +62,22 @@ k_rhs_batch(const BatchJob* __restrict__ jobs, const BatchHdr* __restrict__ hdr,
     const BatchJob* J = jobs + wk.x;
     const GridDev G = J->G;
     const StageArgs st = J->st[stage];
-    rhs_tile<C, AX, KO, H, StagedSrc<H>>(G, J->T, wk.y, ga, J->in[stage], st, nullptr, xs);
+    rhs_tile<C, AX, KO, H, StagedSrc<H>, false>(G, J->T, wk.y, ga, J->in[stage], st, PushDev{}, nullptr, xs);
     __syncthreads();  // the next tile's stencil stage reuses slots that the other wave reads to the end
   }
 }
 
 using FusedLaunch = void (*)(dim3, hipStream_t, const GridDev&, const TileMap&, const Gauge&, const double*,
-                             const StageArgs&, double*);
+                             const StageArgs&, const PushDev&, double*);
 using BatchLaunch = void (*)(dim3, hipStream_t, const BatchJob*, const BatchHdr*, const int2*, int, const int*, int,
                              const Gauge&);
 template <int C, bool AX, bool KO, int H, bool STG>
 void launch_fused_t(dim3 g, hipStream_t s, const GridDev& G, const TileMap& T, const Gauge& ga, const double* y,
-                    const StageArgs& st, double* aux) {
+                    const StageArgs& st, const PushDev& P, double* aux) {
   if constexpr (STG && !AX && H == 5)
     hipLaunchKernelGGL((k_rhs_planes8<C, KO>), g, dim3(128), 0, s, G, T, ga, y, st, aux);
   else
-    hipLaunchKernelGGL((k_rhs_fused<C, AX, KO, H, STG>), g, dim3(128), 0, s, G, T, ga, y, st, aux);
+    hipLaunchKernelGGL((k_rhs_fused<C, AX, KO, H, STG>), g, dim3(128), 0, s, G, T, ga, y, st, P, aux);
 }
 template <int C, bool AX, bool KO, int H>
 void launch_batch_t(dim3 g, hipStream_t s, const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,
@@ -149,13 +151,12 @@ TileMap make_staged_tilemap(const GridDev& G, int band) {
 }
 
 void launch_rhs_fused(const GridDev& G, const Gauge& ga, const double* y, double* aux, const StageArgs& st,
-                      hipStream_t s, const TileCfg& cfg_in) {
-  const TileCfg cfg = tile_fits_periodic(G.coord, cfg_in) ? cfg_in : TileCfg{6, 0, cfg_in.band, cfg_in.waves};
-  const bool staged = cfg.lx == 6;
+                      hipStream_t s, const TileCfg& cfg, const PushDev& push) {
+  const bool staged = rhs_staged(G.coord, cfg);
   const TileMap T = staged ? make_staged_tilemap(G, cfg.band) : make_tilemap(G, cfg.lx, cfg.ly, cfg.band);
   const int per = (T.ntiles + BHAH_NXCD - 1) / BHAH_NXCD;
   const RhsKernels& k = kernels_of(rhs_variant(G.coord, G.N1, G.N2, G.ng));
-  (staged ? k.staged : k.gather)[ga.ko() ? 1 : 0](dim3(per * BHAH_NXCD), s, G, T, ga, y, st, aux);
+  (staged ? k.staged : k.gather)[ga.ko() ? 1 : 0](dim3(per * BHAH_NXCD), s, G, T, ga, y, st, push, aux);
 }
 
 void launch_rhs_batch(int variant, const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,

@@ -69,9 +69,10 @@ struct Stage : StageSize<AX, H> {
 typedef double bhah_d2 __attribute__((ext_vector_type(2), aligned(8)));
 
 // V: double (per lane, twelve results) or bhah_d2 (row pairs, six); e(i) is
-// the element of result i, res(i) its value
+// the element of result i, res(i) its place in the park. With keep the stored
+// values replace the results there.
 template <class V, int N, class E, class RES>
-__device__ __forceinline__ void store_stage(const StageArgs& st, const E& e, const RES& res) {
+__device__ __forceinline__ void store_stage(const StageArgs& st, bool keep, const E& e, const RES& res) {
   auto each = [](const V& k, auto f) {
     if constexpr (std::is_same_v<V, double>) return f(k, 0);
     else return V{f(k.x, 0), f(k.y, 1)};
@@ -84,12 +85,13 @@ __device__ __forceinline__ void store_stage(const StageArgs& st, const E& e, con
 #pragma unroll
     for (int i = 0; i < N; i++) x[i] = *(const V*)(b + e(i));
   };
+  auto k = [&](int i) -> V& { return *(V*)res(i); };
   if (st.rhs) {
 #pragma unroll
-    for (int i = 0; i < N; i++) *(V*)(st.rhs + e(i)) = res(i);
+    for (int i = 0; i < N; i++) *(V*)(st.rhs + e(i)) = k(i);
     return;
   }
-  V b1[N];
+  V b1[N], o[N];
   ld(st.base1, b1);
   if (st.base4) {
     V b2[N], b3[N], b4[N];
@@ -99,49 +101,102 @@ __device__ __forceinline__ void store_stage(const StageArgs& st, const E& e, con
     BHAH_PHASE_BARRIER();
 #pragma unroll
     for (int i = 0; i < N; i++)
-      *(V*)(st.out + e(i)) = each(res(i), [&](double k, int h) {
-        return combine_rk4(st, k, el(b1[i], h), el(b2[i], h), el(b3[i], h), el(b4[i], h));
+      o[i] = each(k(i), [&](double x, int h) {
+        return combine_rk4(st, x, el(b1[i], h), el(b2[i], h), el(b3[i], h), el(b4[i], h));
       });
-    return;
-  }
-  if (st.base2) {
+  } else if (st.base2) {
     V b2[N];
     ld(st.base2, b2);
     BHAH_PHASE_BARRIER();
 #pragma unroll
     for (int i = 0; i < N; i++)
-      *(V*)(st.out + e(i)) =
-          each(res(i), [&](double k, int h) { return combine_mix(st, k, el(b1[i], h), el(b2[i], h)); });
-    return;
-  }
-  BHAH_PHASE_BARRIER();
+      o[i] = each(k(i), [&](double x, int h) { return combine_mix(st, x, el(b1[i], h), el(b2[i], h)); });
+  } else {
+    BHAH_PHASE_BARRIER();
 #pragma unroll
-  for (int i = 0; i < N; i++)
-    *(V*)(st.out + e(i)) = each(res(i), [&](double k, int h) { return combine_plain(st, k, el(b1[i], h)); });
+    for (int i = 0; i < N; i++) o[i] = each(k(i), [&](double x, int h) { return combine_plain(st, x, el(b1[i], h)); });
+  }
+#pragma unroll
+  for (int i = 0; i < N; i++) *(V*)(st.out + e(i)) = o[i];
+  if (keep) {
+#pragma unroll
+    for (int i = 0; i < N; i++) k(i) = o[i];
+  }
 }
 
-__device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs& st, unsigned q, bool live,
-                                               const int (&list)[12], const double* __restrict__ park, int lane) {
+// Ghosts g0 .. g1 - 1 of the pushed list from the tile's stored values
+// (val[i * 64 + lane] of gridfunction list[i]): the sum of weights times
+// values in the order of the ghost lists, then the parity sign, as the ghost
+// kernel forms them. A separate kernel for the few thousand ghosts of a stage
+// takes 4.5 to 5 us, most of it launch and three dependent rounds of loads.
+// (Fetching a tile's range and first records before the last phase, to hide
+// their latency, costs 200 to 400 bytes of spills and 20% of the step.)
+__device__ __forceinline__ void push_ghosts(const GridDev& G, const PushDev& P, int g0, int g1, double* out,
+                                            const int (&list)[12], const double* val, int lane) {
+  for (int t = g0 + lane; t < g1; t += 64) {
+    const int4 r = ((const int4*)P.rec)[t];
+    const int par = r.y & 7;
+    double x[12];
+    if (r.y & 32) {
+      const int n = r.y >> 8;
+#pragma unroll
+      for (int i = 0; i < 12; i++) x[i] = 0.0;
+      for (int k = 0; k < n; k++) {
+        const int2 lw = ((const int2*)P.terms)[r.z + k];
+#pragma unroll
+        for (int i = 0; i < 12; i++) x[i] = fma((double)lw.y, val[i * 64 + lw.x], x[i]);
+      }
+    } else if ((r.y >> 3) == 1) {
+#pragma unroll
+      for (int i = 0; i < 12; i++) x[i] = val[i * 64 + (r.z & 63)];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 12; i++) x[i] = 0.0;
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        const double w = (double)(signed char)(r.w >> (8 * k));
+        const double* v = val + ((r.z >> (6 * k)) & 63);
+#pragma unroll
+        for (int i = 0; i < 12; i++) x[i] = fma(w, v[i * 64], x[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 12; i++) out[list[i] * G.sgf + r.x] = gf_flip(list[i], par) ? -x[i] : x[i];
+  }
+}
+
+template <int C, int H, bool PUSH>
+__device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs& st, const PushDev& P,
+                                               const TilePoint& p, const int (&list)[12], double* __restrict__ park,
+                                               int lane) {
+  const unsigned q = p.q;
+  const bool live = p.live;
+  int g0 = 0, g1 = 0;  // the tile's pushed ghosts
+  if (PUSH && P.start) {
+    const int n = patch_number<C, H>(P, p.t0, p.t1, p.t2);
+    g0 = P.start[n];
+    g1 = P.start[n + 1];
+  }
+  const bool push = g0 < g1;
   const int p2 = 2 * (lane & 31), gs = lane >> 5;
   const unsigned qa = (unsigned)__shfl((int)q, p2), qb = (unsigned)__shfl((int)q, p2 + 1);
   if (__all(live && qb == qa + 1u)) {
-    const double* pk = park - lane + p2 + gs * 64;  // result 2 i + gs of point p2 at pk[128 i]
+    double* pk = park - lane + p2 + gs * 64;  // result 2 i + gs of point p2 at pk[128 i]
     long long e[6];
 #pragma unroll
     for (int i = 0; i < 6; i++) e[i] = (gs ? list[2 * i + 1] : list[2 * i]) * G.sgf + (long long)qa;
-    store_stage<bhah_d2, 6>(st, [&](int i) { return e[i]; },
-                            [&](int i) { return bhah_d2{pk[128 * i], pk[128 * i + 1]}; });
-    return;
+    store_stage<bhah_d2, 6>(st, push, [&](int i) { return e[i]; }, [&](int i) { return pk + 128 * i; });
+  } else if (live) {
+    store_stage<double, 12>(st, push, [&](int i) { return list[i] * G.sgf + q; }, [&](int i) { return park + i * 64; });
   }
-  if (!live) return;
-  store_stage<double, 12>(st, [&](int i) { return list[i] * G.sgf + q; }, [&](int i) { return park[i * 64]; });
+  if (push) push_ghosts(G, P, g0, g1, st.out, list, park - lane, lane);
 }
 
 // ---- metric wave ---------------------------------------------------------------
-template <int C, bool AX, bool KO, int H, class SRC>
+template <int C, bool AX, bool KO, int H, class SRC, bool PUSH>
 __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
-                                            const StageArgs& st, const TilePoint& p, double* __restrict__ aux,
-                                            double* __restrict__ xs0, int lane) {
+                                            const StageArgs& st, const PushDev& P, const TilePoint& p,
+                                            double* __restrict__ aux, double* __restrict__ xs0, int lane) {
   constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2;
   double* xs = xs0 + lane;
   auto put = [&](int v, double x) { xs[v * 64] = x; };
@@ -358,14 +413,14 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
     put(R_METRIC + 6 + c, rh[c]);
   }
   constexpr int out[12] = {0, 1, 2, 3, 4, 5, G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
-  stage_epilogue(G, st, p.q, p.live, out, xs + R_METRIC * 64, lane);
+  stage_epilogue<C, H, PUSH>(G, st, P, p, out, xs + R_METRIC * 64, lane);
 }
 
 // ---- gauge wave ------------------------------------------------------------------
-template <int C, bool AX, bool KO, int H, class SRC>
+template <int C, bool AX, bool KO, int H, class SRC, bool PUSH>
 __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
-                                           const StageArgs& st, const TilePoint& p, double* __restrict__ xs0,
-                                           int lane) {
+                                           const StageArgs& st, const PushDev& P, const TilePoint& p,
+                                           double* __restrict__ xs0, int lane) {
   constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2;
   double* xs = xs0 + lane;
   auto put = [&](int v, double x) { xs[v * 64] = x; };
@@ -614,21 +669,22 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
   }
   constexpr int out[12] = {G_ALPHA, G_BETU0, G_BETU0 + 1, G_BETU0 + 2, G_CF, G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2, G_TRK,
                            G_VETU0, G_VETU0 + 1, G_VETU0 + 2};
-  stage_epilogue(G, st, p.q, p.live, out, xs + R_GAUGE * 64, lane);
+  stage_epilogue<C, H, PUSH>(G, st, P, p, out, xs + R_GAUGE * 64, lane);
 }
 
 // One tile by the block's two waves. Every lane takes part (lanes past the
-// grid compute a point on it and store nothing).
-template <int C, bool AX, bool KO, int H, class SRC>
+// grid compute a point on it and store nothing). PUSH: with the tile's pushed
+// ghosts.
+template <int C, bool AX, bool KO, int H, class SRC, bool PUSH>
 __device__ __forceinline__ void rhs_tile(const GridDev& G, const TileMap& T, int w, const Gauge& ga,
-                                         const double* __restrict__ y, const StageArgs& st, double* __restrict__ aux,
-                                         double* __restrict__ xs) {
+                                         const double* __restrict__ y, const StageArgs& st, const PushDev& P,
+                                         double* __restrict__ aux, double* __restrict__ xs) {
   const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   TilePoint p;
   p.live = tile_point<H>(G, T, w, lane, p.t0, p.t1, p.t2, p.i0, p.i1, p.i2);
   p.q = (unsigned)(p.i0 + G.s1 * p.i1 + G.s2 * p.i2);
-  if (wave == 0) metric_wave<C, AX, KO, H, SRC>(G, ga, y, st, p, aux, xs, lane);
-  else gauge_wave<C, AX, KO, H, SRC>(G, ga, y, st, p, xs, lane);
+  if (wave == 0) metric_wave<C, AX, KO, H, SRC, PUSH>(G, ga, y, st, P, p, aux, xs, lane);
+  else gauge_wave<C, AX, KO, H, SRC, PUSH>(G, ga, y, st, P, p, xs, lane);
 }
 
 }  // namespace bhah

@@ -131,7 +131,7 @@ __device__ __forceinline__ double d1_sum(const double (&v)[2 * R + 1]) {
 // counts is the number of instructions: a 16 x 4 patch with its halo at 4th
 // order is 22 x 10 values, two loads, where a row of 64 points would be 7 x
 // 70, four, and per-lane gathers 30 to 70.
-constexpr int TLX = 4, TEX = 1 << TLX, TEE = 64 >> TLX;
+constexpr int TLX = PATCH_LX, TEX = PATCH_X, TEE = PATCH_E;
 // row length and 16-byte pieces of the main patch (halo H) and of one pair of
 // phi planes (halo R each)
 template <int H>
@@ -611,6 +611,14 @@ __device__ __forceinline__ void run_stencils(const GatherSrc<H>& S, const int (&
     fn(t, s, dd);
     BHAH_PHASE_BARRIER();
   });
+}
+
+// the number of a staged tile as the pushed ghosts are grouped (PushDev)
+template <int C, int H>
+__device__ __forceinline__ int patch_number(const PushDev& P, int t0, int t1, int t2) {
+  const int x = (t0 - H) >> TLX;
+  if constexpr (C == BHAH_SINH_CYLINDRICAL) return ((t1 - H) * P.ne + (t2 - H) / TEE) * P.nx + x;
+  else return ((t2 - H) * P.ne + (t1 - H) / TEE) * P.nx + x;
 }
 
 // the point of a lane and the tile it belongs to
