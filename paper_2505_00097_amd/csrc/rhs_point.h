@@ -262,6 +262,16 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
 #pragma unroll
   for (int i = 0; i < 3; i++) v[i] = at(G_VETU0 + i);
   const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
+  // for the last phase: fetched there, they would wait behind the loads and
+  // stores of the other waves' epilogues (that phase took 6900 cycles, 14600
+  // in a Runge-Kutta stage, of 30000 and 47000; the gauge wave's, no shorter,
+  // 1700)
+  double a6[6], lam[3];
+#pragma unroll
+  for (int c = 0; c < 6; c++) a6[c] = at(G_ADD00 + c);
+#pragma unroll
+  for (int i = 0; i < 3; i++) lam[i] = at(G_LAMU0 + i);
+  const double alpha = at(G_ALPHA), W = at(G_CF), K = at(G_TRK);
   BHAH_PHASE_BARRIER();
   // psi = 1/2 ln det(gammabar/gammahat): psi_m = 1/2 gammabar^ab h_ab,m and
   // v^m psi_km = 1/2 (v^m gammabar^ab h_ab,km - (gammabar^-1 v^m h_m gammabar^-1)^ab h_ab,k)
@@ -318,17 +328,11 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
   }
   BHAH_PHASE_BARRIER();
   add_ricci_delta(gU, D, DU, [&](int k, int c) { return get(X_DEL + 6 * k + c); }, Rc);
-  double a6[6];
-#pragma unroll
-  for (int c = 0; c < 6; c++) a6[c] = at(G_ADD00 + c);
-  const double alpha = at(G_ALPHA), W = at(G_CF), K = at(G_TRK);
   __syncthreads();
 
   // ---- Lambdabar part of the Ricci tensor, Eq. 8's X_ij -------------------
   {
-    double lam[3], lk[3][3], Dl[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; i++) lam[i] = at(G_LAMU0 + i);
+    double lk[3][3], Dl[3][3];
 #pragma unroll
     for (int k = 0; k < 3; k++)
 #pragma unroll
