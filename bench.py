@@ -33,12 +33,12 @@ PEAK_HBM = 8.0e12           # bytes/s
 # paper_2505_00097_amd/count_flops.py prints it (a CPU test keeps the two in
 # step). On grids with two phi planes the kernel variant drops the phi
 # derivatives that vanish identically there, and its own count applies.
-F_ALG = {(0, False): 5187, (0, True): 3923, (1, False): 4968, (1, True): 3684, (2, False): 5168,
-         (2, True): 3904}
+F_ALG = {(0, False): 4663, (0, True): 3575, (1, False): 4444, (1, True): 3336, (2, False): 4644,
+         (2, True): 3556}
 # the same for the 8th-order kernels (five ghost layers), with Kreiss-Oliger
 # dissipation as the production head-on numerics run them
-F_ALG8_KO = {(0, False): 9453, (0, True): 5924, (1, False): 9234, (1, True): 5685, (2, False): 9434,
-             (2, True): 5905}
+F_ALG8_KO = {(0, False): 6938, (0, True): 4861, (1, False): 6719, (1, True): 4622, (2, False): 6919,
+             (2, True): 4842}
 
 
 def two_planes(coord, N):
@@ -60,7 +60,8 @@ COUNTERS = os.path.join(ROOT, "profiles", "k_rhs_fused_headon_counters.txt")
 COUNTERS_3D = os.path.join(ROOT, "profiles", "k_rhs_fused_vacuum3d_counters.txt")
 COUNTERS_8 = os.path.join(ROOT, "profiles", "k_rhs_fused_headon_8th_order_counters.txt")
 COUNTERS_3D_8 = os.path.join(ROOT, "profiles", "k_rhs_fused_vacuum3d_8th_order_counters.txt")
-KERNEL_SOURCES = ["paper_2505_00097_amd/csrc/rhs_fused.hip", "paper_2505_00097_amd/csrc/rhs_stencil.h",
+KERNEL_SOURCES = ["paper_2505_00097_amd/csrc/rhs_fused.hip", "paper_2505_00097_amd/csrc/rhs_point.h",
+                  "paper_2505_00097_amd/csrc/rhs_stencil.h", "paper_2505_00097_amd/csrc/rhs_frame.h",
                   "paper_2505_00097_amd/csrc/rhs_common.h", "paper_2505_00097_amd/csrc/bhah_internal.h"]
 
 
@@ -138,17 +139,13 @@ def roofline(kernel, flops_per_point, points, launch_s, traffic, probe=None):
     return out
 
 
-def kernel_name(coord, N, ko=False, nghosts=3, tile=None):
-    """The right-hand-side kernel the library launches for this grid and
-    tile: with the default tile (lx = 6) the one that brings its stencils
-    through LDS patches (last template argument; k_rhs_planes8 at 8th order
-    with more than two phi planes)."""
-    ax = two_planes(coord, N)
+def kernel_name(coord, N, ko=False, nghosts=3):
+    """The right-hand-side kernel of a bare evaluation on this grid (the stages
+    of a step that are followed by another run its form with stage ghosts,
+    last template argument true, except at 8th order with more than two phi
+    planes)."""
     b = lambda v: "true" if v else "false"
-    staged = tile is not None and tile[0] == 6
-    if staged and nghosts == 5 and not ax:
-        return "k_rhs_planes8<%d,%s>" % (coord, b(ko))
-    return "k_rhs_fused<%d,%s,%s,%d,%s>" % (coord, b(ax), b(ko), nghosts, b(staged))
+    return "k_rhs_fused<%d,%s,%s,%d,false>" % (coord, b(two_planes(coord, N)), b(ko), nghosts)
 
 
 def percentile(v, p):
@@ -275,7 +272,7 @@ def run_ssprk3(capi, wl, stream, steps, diss=(0.0, 0.0), bc_kind=0, nghosts=3, r
             out["rhs_frac_fp64_peak"] = f * n / rhs_s / PEAK_FP64_VECTOR
             if nghosts == 5:
                 tile = list(capi.grid_get_tile(ge.h))
-                out["roofline"] = roofline(kernel_name(w["coord"], w["N"], ko=True, nghosts=5, tile=tile), f, n, rhs_s,
+                out["roofline"] = roofline(kernel_name(w["coord"], w["N"], ko=True, nghosts=5), f, n, rhs_s,
                                            measured_traffic("headon_sinhcylindrical_128x2x256", tile, nghosts=5))
         del ye
     return out
@@ -461,7 +458,7 @@ def run_rhs_study(capi, wl, stream, reps, steps):
     name = "vacuum3d_sinhspherical_256x128x64"
     eighth = {"rhs_launch_s": rhs8_s, "flops_per_point": f8, "rhs_TFLOPs": f8 * n / rhs8_s / 1e12,
               "rhs_frac_fp64_peak": f8 * n / rhs8_s / PEAK_FP64_VECTOR, "tile": tile8,
-              "roofline": roofline(kernel_name(w["coord"], w["N"], ko=True, nghosts=5, tile=tile8), f8, n, rhs8_s,
+              "roofline": roofline(kernel_name(w["coord"], w["N"], ko=True, nghosts=5), f8, n, rhs8_s,
                                    measured_traffic(name, tile8, nghosts=5))}
     del y8
     return {"workload": name, "interior_points": n,
@@ -470,7 +467,7 @@ def run_rhs_study(capi, wl, stream, reps, steps):
             "rhs_alg_GBps": BYTES_ALG * n / rhs_s / 1e9,
             "rk4_step_ms": step_s * 1e3, "value": n / step_s, "unit": UNIT,
             "tile": tile, "rhs_8th_order_with_dissipation": eighth,
-            "roofline": roofline(kernel_name(w["coord"], w["N"], tile=tile), f_alg(w["coord"], w["N"]), n, rhs_s,
+            "roofline": roofline(kernel_name(w["coord"], w["N"]), f_alg(w["coord"], w["N"]), n, rhs_s,
                                  measured_traffic(name, tile))}
 
 
@@ -713,7 +710,7 @@ def main():
                            "event pair per step",
                     "timed_chunks_ms_per_step": chunk_ms},
         "finite": finite,
-        "roofline": roofline(kernel_name(w["coord"], w["N"], tile=capi.grid_get_tile(g.h)),
+        "roofline": roofline(kernel_name(w["coord"], w["N"]),
                              f_alg(w["coord"], w["N"]), n_int, rhs_s,
                              traffic,
                              probe),

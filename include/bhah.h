@@ -291,17 +291,16 @@ int bhah_rk4_step_noalloc(const bhah_grid* g, const bhah_gauge_params* gp, doubl
 int bhah_constraints(const bhah_grid* g, const double* y, double* H, double* M,
                      double* C, void* stream);
 
-/* Tile shape of this grid's right-hand-side kernel (bhah_bssn_rhs,
- * bhah_rk4_step, bhah_ssprk3_step, bhah_evolve): 64 points, 2^lx along i0,
- * 2^ly along i1, 64 >> (lx + ly) along i2, walked in bands of `band` tile
- * rows of i1. The extent along phi (i1 on SinhCylindrical grids, i2
- * otherwise) must be 1. Default (6, 0, 4). The shape changes speed only: the
- * results are bitwise equal across shapes. With lx = 6 the kernel brings its
- * stencils through LDS and is free to take the 64 points as a compact patch
- * (16 along i0 by 4 along the other non-phi direction; band then counts rows
- * of such patches): the fastest form. With any other lx each point reads its
- * own stencil with tiles of exactly that shape. Setting a shape keeps the
- * number of waves per tile (below).                                         */
+/* Tile walk of this grid's right-hand-side kernel (bhah_bssn_rhs,
+ * bhah_rk4_step, bhah_ssprk3_step, bhah_evolve). The kernel takes its points
+ * as patches of 16 along i0 by 4 along the other non-phi direction (phi: i1 on
+ * SinhCylindrical grids, i2 otherwise), walked in bands of `band` rows of
+ * patches (phi planes on SinhCylindrical grids). lx and ly name a shape of 64
+ * points, 2^lx along i0, 2^ly along i1, 64 >> (lx + ly) along i2, with extent
+ * 1 along phi; they are checked, kept and reported, and neither results nor
+ * speed depend on them. Default (6, 0, 4). band changes speed only: the
+ * results are bitwise equal. Setting a shape keeps the number of waves per
+ * tile (below).                                                             */
 int bhah_grid_set_tile(bhah_grid* g, int lx, int ly, int band);
 int bhah_grid_get_tile(const bhah_grid* g, int* lx, int* ly, int* band);
 
@@ -314,10 +313,10 @@ int bhah_grid_get_tile(const bhah_grid* g, int* lx, int* ly, int* band);
 int bhah_grid_set_waves_per_tile(bhah_grid* g, int waves);
 int bhah_grid_get_waves_per_tile(const bhah_grid* g, int* waves);
 
-/* Time every allowed tile shape for this grid on state y (valid ghosts),
- * writing right-hand sides into rhs (state layout, caller-owned scratch),
- * after a few warm-up launches, in two passes; keep the first candidate
- * within 2% of the fastest, larger extents along i0 first. The number of
+/* Time the right-hand side with bands of 16, 4 and 1 on state y (valid
+ * ghosts), writing right-hand sides into rhs (state layout, caller-owned
+ * scratch), after a few warm-up launches, in two passes; keep the first within
+ * 2% of the fastest, wider bands first; the shape becomes (6, 0). The number of
  * waves per tile becomes 1. Synchronises stream.                            */
 int bhah_grid_tune(bhah_grid* g, const bhah_gauge_params* gp, const double* y,
                    double* rhs, void* stream);
@@ -413,9 +412,8 @@ int bhah_batch_set_launch_tuning(bhah_batch* b, int on);
 
 /* Tile choice for job j's size class: log2 extents along i0 and i1 (the
  * extent along i2 is 64 >> (lx + ly)) and band (tile rows of i1 walked
- * together). Defaults (6, 0, 4) before the class is tuned. The ensemble
- * kernels bring every stencil through LDS on 16 x 4 patches (as the solo
- * kernel with lx = 6), so of a choice only the band matters.                */
+ * together). Defaults (6, 0, 4) before the class is tuned. The kernels work
+ * on 16 x 4 patches, so of a choice only the band matters.                  */
 int bhah_batch_get_tile(const bhah_batch* b, int j, int* lx, int* ly, int* band);
 
 void bhah_batch_destroy(bhah_batch* b);

@@ -172,17 +172,16 @@ inline Gauge gauge_of(const bhah_gauge_params& p) { return Gauge{p.eta, p.diss_g
 // BHAH_OK, or BHAH_EINVAL with a message naming the caller
 int check_gauge(const bhah_gauge_params* gp, const char* who);
 
-// Tile shape and walk of the right-hand-side kernel over one grid: tiles of
-// 64 points, 2^lx along i0, 2^ly along i1 and 64 >> (lx + ly) along i2,
-// walked in bands of `band` tile rows of i1.
+// Walk of the right-hand-side kernel's tiles over one grid: bands of `band`
+// rows of patches of i1. lx and ly are the shape as set (checked, kept and
+// reported; no kernel depends on it).
 struct TileCfg {
   int lx, ly, band;
   int waves = 1;  // as set by bhah_grid_set_waves_per_tile (1 or 2); no kernel depends on it
 };
 
-// The stencil code reads the periodic direction (phi: i1 on SinhCylindrical
-// grids, i2 otherwise) with a wave-uniform wrapped index, so a tile must
-// have extent 1 along it.
+// Shapes have extent 1 along phi (i1 on SinhCylindrical grids, i2 otherwise):
+// a wave's wrapped phi planes are uniform.
 inline bool tile_fits_periodic(int coord, const TileCfg& c) {
   return coord == BHAH_SINH_CYLINDRICAL ? c.ly == 0 : c.lx + c.ly == 6;
 }
@@ -324,23 +323,20 @@ int launch_brill_lindquist(const GridDev& G, int n, const double* m, const doubl
                            double* y, hipStream_t s);
 // push: ghosts of st.out to write beside the interior (where rhs_pushes)
 void launch_rhs_fused(const GridDev& G, const Gauge& ga, const double* y, double* aux, const StageArgs& st,
-                      hipStream_t s, const TileCfg& cfg, const PushDev& push = PushDev{});
-// whether a tile choice runs the staged kernel
-inline bool rhs_staged(int coord, const TileCfg& c) { return c.lx == 6 || !tile_fits_periodic(coord, c); }
-// Whether the solo kernel writes the stage ghosts itself: the staged forms
-// but the 8th-order general one, which has no registers for it (3-D
+                      hipStream_t s, int band, const PushDev& push = PushDev{});
+// Whether the solo kernel writes the stage ghosts itself: every form but
+// the 8th-order general one, which has no registers for it (3-D
 // production step 5.06 -> 5.23 ms). The ensemble kernels do not either: with
 // tiles enough to fill the card the ghost kernel costs 33 us of a 370 us stage
 // for 16 jobs, and border tiles that write their ghosts make the step 1% longer.
-inline bool rhs_pushes(const GridDev& G, const TileCfg& c) {
+inline bool rhs_pushes(const GridDev& G) {
   const bool two = (G.coord == BHAH_SINH_CYLINDRICAL ? G.N1 : G.N2) == 2;
-  return rhs_staged(G.coord, c) && (two || G.ng == NG);
+  return two || G.ng == NG;
 }
-TileMap make_tilemap(const GridDev& G, int lx, int ly, int band);
 // the tile map of the kernels that bring their stencils through LDS patches
 // (rhs_stencil.h): 16 points along i0 by 4 along the other non-periodic
 // direction
-TileMap make_staged_tilemap(const GridDev& G, int band);
+TileMap make_tilemap(const GridDev& G, int band);
 // counts (device, one int per job; NULL: every job) and kk: step kk of a
 // graph launch runs only the jobs with kk < counts[job].
 void launch_rhs_batch(int variant, const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,

@@ -163,8 +163,8 @@ static hipError_t upload_radiation(bhah_grid* g) {
 static int run_stage(const bhah_grid* g, const Gauge& ga, const double* in, const StageArgs& st, double* gdst,
                      bool last, hipStream_t s) {
   const bool rad = g->params.bc_kind == BHAH_BC_RADIATION;
-  const bool push = !last && rhs_pushes(g->dev, g->tile);
-  launch_rhs_fused(g->dev, ga, in, nullptr, st, s, g->tile, push ? g->push_dev : PushDev{});
+  const bool push = !last && rhs_pushes(g->dev);
+  launch_rhs_fused(g->dev, ga, in, nullptr, st, s, g->tile.band, push ? g->push_dev : PushDev{});
   if (rad) launch_radiation(g->dev, g->rad, in, st, push, s);
   if (push) launch_ghosts(g->ghost_left, gdst, g->dev.sgf, s);
   else if (rad) launch_ghosts(last ? g->ghost_inner : g->ghost_inner_stage, gdst, g->dev.sgf, s);
@@ -283,7 +283,7 @@ int bhah_bssn_rhs(const bhah_grid* g, const bhah_gauge_params* gp, const double*
   if (int rc = check_aligned("bhah_bssn_rhs", {y, rhs, aux})) return rc;
   if (int rc = check_gauge(gp, "bhah_bssn_rhs")) return rc;
   StageArgs st{rhs, nullptr, nullptr, 0.0, nullptr, 0.0, 0.0, nullptr, nullptr};
-  launch_rhs_fused(g->dev, gauge_of(*gp), y, aux, st, (hipStream_t)stream, g->tile);
+  launch_rhs_fused(g->dev, gauge_of(*gp), y, aux, st, (hipStream_t)stream, g->tile.band);
   if (g->params.bc_kind == BHAH_BC_RADIATION) launch_radiation(g->dev, g->rad, y, st, false, (hipStream_t)stream);
   return check_launch("bhah_bssn_rhs");
 }
@@ -408,13 +408,13 @@ int bhah_grid_tune(bhah_grid* g, const bhah_gauge_params* gp, const double* y, d
   const std::vector<TileCfg> cand = tile_candidates(cls);
   // a few launches first (clocks and caches settle), then every candidate
   // timed in two passes; each keeps its better pass
-  for (int r = 0; r < 8; r++) launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, g->tile);
+  for (int r = 0; r < 8; r++) launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, g->tile.band);
   std::vector<float> t(cand.size(), 1e30f);
   for (int pass = 0; pass < 2 && !rc; pass++)
     for (size_t i = 0; i < cand.size(); i++) {
-      launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, cand[i]);
+      launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, cand[i].band);
       (void)hipEventRecord(e0, s);
-      for (int r = 0; r < 3; r++) launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, cand[i]);
+      for (int r = 0; r < 3; r++) launch_rhs_fused(g->dev, gauge_of(*gp), y, nullptr, st, s, cand[i].band);
       (void)hipEventRecord(e1, s);
       if ((rc = check_hip(hipEventSynchronize(e1), "bhah_grid_tune"))) break;
       float ms = 0.f;

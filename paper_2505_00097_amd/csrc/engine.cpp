@@ -42,25 +42,14 @@ double now_s() {
 
 // candidate tile configurations for one size class
 std::vector<TileCfg> tile_candidates(const SizeClass& c) {
-  const int N0 = std::get<1>(c), N1 = std::get<2>(c), N2 = std::get<3>(c);
+  const int N1 = std::get<2>(c), ty = std::get<0>(c) == BHAH_SINH_CYLINDRICAL ? N1 : (N1 + PATCH_E - 1) / PATCH_E;
   std::vector<TileCfg> out;
-  for (int lx = 6; lx >= 3; lx--)
-    for (int ly = 0; ly <= 3 && lx + ly <= 6; ly++) {
-      if (!tile_fits_periodic(std::get<0>(c), TileCfg{lx, ly, 1})) continue;
-      if (ly > 0 && (1 << ly) > N1) continue;
-      const int ez = 64 >> (lx + ly);
-      if (ez > 1 && ez > N2) continue;
-      if (lx < 6 && (1 << lx) > 2 * N0) continue;
-      const int ty = (N1 + (1 << ly) - 1) >> ly;
-      // bands of 4 and 16 tile rows: tiles that run at the same time share
-      // stencil planes in the XCD's L2 (16 pays on large 3-D grids). Wider
-      // bands first: near-ties go to the walk with the better L2 reuse (on
-      // the head-on grid band 1 moves 1.4x the HBM bytes of band 4 at the
-      // same speed within noise)
-      if (ty > 8) out.push_back(TileCfg{lx, ly, 16});
-      if (ty > 1) out.push_back(TileCfg{lx, ly, 4});
-      out.push_back(TileCfg{lx, ly, 1});
-    }
+  // bands of 4 and 16 tile rows: tiles that run at the same time share
+  // stencil planes in the XCD's L2. Wider bands first: near-ties go to the
+  // walk with the better L2 reuse
+  if (ty > 8) out.push_back(TileCfg{6, 0, 16});
+  if (ty > 1) out.push_back(TileCfg{6, 0, 4});
+  out.push_back(TileCfg{6, 0, 1});
   return out;
 }
 
@@ -149,7 +138,7 @@ void Engine::build_blob(const std::vector<TileCfg>& cfg, const std::vector<int>&
   std::vector<TileMap> maps(jobs_.size());
   int nt = 0, nc = 0;
   for (int j = 0; j < (int)jobs_.size(); j++)
-    maps[j] = make_staged_tilemap(jobs_[j].g->dev, cfg[j].band);
+    maps[j] = make_tilemap(jobs_[j].g->dev, cfg[j].band);
   for (int j : sel) {
     nt += maps[j].ntiles * repeat;
     const JobLists l = lists_of(j);
@@ -273,7 +262,7 @@ int Engine::time_class(const SizeClass& c, const TileCfg& cfg, hipStream_t s, do
     if (class_of(jobs_[j].g) == c) {
       only.push_back(j);
       cfgs[j] = cfg;
-      tiles += make_staged_tilemap(jobs_[j].g->dev, cfg.band).ntiles;
+      tiles += make_tilemap(jobs_[j].g->dev, cfg.band).ntiles;
     }
   // time the class at full occupancy: repeat its tiles until every
   // persistent block slot sees several
@@ -324,7 +313,6 @@ int Engine::tune_missing(hipStream_t s) {
     double best = 1e300;
     TileCfg bc{6, 0, 1};
     for (const TileCfg& cfg : tile_candidates(c)) {
-      if (cfg.lx != 6) continue;  // the ensemble kernels stage every tile: only the band matters
       double us = 0.0;
       const int rc = time_class(c, cfg, s, &us);
       if (rc) return rc;

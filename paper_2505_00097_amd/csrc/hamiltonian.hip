@@ -19,7 +19,7 @@
 // two waves per SIMD the latency of the stage and the algebra; one thread per
 // point with every stencil value read per lane (and 300 to 500 bytes of
 // spills) took 34 us for H on the 128 x 2 x 256 grid and 244 us for all
-// three on a spherical 128 x 64 x 32 one, now 7.6 and 43 us.
+// three on a spherical 128 x 64 x 32 one, now 7.6 and 38 us.
 #include "rhs_stencil.h"
 
 // The library builds this source in parts (one kernel variant each, as
@@ -50,7 +50,6 @@ __device__ __forceinline__ void constraints_tile(const GridDev& G, const TileMap
                                                  double* __restrict__ xs0) {
   constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2;
   using CS = ConSlots<AX, H>;
-  using SRC = StagedSrc<H>;
   const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   TilePoint p;
   p.live = tile_point<H>(G, T, w, lane, p.t0, p.t1, p.t2, p.i0, p.i1, p.i2);
@@ -59,7 +58,7 @@ __device__ __forceinline__ void constraints_tile(const GridDev& G, const TileMap
   auto put = [&](int v, double x) { xs[v * 64] = x; };
   auto get = [&](int v) { return xs[v * 64]; };
   auto at = [&](int g) { return gf_ld(y, G.sgf, g, p.q * 8u, 0); };
-  const SRC S = make_source<SRC, C, AX, H>(y, G, p, lane, xs0 + (wave ? CS::GAUGE * 64 : 0));
+  const auto S = make_source<C, AX, H>(y, G, p, lane, xs0 + (wave ? CS::GAUGE * 64 : 0));
   double gU[6], gd[6];
   {
     double h[6];
@@ -86,7 +85,7 @@ __device__ __forceinline__ void constraints_tile(const GridDev& G, const TileMap
     for (int a = 0; a < 6; a++) L6[a] = 0.0;
     constexpr int list[6] = {G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
     run_stencils<C, AX, H, 0, 6, 6, false>(
-        S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+        S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
 #pragma unroll
           for (int k = 0; k < 3; k++)
             if (!(AX && k == PD)) put(CS::HK + 6 * k + a, c.s1[k] * s[k].d1);
@@ -160,7 +159,7 @@ __device__ __forceinline__ void constraints_tile(const GridDev& G, const TileMap
 #pragma unroll
     for (int t = 0; t < N; t++) list[t] = full[t];
     run_stencils<C, AX, H, 0, 1, N, false>(
-        S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+        S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
           double d[3];
 #pragma unroll
           for (int k = 0; k < 3; k++) d[k] = AX && k == PD ? 0.0 : c.s1[k] * s[k].d1;
@@ -304,7 +303,7 @@ void launch_constraints(const GridDev& G, const double* y, double* Hc, double* M
   using Get = ConLaunch (*)(bool);
   static const Get get[NVAR] = {con_part<0>, con_part<1>, con_part<2>, con_part<3>, con_part<4>,  con_part<5>,
                                 con_part<6>, con_part<7>, con_part<8>, con_part<9>, con_part<10>, con_part<11>};
-  const TileMap T = make_staged_tilemap(G, BHAH_DEFAULT_BAND);
+  const TileMap T = make_tilemap(G, BHAH_DEFAULT_BAND);
   const int per = (T.ntiles + BHAH_NXCD - 1) / BHAH_NXCD;
   get[rhs_variant(G.coord, G.N1, G.N2, G.ng)](Mo || Co)(dim3(per * BHAH_NXCD), s, G, T, y, Hc, Mo, Co);
 }

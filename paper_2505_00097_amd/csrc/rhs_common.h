@@ -77,61 +77,6 @@ struct FdW<4> {
   static constexpr double ko[6] = {-252.0, 210.0, -120.0, 45.0, -10.0, 1.0}, kden = 1024.0;
 };
 
-// Stencil access around one point, H = N_G ghost layers (stencil radius up
-// to H). Stencil values are read with raw buffer loads: the per-lane part of
-// the byte offset goes in the vector offset, the part shared by the wave in
-// the scalar offset. The periodic direction phi (i1 on SinhCylindrical
-// grids, i2 on spherical ones) is read with the index wrapped onto the
-// interior planes, so phi ghost points are never read: they are exact copies
-// of those planes (periodicity, no parity change), and the values read are
-// identical. The phi index must be the same for every lane of the wave (tile
-// extent 1 along phi).
-template <int H_>
-struct PtT {
-  static constexpr int H = H_, R = H_ - 1;
-  const double* __restrict__ y;
-  long long sgf;
-  int pd;            // periodic direction (1 or 2)
-  int se;            // stride of the other transverse direction
-  unsigned vb;       // per-lane byte offset of (i0 - H, i_e - H) with the phi index removed
-  int sw[2 * H + 1];  // byte offsets of the wrapped phi planes at offsets -H..H (wave-uniform)
-
-  __device__ __forceinline__ PtT(const double* y_, const GridDev& G, int C, int i0, int i1, int i2)
-      : y(y_), sgf(G.sgf) {
-    pd = C == BHAH_SINH_CYLINDRICAL ? 1 : 2;
-    const int sd = pd == 1 ? G.s1 : G.s2;
-    const int nd = pd == 1 ? G.N1 : G.N2;
-    se = pd == 1 ? G.s2 : G.s1;
-    const int ie = pd == 1 ? i2 : i1;
-    const int id = __builtin_amdgcn_readfirstlane((pd == 1 ? i1 : i2) - H);
-    vb = (unsigned)(i0 - H + se * (ie - H)) * 8u;
-#pragma unroll
-    for (int o = -H; o <= H; o++) {
-      int x = id + o;
-      if constexpr (H == 3) {  // nd >= 2: two corrections each way suffice
-        x += x < 0 ? nd : 0;
-        x += x < 0 ? nd : 0;
-        x -= x >= nd ? nd : 0;
-        x -= x >= nd ? nd : 0;
-      } else {
-        x %= nd;
-        x += x < 0 ? nd : 0;
-      }
-      sw[o + H] = (H + x) * sd * 8;
-    }
-  }
-
-  // value at offsets (a, b, c) along (i0, i1, i2)
-  __device__ __forceinline__ double at(int g, int a, int b, int c) const {
-    const int od = pd == 1 ? b : c, oe = pd == 1 ? c : b;
-    return gf_ld(y, sgf, g, vb + (unsigned)((a + H) * 8), sw[od + H] + (oe + H) * se * 8);
-  }
-};
-
-// index of offset m (m != 0) in a cross-stencil row
-template <int R>
-__host__ __device__ constexpr int xo(int m) { return m < 0 ? m + R : m + R - 1; }
-
 // inverse of a symmetric matrix
 __device__ __forceinline__ void sym_inverse(const double g[6], double gi[6]) {
   const double c00 = g[3] * g[5] - g[4] * g[4];

@@ -15,9 +15,9 @@ namespace bhah {
 #define BHAH_RHS_WAVES 2
 #endif
 
-// One tile per block. STG: the stencils come from LDS patches (16 x 4
-// points); otherwise from per-lane loads, for the other tile shapes.
-template <int C, bool AX, bool KO, int H, bool STG>
+// One tile per block. PUSH: the form for Runge-Kutta stages, with the stage
+// ghosts of its tile where the launch passes some.
+template <int C, bool AX, bool KO, int H, bool PUSH>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(BHAH_RHS_WAVES, BHAH_RHS_WAVES)))
 k_rhs_fused(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageArgs st, PushDev P,
             double* __restrict__ aux) {
@@ -25,20 +25,7 @@ k_rhs_fused(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageA
   const int w = xcd_remap((int)blockIdx.x, per);
   if (w >= T.ntiles) return;
   __shared__ __attribute__((aligned(16))) double xs[X_SLOTS * 64];
-  using SRC = std::conditional_t<STG, StagedSrc<H>, GatherSrc<H>>;
-  rhs_tile<C, AX, KO, H, SRC, STG>(G, T, w, ga, y, st, P, aux, xs);
-}
-
-// the staged form at 8th order on grids with more than two phi planes
-template <int C, bool KO>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(BHAH_RHS_WAVES, BHAH_RHS_WAVES)))
-k_rhs_planes8(GridDev G, TileMap T, Gauge ga, const double* __restrict__ y, StageArgs st,
-              double* __restrict__ aux) {
-  const int per = (T.ntiles + BHAH_NXCD - 1) / BHAH_NXCD;
-  const int w = xcd_remap((int)blockIdx.x, per);
-  if (w >= T.ntiles) return;
-  __shared__ __attribute__((aligned(16))) double xs[X_SLOTS * 64];
-  rhs_tile<C, false, KO, 5, StagedSrc<5>, false>(G, T, w, ga, y, st, PushDev{}, aux, xs);
+  rhs_tile<C, AX, KO, H, PUSH>(G, T, w, ga, y, st, P, aux, xs);
 }
 
 // Persistent form for ensembles: a fixed grid of blocks (a multiple of the
@@ -62,7 +49,7 @@ k_rhs_batch(const BatchJob* __restrict__ jobs, const BatchHdr* __restrict__ hdr,
     const BatchJob* J = jobs + wk.x;
     const GridDev G = J->G;
     const StageArgs st = J->st[stage];
-    rhs_tile<C, AX, KO, H, StagedSrc<H>, false>(G, J->T, wk.y, ga, J->in[stage], st, PushDev{}, nullptr, xs);
+    rhs_tile<C, AX, KO, H, false>(G, J->T, wk.y, ga, J->in[stage], st, PushDev{}, nullptr, xs);
     __syncthreads();  // the next tile's stencil stage reuses slots that the other wave reads to the end
   }
 }
@@ -71,13 +58,10 @@ using FusedLaunch = void (*)(dim3, hipStream_t, const GridDev&, const TileMap&, 
                              const StageArgs&, const PushDev&, double*);
 using BatchLaunch = void (*)(dim3, hipStream_t, const BatchJob*, const BatchHdr*, const int2*, int, const int*, int,
                              const Gauge&);
-template <int C, bool AX, bool KO, int H, bool STG>
+template <int C, bool AX, bool KO, int H, bool PUSH>
 void launch_fused_t(dim3 g, hipStream_t s, const GridDev& G, const TileMap& T, const Gauge& ga, const double* y,
                     const StageArgs& st, const PushDev& P, double* aux) {
-  if constexpr (STG && !AX && H == 5)
-    hipLaunchKernelGGL((k_rhs_planes8<C, KO>), g, dim3(128), 0, s, G, T, ga, y, st, aux);
-  else
-    hipLaunchKernelGGL((k_rhs_fused<C, AX, KO, H, STG>), g, dim3(128), 0, s, G, T, ga, y, st, P, aux);
+  hipLaunchKernelGGL((k_rhs_fused<C, AX, KO, H, PUSH>), g, dim3(128), 0, s, G, T, ga, y, st, P, aux);
 }
 template <int C, bool AX, bool KO, int H>
 void launch_batch_t(dim3 g, hipStream_t s, const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,
@@ -87,14 +71,19 @@ void launch_batch_t(dim3 g, hipStream_t s, const BatchJob* jobs, const BatchHdr*
 
 // launch tables of one variant (rhs_variant): [dissipation]
 struct RhsKernels {
-  FusedLaunch gather[2], staged[2];
+  FusedLaunch plain[2], push[2];  // push: none where rhs_pushes is false
   BatchLaunch batch[2];
 };
 template <int C, bool AX, int H>
 constexpr RhsKernels rhs_kernels() {
-  return RhsKernels{{launch_fused_t<C, AX, false, H, false>, launch_fused_t<C, AX, true, H, false>},
-                    {launch_fused_t<C, AX, false, H, true>, launch_fused_t<C, AX, true, H, true>},
-                    {launch_batch_t<C, AX, false, H>, launch_batch_t<C, AX, true, H>}};
+  RhsKernels k{{launch_fused_t<C, AX, false, H, false>, launch_fused_t<C, AX, true, H, false>},
+               {nullptr, nullptr},
+               {launch_batch_t<C, AX, false, H>, launch_batch_t<C, AX, true, H>}};
+  if constexpr (AX || H == 3) {
+    k.push[0] = launch_fused_t<C, AX, false, H, true>;
+    k.push[1] = launch_fused_t<C, AX, true, H, true>;
+  }
+  return k;
 }
 // part p holds variant p: family p / 2 % 3, two phi planes p % 2, order p / 6
 template <int V>
@@ -133,11 +122,11 @@ static const RhsKernels& kernels_of(int variant) {
   return get[variant]();
 }
 
-TileMap make_tilemap(const GridDev& G, int lx, int ly, int band) {
+TileMap make_tilemap(const GridDev& G, int band) {
   TileMap T;
-  T.lx = lx;
-  T.ly = ly;
-  const int ex = 1 << lx, ey = 1 << ly, ez = 64 >> (lx + ly);
+  T.lx = TLX;
+  T.ly = G.coord == BHAH_SINH_CYLINDRICAL ? 0 : 6 - TLX;
+  const int ex = 1 << T.lx, ey = 1 << T.ly, ez = 64 >> (T.lx + T.ly);
   T.tx = (G.N0 + ex - 1) / ex;
   T.ty = (G.N1 + ey - 1) / ey;
   T.tz = (G.N2 + ez - 1) / ez;
@@ -146,17 +135,16 @@ TileMap make_tilemap(const GridDev& G, int lx, int ly, int band) {
   return T;
 }
 
-TileMap make_staged_tilemap(const GridDev& G, int band) {
-  return make_tilemap(G, TLX, G.coord == BHAH_SINH_CYLINDRICAL ? 0 : 6 - TLX, band);
-}
-
 void launch_rhs_fused(const GridDev& G, const Gauge& ga, const double* y, double* aux, const StageArgs& st,
-                      hipStream_t s, const TileCfg& cfg, const PushDev& push) {
-  const bool staged = rhs_staged(G.coord, cfg);
-  const TileMap T = staged ? make_staged_tilemap(G, cfg.band) : make_tilemap(G, cfg.lx, cfg.ly, cfg.band);
+                      hipStream_t s, int band, const PushDev& push) {
+  const TileMap T = make_tilemap(G, band);
   const int per = (T.ntiles + BHAH_NXCD - 1) / BHAH_NXCD;
   const RhsKernels& k = kernels_of(rhs_variant(G.coord, G.N1, G.N2, G.ng));
-  (staged ? k.staged : k.gather)[ga.ko() ? 1 : 0](dim3(per * BHAH_NXCD), s, G, T, ga, y, st, push, aux);
+  // one form for all stages of a step, also the last, which pushes nothing:
+  // a change of kernel between stages costs a cold instruction cache (the
+  // 32 x 16 x 2 RK4 step 41.0 us so, 41.8 with the plain form at the last stage)
+  const FusedLaunch stage = k.push[ga.ko() ? 1 : 0];
+  (!st.rhs && stage ? stage : k.plain[ga.ko() ? 1 : 0])(dim3(per * BHAH_NXCD), s, G, T, ga, y, st, push, aux);
 }
 
 void launch_rhs_batch(int variant, const BatchJob* jobs, const BatchHdr* hdr, const int2* work, int stage,

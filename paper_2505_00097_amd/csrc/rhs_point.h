@@ -12,14 +12,14 @@
 //     It stores the other twelve.
 // What bounds it: the latency of a wave's own loads, LDS reads and arithmetic,
 // so the aim is two waves per SIMD, each within 256 registers and half of
-// 40 KB of LDS (four blocks, eight waves, per CU); on large grids the LDS and
-// vector memory pipes come next (44% and 35% busy on the 3-D grid). The split
+// 40 KB of LDS (four blocks, eight waves, per CU); on large grids it is the
+// rate of line requests to the L2s (rhs_stencil.h). The split
 // keeps about 60 values per point in each wave; what the waves exchange and
 // the stencil stages share 80 LDS slots per point (slot v of lane l at
 // xs[v * 64 + l]). One wave per tile and SIMD with the algebra in coordinate
 // components took 19.2 us for a right-hand side on the 128 x 2 x 256 head-on
 // grid, 954 us on a 256 x 128 x 64 one and 2.44 ms there at 8th order with
-// dissipation; this form takes 14.0 us, 690 us and 1.58 ms.
+// dissipation; this form takes 13.3 us, 685 us and 1.33 ms.
 #pragma once
 
 #include "rhs_stencil.h"
@@ -193,7 +193,7 @@ __device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs
 }
 
 // ---- metric wave ---------------------------------------------------------------
-template <int C, bool AX, bool KO, int H, class SRC, bool PUSH>
+template <int C, bool AX, bool KO, int H, bool PUSH>
 __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
                                             const StageArgs& st, const PushDev& P, const TilePoint& p,
                                             double* __restrict__ aux, double* __restrict__ xs0, int lane) {
@@ -202,14 +202,14 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
   auto put = [&](int v, double x) { xs[v * 64] = x; };
   auto get = [&](int v) { return xs[v * 64]; };
   auto at = [&](int g) { return gf_ld(y, G.sgf, g, p.q * 8u, 0); };
-  const SRC S = make_source<SRC, C, AX, H>(y, G, p, lane, xs0);
+  const auto S = make_source<C, AX, H>(y, G, p, lane, xs0);
   using ST = Stage<AX, H>;
   double gU[6], Pc[6], ck[6], late[24];  // late: what the park cannot take
   auto keep = [&](int i, double x) {
-    if (SRC::STG && i < ST::CAP) put(ST::park(i), x);
+    if (i < ST::CAP) put(ST::park(i), x);
     else late[i] = x;
   };
-  auto kept = [&](int i) { return SRC::STG && i < ST::CAP ? get(ST::park(i)) : late[i]; };
+  auto kept = [&](int i) { return i < ST::CAP ? get(ST::park(i)) : late[i]; };
   {
     Coefs<H> c;
     double w[6], gd[6];
@@ -232,7 +232,7 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
     for (int a = 0; a < 6; a++) { Pc[a] = 0.0; ck[a] = 0.0; }
     constexpr int list[6] = {G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
     //   Pc_ij = gammabar^kl h_ij,kl,  ck_kl = gammabar^ab h_ab,kl (unscaled)
-    run_stencils<C, AX, H, 0, 6, 6, true>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+    run_stencils<C, AX, H, 0, 6, 6, true>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
 #pragma unroll
       for (int k = 0; k < 3; k++)
         if (!(AX && k == PD)) keep(3 * a + k, c.s1[k] * s[k].d1);
@@ -421,7 +421,7 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
 }
 
 // ---- gauge wave ------------------------------------------------------------------
-template <int C, bool AX, bool KO, int H, class SRC, bool PUSH>
+template <int C, bool AX, bool KO, int H, bool PUSH>
 __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, const double* __restrict__ y,
                                            const StageArgs& st, const PushDev& P, const TilePoint& p,
                                            double* __restrict__ xs0, int lane) {
@@ -430,7 +430,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
   auto put = [&](int v, double x) { xs[v * 64] = x; };
   auto get = [&](int v) { return xs[v * 64]; };
   auto at = [&](int g) { return gf_ld(y, G.sgf, g, p.q * 8u, 0); };
-  const SRC S = make_source<SRC, C, AX, H>(y, G, p, lane, xs0 + Stage<AX, H>::GAUGE * 64);
+  const auto S = make_source<C, AX, H>(y, G, p, lane, xs0 + Stage<AX, H>::GAUGE * 64);
   double gU[6], Y[6], Za = 0.0, Bv[3], Bd[3], ak[3], phi[3], Kk[3];
   double advW = 0.0, advAl = 0.0, advK = 0.0, advV[3], advL[3], advB[3], koL[3];
 #pragma unroll
@@ -458,7 +458,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
     // the gridfunctions with second derivatives come while few results wait in registers
     constexpr int list[18] = {0, 1, 2, 3, 4, 5, G_VETU0, G_VETU0 + 1, G_VETU0 + 2, G_CF, G_ALPHA,
                               G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2, G_TRK, G_BETU0, G_BETU0 + 1, G_BETU0 + 2};
-    run_stencils<C, AX, H, 6, 11, 15, true>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6]) BHAH_INLINE {
+    run_stencils<C, AX, H, 6, 11, 15, true>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
       const bool gauge = (t >= 6 && t < 9) || t == 10 || t >= 15;
       const double adv = gauge ? advect<H>(s, c.ch, c.qg) : advect<H>(s, c.ch, c.q);
       double d[3];
@@ -679,7 +679,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
 // One tile by the block's two waves. Every lane takes part (lanes past the
 // grid compute a point on it and store nothing). PUSH: with the tile's pushed
 // ghosts.
-template <int C, bool AX, bool KO, int H, class SRC, bool PUSH>
+template <int C, bool AX, bool KO, int H, bool PUSH>
 __device__ __forceinline__ void rhs_tile(const GridDev& G, const TileMap& T, int w, const Gauge& ga,
                                          const double* __restrict__ y, const StageArgs& st, const PushDev& P,
                                          double* __restrict__ aux, double* __restrict__ xs) {
@@ -687,8 +687,8 @@ __device__ __forceinline__ void rhs_tile(const GridDev& G, const TileMap& T, int
   TilePoint p;
   p.live = tile_point<H>(G, T, w, lane, p.t0, p.t1, p.t2, p.i0, p.i1, p.i2);
   p.q = (unsigned)(p.i0 + G.s1 * p.i1 + G.s2 * p.i2);
-  if (wave == 0) metric_wave<C, AX, KO, H, SRC, PUSH>(G, ga, y, st, P, p, aux, xs, lane);
-  else gauge_wave<C, AX, KO, H, SRC, PUSH>(G, ga, y, st, P, p, xs, lane);
+  if (wave == 0) metric_wave<C, AX, KO, H, PUSH>(G, ga, y, st, P, p, aux, xs, lane);
+  else gauge_wave<C, AX, KO, H, PUSH>(G, ga, y, st, P, p, xs, lane);
 }
 
 }  // namespace bhah

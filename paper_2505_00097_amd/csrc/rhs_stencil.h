@@ -1,7 +1,7 @@
 // rhs_stencil.h -- the stencil side of the right-hand side (rhs_point.h) and
 // the constraints (hamiltonian.hip): the stencil sums of one gridfunction,
-// where its values come from (LDS patches of a tile, or per-lane loads), the
-// loops over gridfunctions, and the tile walk.
+// the LDS patches its values come from, the loop over gridfunctions, and the
+// tile walk.
 #pragma once
 
 #include <type_traits>
@@ -118,60 +118,93 @@ __device__ __forceinline__ double d1_sum(const double (&v)[2 * R + 1]) {
 }
 
 // ---- where stencil values come from ----------------------------------------
-// A tile is a patch of EX points along i0 and EE along the other
-// non-periodic direction e (i2 on SinhCylindrical grids, i1 otherwise) on one
-// phi plane: 16 x 4. For one gridfunction at a time the wave brings the
-// patch with its halo into LDS with 16-byte loads and takes every stencil
-// value along i0 and e and of the mixed pair (0, e) from there. On grids with
-// more than two phi planes the planes at phi offsets +-j follow in pairs, for
-// the mixed pairs (0, phi) and (e, phi); values at phi offsets +-(R+1), and
-// all phi offsets of gridfunctions without second derivatives, are read per
-// lane. The CU's vector memory path takes about the same time for every load
-// instruction whatever its width (16 cycles measured for 64 lanes), so what
-// counts is the number of instructions: a 16 x 4 patch with its halo at 4th
-// order is 22 x 10 values, two loads, where a row of 64 points would be 7 x
-// 70, four, and per-lane gathers 30 to 70.
+// A tile is a patch of 16 points along i0 and 4 along the other non-periodic
+// direction e (i2 on SinhCylindrical grids, i1 otherwise) on one phi plane.
+// For one gridfunction at a time the wave brings the patch with its halo into
+// LDS with 16-byte loads and takes every stencil value along i0 and e from
+// there; values at other phi planes are read per lane. The CU's vector memory
+// path takes about the same time for every load instruction whatever its width
+// (16 cycles measured for 64 lanes), so what counts is the number of
+// instructions: a 16 x 4 patch with its halo at 4th order is 22 x 10 values,
+// two loads, where a row of 64 points would be 7 x 70, four, and per-lane
+// gathers 30 to 70.
+// Mixed derivatives are taken one direction at a time: every lane's D_e f
+// (which its first derivative needs anyway) goes into a second LDS patch, with
+// those of the halo columns, and D_0 of it is the mixed pair (0, e); the same
+// with D_phi f and a halo in both directions for (0, phi) and (e, phi). On
+// general grids this reads 16 values from LDS per gridfunction at 4th order
+// and 32 at 8th where products of stencils read 52 and 192, and leaves
+// registers free: a right-hand side of one 72 x 12 x 24 grid takes 12.6 us
+// instead of 14.3, at 8th order with dissipation 1.32 ms instead of 1.53 on a
+// 256 x 128 x 64 one.
 constexpr int TLX = PATCH_LX, TEX = PATCH_X, TEE = PATCH_E;
-// row length and 16-byte pieces of the main patch (halo H) and of one pair of
-// phi planes (halo R each)
-template <int H>
+template <int H, bool AX>
 struct Patch {
   static constexpr int R = H - 1;
-  static constexpr int RL = TEX + 2 * H, RE = TEE + 2 * H, NP = RL * RE / 2, NR = (NP + 63) / 64;
-  static constexpr int QL = TEX + 2 * R, QE = TEE + 2 * R, QN = QL * QE, QP = QN, QR = (QP + 63) / 64;
-  static constexpr int MAIN = 2 * NP, PAIR = 2 * QN;  // doubles
+  // the main patch (halo H): row length, 16-byte pieces, loads, doubles
+  static constexpr int RL = TEX + 2 * H, NP = RL * (TEE + 2 * H) / 2, NR = (NP + 63) / 64, MAIN = 2 * NP;
+  // the derivative patches: of D_e with a halo R along i0, on general grids
+  // of D_phi with one along e too
+  static constexpr int GL = TEX + 2 * R, EN = GL * TEE, PN = AX ? 0 : GL * (TEE + 2 * R);
+  // The phi planes at offsets -R..R, in pairs of points. 4th order (RAW): the
+  // patch's rows with their halo along i0, then the rows of the halo along e,
+  // D_phi of each formed in registers; the point's own values come from the
+  // same loads through LDS (a raw patch of the four planes). What bounds 3-D
+  // grids is the rate of line requests from the CUs to the L2s (115 per ns),
+  // so no line is asked for twice: with the halo alone in pairs and the
+  // point's own column loaded apart the 256 x 128 x 64 right-hand side makes
+  // 92 instead of 83 million requests, 716 instead of 687 us. At 8th order
+  // LDS has no room for the raw patch: halo (rows along e, then columns) and
+  // own column there.
+  static constexpr bool RAW = !AX && H == 3;
+  static constexpr int IN = GL / 2 * TEE, HROWS = 2 * R * TEX / 2, HP = RAW ? IN + HROWS : HROWS + TEE * R;
+  static constexpr int HR = (HP + 63) / 64;
+  static constexpr int RAWP = GL * TEE, RN = RAW ? 2 * R * RAWP : 0, DUMP = RAW ? 2 * (64 - IN) : 0;
 };
 
-// All accessors give f at offsets (d0, de) on the point's phi plane or on the
-// plane at phi offset +-j, and the phi column of the point.
-template <int H>
-struct StagedSrc {
-  static constexpr bool STG = true;
-  using PG = Patch<H>;
-  static constexpr int R = H - 1;
+// a wave's stencil stage: PER gridfunctions at a time (main patch, D_e
+// patch), then the D_phi patch
+template <bool AX, int H>
+struct StageSize {
+  static constexpr int PER = AX && H == 3 ? 2 : 1;
+  using PG = Patch<H, AX>;
+  static constexpr int DN = PER * PG::EN + PG::PN;  // the derivative patches; the raw patch lies over them
+  static constexpr int N = PER * PG::MAIN + (PG::RN > DN ? PG::RN : DN) + PG::DUMP;  // doubles
+  static constexpr int SL = (N + 63) / 64;                                           // slots of 64
+};
+
+// All lanes work at their own place in the patch, also where it lies past the
+// grid (their loads stay in the descriptors' bounds, their values reach no
+// point on the grid).
+template <int H, bool AX>
+struct Source {
+  using PG = Patch<H, AX>;
+  static constexpr int R = H - 1, PER = StageSize<AX, H>::PER;
+  static constexpr int EB = PER * PG::MAIN, PB = EB + PER * PG::EN;  // where the D_e and D_phi patches begin
   const double* y;
   long long sgf;
-  double* lds;         // the wave's stage: main patches, then a pair of phi planes
-  unsigned voff[PG::NR], qoff[PG::QR];  // per-lane byte offsets of the lane's pieces
+  double* lds;             // the wave's stage
   int lane;
-  unsigned vlane;      // per-lane byte offset of the point, phi index removed
-  int sw[2 * H + 1];   // byte offsets of the (wrapped) phi planes at offsets -H..H, wave-uniform
-  unsigned org;        // byte offset of the patch origin (halo H), phi index removed, wave-uniform
-  int c0, q0;          // the point's place in the main patch and in a phi-plane patch
+  unsigned voff[PG::NR];   // per-lane byte offsets of the lane's pieces of the main patch
+  unsigned hoff[PG::HR];   // ... of its pairs of the phi halo
+  int hpos[PG::HR];        // their place in the D_phi patch
+  int rpos, rstep;         // place of the first pairs in the raw patch, step from plane to plane
+  unsigned vlane;          // byte offset of the point, phi index removed
+  int sw[2 * H + 1];       // byte offsets of the (wrapped) phi planes at offsets -H..H, wave-uniform
+  unsigned org;            // byte offset of the patch origin (halo H), phi index removed, wave-uniform
+  int c0, g0;              // the point's place in the main and in a D_e patch
+  int hc0, hg0;            // the same of the lane's halo column point
 
-  // tile origin (it, et), point (i0, ie), phi index ip; sE, sP strides
-  __device__ __forceinline__ void init(const double* y_, const GridDev& G, int pd, int it, int et, int i0, int ie,
-                                       int ip, int lane_, double* lds_, bool two_planes) {
-    y = y_;
-    lane = lane_;
-    sgf = G.sgf;
-    lds = lds_;
+  // tile origin (it, et), phi index ip; pd: the phi direction
+  __device__ __forceinline__ Source(const double* y_, const GridDev& G, int pd, int it, int et, int ip, int lane_,
+                                    double* lds_)
+      : y(y_), sgf(G.sgf), lds(lds_), lane(lane_) {
     const int sP = pd == 1 ? G.s1 : G.s2, sE = pd == 1 ? G.s2 : G.s1, nP = pd == 1 ? G.N1 : G.N2;
     const int id = ip - H;
 #pragma unroll
     for (int o = -H; o <= H; o++) {
       int x = id + o;
-      if (two_planes) {
+      if (AX) {
         x = (x + 2 * H) & 1;
       } else if constexpr (H == 3) {  // nP >= 2: two corrections each way suffice
         x += x < 0 ? nP : 0;
@@ -185,40 +218,65 @@ struct StagedSrc {
       sw[o + H] = (H + x) * sP * 8;
     }
     org = (unsigned)((it - H) + sE * (et - H)) * 8u;
-    vlane = (unsigned)(i0 + sE * ie) * 8u;
+    const int x = lane & (TEX - 1), e = lane >> TLX;
+    vlane = org + (unsigned)((x + H) + sE * (e + H)) * 8u;
 #pragma unroll
     for (int r = 0; r < PG::NR; r++) {
       const int p = piece<PG::NP>(r), row = p / (PG::RL / 2), col = 2 * (p - row * (PG::RL / 2));
       voff[r] = (unsigned)(col + row * sE) * 8u;
     }
-    if (!two_planes) {
+    c0 = (e + H) * PG::RL + x + H;
+    g0 = e * PG::GL + x + R;
+    {  // 2R halo columns of TEE points; lanes beyond repeat them
+      const int p = lane & (2 * R * TEE - 1), he = p / (2 * R), k = p & (2 * R - 1);
+      const int hx = k < R ? k - R : TEX + k - R;
+      hc0 = (he + H) * PG::RL + hx + H;
+      hg0 = he * PG::GL + hx + R;
+    }
+    if constexpr (!AX) {
 #pragma unroll
-      for (int r = 0; r < PG::QR; r++) {
-        int p = piece<PG::QP>(r);
-        if (far_plane(r)) p -= PG::QN / 2;
-        const int row = p / (PG::QL / 2), col = 2 * (p - row * (PG::QL / 2));
-        qoff[r] = (unsigned)((col + 1) + (row + 1) * sE) * 8u;  // halo R = H - 1
+      for (int r = 0; r < PG::HR; r++) {
+        int hx, he;
+        const int p = piece<PG::HP>(r), q = p - (PG::RAW ? PG::IN : PG::HROWS);
+        if (PG::RAW ? q >= 0 : q < 0) {
+          const int row = PG::RAW ? q : p;
+          he = row / (TEX / 2);
+          hx = 2 * (row & (TEX / 2 - 1));
+          he = he < R ? he - R : TEE + he - R;
+        } else if (PG::RAW) {
+          he = p / (PG::GL / 2);
+          hx = 2 * (p - he * (PG::GL / 2)) - R;
+        } else {
+          he = q / R;
+          hx = 2 * (q & (R - 1));
+          hx = hx < R ? hx - R : TEX + hx - R;
+        }
+        hoff[r] = (unsigned)((hx + H) + (he + H) * sE) * 8u;
+        hpos[r] = (he + R) * PG::GL + hx + R;
+      }
+      if constexpr (PG::RAW) {  // the pairs of other rows go to places that nobody reads
+        rpos = EB + (lane < PG::IN ? 2 * lane : PG::RN + 2 * (lane - PG::IN));
+        rstep = lane < PG::IN ? PG::RAWP : 0;
       }
     }
-    c0 = (ie - et + H) * PG::RL + (i0 - it + H);
-    q0 = (ie - et + R) * PG::QL + (i0 - it + R);
   }
-  // the lane's r-th 16-byte piece of N; past the last one it repeats it, so
-  // that every lane loads and stores in bounds
+  // the lane's r-th piece of N; past the last one it repeats it, so that every
+  // lane loads and stores in bounds
   template <int N>
   __device__ __forceinline__ int piece(int r) const {
     return (r + 1) * 64 <= N ? r * 64 + lane : min(r * 64 + lane, N - 1);
   }
-  // whether it lies on the second plane (phi offset -j) of a pair
-  __device__ __forceinline__ bool far_plane(int r) const {
-    constexpr int half = PG::QN / 2;
-    return (r + 1) * 64 <= half ? false : (r * 64 >= half ? true : r * 64 + lane >= half);
+  // two values at an even place, in one 16-byte write (as two writes of 8
+  // bytes neighbouring lanes' would conflict)
+  __device__ __forceinline__ void put2(int at, double a, double b) const {
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    *(d2*)(lds + at) = d2{a, b};
   }
   struct MainRegs {
     double lo[PG::NR], hi[PG::NR];
   };
-  struct PairRegs {
-    double lo[PG::QR], hi[PG::QR];
+  struct HaloRegs {
+    double lo[2 * R + 1], hi[2 * R + 1];  // phi offsets -R..R (0 unused)
   };
   __device__ __forceinline__ void issue_main(int g, MainRegs& m) const {
 #pragma unroll
@@ -227,41 +285,72 @@ struct StagedSrc {
   __device__ __forceinline__ void commit_main(const MainRegs& m, int slot) const {
 #pragma unroll
     for (int r = 0; r < PG::NR; r++) {
-      lds[slot * PG::MAIN + 2 * piece<PG::NP>(r)] = m.lo[r];
-      lds[slot * PG::MAIN + 2 * piece<PG::NP>(r) + 1] = m.hi[r];
+      put2(slot * PG::MAIN + 2 * piece<PG::NP>(r), m.lo[r], m.hi[r]);
     }
   }
-  __device__ __forceinline__ void issue_pair(int g, int j, PairRegs& m) const {
+  __device__ __forceinline__ void issue_halo(int g, int r, HaloRegs& h) const {
+    h.lo[R] = h.hi[R] = 0.0;
 #pragma unroll
-    for (int r = 0; r < PG::QR; r++)
-      gf_ld2(y, sgf, g, qoff[r] + (unsigned)(far_plane(r) ? sw[H - j] : sw[H + j]), (int)org, m.lo[r], m.hi[r]);
+    for (int m = -R; m <= R; m++)
+      if (m != 0) gf_ld2(y, sgf, g, hoff[r], (int)org + sw[H + m], h.lo[R + m], h.hi[R + m]);
   }
-  __device__ __forceinline__ void commit_pair(const PairRegs& m, int base) const {
+  // the lane's first pair of every plane, into the raw patch
+  __device__ __forceinline__ void commit_raw(const HaloRegs& h) const {
+    int at = rpos;
 #pragma unroll
-    for (int r = 0; r < PG::QR; r++) {
-      lds[base + 2 * piece<PG::QP>(r)] = m.lo[r];
-      lds[base + 2 * piece<PG::QP>(r) + 1] = m.hi[r];
-    }
+    for (int m = -R; m <= R; m++)
+      if (m != 0) {
+        put2(at, h.lo[R + m], h.hi[R + m]);
+        at += rstep;
+      }
   }
-  __device__ __forceinline__ double main_at(int slot, int d0, int de) const {
-    return lds[slot * PG::MAIN + c0 + de * PG::RL + d0];
+  // the point's own values there (v[H + m])
+  __device__ __forceinline__ void raw_column(double (&v)[2 * H + 1]) const {
+#pragma unroll
+    for (int m = -R; m <= R; m++)
+      if (m != 0) v[H + m] = lds[EB + (m + R - (m > 0)) * PG::RAWP + g0];
   }
-  __device__ __forceinline__ double pair_at(int base, int side, int d0, int de) const {
-    return lds[base + side * PG::QN + q0 + de * PG::QL + d0];
+  // D_phi of the lane's r-th pair of points
+  __device__ __forceinline__ void put_halo(int r, double lo, double hi) const {
+    put2(PB + hpos[r], lo, hi);
   }
+  __device__ __forceinline__ void commit_halo(const HaloRegs& h, int r) const {
+    put_halo(r, d1_sum<R>(h.lo), d1_sum<R>(h.hi));
+  }
+  // the values along i0 and e around the point
+  __device__ __forceinline__ void cross(int slot, double (&v0)[2 * H + 1], double (&vE)[2 * H + 1]) const {
+    const double* p = lds + slot * PG::MAIN + c0;
+#pragma unroll
+    for (int m = -H; m <= H; m++) vE[H + m] = p[m * PG::RL];
+#pragma unroll
+    for (int m = -H; m <= H; m++) v0[H + m] = m == 0 ? vE[H] : p[m];
+  }
+  // the values along e around the lane's halo column point
+  __device__ __forceinline__ void halo_column(int slot, double (&v)[2 * R + 1]) const {
+    v[R] = 0.0;
+#pragma unroll
+    for (int m = -R; m <= R; m++)
+      if (m != 0) v[R + m] = lds[slot * PG::MAIN + hc0 + m * PG::RL];
+  }
+  __device__ __forceinline__ void put_e(int slot, double own, double halo) const {
+    lds[EB + slot * PG::EN + g0] = own;
+    lds[EB + slot * PG::EN + hg0] = halo;
+  }
+  __device__ __forceinline__ void put_p(double own) const { lds[PB + R * PG::GL + g0] = own; }
+  // values of a derivative patch around the point: D_e along i0, D_phi along i0 and e
+  __device__ __forceinline__ void around(int at, int step, double (&v)[2 * R + 1]) const {
+    v[R] = 0.0;
+#pragma unroll
+    for (int m = -R; m <= R; m++)
+      if (m != 0) v[R + m] = lds[at + m * step];
+  }
+  __device__ __forceinline__ void e_along_0(int slot, double (&v)[2 * R + 1]) const {
+    around(EB + slot * PG::EN + g0, 1, v);
+  }
+  __device__ __forceinline__ void p_along_0(double (&v)[2 * R + 1]) const { around(PB + R * PG::GL + g0, 1, v); }
+  __device__ __forceinline__ void p_along_e(double (&v)[2 * R + 1]) const { around(PB + R * PG::GL + g0, PG::GL, v); }
   // value in the point's phi column
   __device__ __forceinline__ double column(int g, int m) const { return gf_ld(y, sgf, g, vlane, sw[H + m]); }
-};
-
-// per-lane loads (tile shapes other than the staged patch)
-template <int H>
-struct GatherSrc {
-  static constexpr bool STG = false;
-  PtT<H> P;
-  int pd;
-  __device__ __forceinline__ double at(int g, int d0, int de, int dp) const {
-    return pd == 1 ? P.at(g, d0, dp, de) : P.at(g, d0, de, dp);
-  }
 };
 
 // Tiles: 64 points, 2^lx along i0 times 2^ly along i1 times 64 >> (lx + ly)
@@ -306,15 +395,6 @@ __device__ __forceinline__ bool tile_point(const GridDev& G, const TileMap& T, i
 // multiple of the XCD count, block b runs on XCD b % nxcd
 __device__ __forceinline__ int xcd_remap(int b, int per) { return (b % BHAH_NXCD) * per + b / BHAH_NXCD; }
 
-// a wave's stencil stage: PER main patches on grids with two phi planes (a
-// batch of gridfunctions), else one main patch and a pair of phi planes
-template <bool AX, int H>
-struct StageSize {
-  static constexpr int PER = AX && H == 3 ? 2 : 1;
-  static constexpr int N = AX ? PER * Patch<H>::MAIN : Patch<H>::MAIN + Patch<H>::PAIR;  // doubles
-  static constexpr int SL = (N + 63) / 64;                                              // slots of 64
-};
-
 // scales of the derivatives and upwind coefficients at a point
 template <int H>
 struct Coefs {
@@ -354,62 +434,30 @@ __device__ __forceinline__ double advect(const AxisSums (&s)[3], const double (&
   return a;
 }
 
-// ---- stencil drivers ---------------------------------------------------------
-// Runs over the gridfunctions list[0..N): for each, fn(t, axis sums
-// along the three directions, raw second differences dd[sy(k, l)]); dd is
-// formed for t in [F0, F1), first derivatives are used for t in [F0, F2), the
-// upwinded sums where ADV.
-// Identically vanishing phi derivatives of two-plane
-// grids are literal zeros. The arithmetic is the same for both sources.
+// ---- the stencil loop ----------------------------------------------------------
 // whether d_k d_l, kl = sy(k, l), vanishes identically (mixed with phi on two planes)
 template <bool AX, int PD>
 __device__ __forceinline__ constexpr bool zero_pair(int kl) {
   return AX && (kl == sy(0, PD) || kl == sy(3 - PD, PD));
 }
-template <int R>
-__device__ __forceinline__ double acc_pair(int j, double acc, double p, double m) {
-  return j == 1 ? FdW<R>::d1[1] * (p - m) : fma(FdW<R>::d1[j], p - m, acc);
-}
 
+// For each gridfunction list[t], t < N: fn(t, raw sums along the three
+// directions, raw second differences dd[sy(k, l)], value at the point); dd is
+// formed for t in [F0, F1), first derivatives are used for t in [F0, F2), the
+// upwinded sums where ADV. Identically vanishing phi derivatives of two-plane
+// grids are literal zeros. Loads run one gridfunction (two-plane grids at 4th
+// order: a batch of two) ahead of their use: at 4th order all of the next
+// gridfunction's at the start of an iteration (those of other phi planes in
+// its middle: 657 instead of 643 us on the 3-D grid), at 8th order, short of
+// registers, the phi planes in the middle. Two ahead takes 3% longer: the
+// waves' lines push each other out of the L1.
 template <int C, bool AX, int H, int F0, int F1, int F2, bool ADV, int N, class FN>
-__device__ __forceinline__ void run_stencils(const StagedSrc<H>& S, const int (&list)[N], const FN& fn) {
+__device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (&list)[N], const FN& fn) {
   constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
-  using SS_ = StagedSrc<H>;
-  auto in_plane = [&](int slot, bool full, bool first, AxisSums(&s)[3], double (&dd)[6], double& c) BHAH_INLINE {
-    double v0[2 * H + 1], vE[2 * H + 1];
-#pragma unroll
-    for (int m = -H; m <= H; m++) {
-      v0[H + m] = S.main_at(slot, m, 0);
-      vE[H + m] = m == 0 ? v0[H] : S.main_at(slot, 0, m);
-    }
-    c = v0[H];
-    s[0] = axis_sums<R>(v0);
-    s[E] = axis_sums<R>(vE);
-    pin<ADV>(s[0], first, full);
-    pin<ADV>(s[E], first, full);
-    if (full) {
-      if constexpr (H == 5) BHAH_PHASE_BARRIER();
-      double e[2 * R + 1];
-      e[R] = 0.0;
-#pragma unroll
-      for (int m = -R; m <= R; m++)
-        if (m != 0) {
-          double r[2 * R + 1];
-          r[R] = 0.0;
-#pragma unroll
-          for (int n = -R; n <= R; n++)
-            if (n != 0) r[R + n] = S.main_at(slot, n, m);
-          e[R + m] = d1_sum<R>(r);
-          pin(e[R + m]);
-          if constexpr (H == 5) BHAH_PHASE_BARRIER();
-        }
-      dd[sy(0, E)] = d1_sum<R>(e);
-      pin(dd[sy(0, E)]);
-    }
-  };
+  using PG = Patch<H, AX>;
   if constexpr (AX) {
     constexpr int PER = StageSize<AX, H>::PER, NB = (N + PER - 1) / PER;
-    typename SS_::MainRegs m[PER];
+    typename Source<H, AX>::MainRegs m[PER];
     double ph[PER];
     auto issue = [&](int b) {
 #pragma unroll
@@ -431,46 +479,70 @@ __device__ __forceinline__ void run_stencils(const StagedSrc<H>& S, const int (&
         }
       if constexpr (b + 1 < NB) issue(b + 1);
       BHAH_PHASE_BARRIER();
+      // every read of the batch's main patches, then its D_e patches, so that
+      // one gridfunction's reads are under way while another's are waited for
+      double v0[PER][2 * H + 1], vE[PER][2 * H + 1], vh[PER][2 * R + 1];
+      AxisSums s[PER][3];
       static_for<PER>([&](auto tc) BHAH_INLINE {
         constexpr int t = decltype(tc)::value, tt = b * PER + t;
         if constexpr (tt < N) {
-          AxisSums s[3];
-          double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
-          in_plane(t, tt >= F0 && tt < F1, tt >= F0 && tt < F2, s, dd, c);
-          s[PD] = axis_sums_two_planes<R>(c, o[t]);
+          S.cross(t, v0[t], vE[t]);
+          if constexpr (tt >= F0 && tt < F1) S.halo_column(t, vh[t]);
+        }
+      });
+      static_for<PER>([&](auto tc) BHAH_INLINE {
+        constexpr int t = decltype(tc)::value, tt = b * PER + t;
+        if constexpr (tt < N) {
+          s[t][E] = axis_sums<R>(vE[t]);
+          pin<ADV>(s[t][E], tt >= F0 && tt < F2, tt >= F0 && tt < F1);
+          if constexpr (tt >= F0 && tt < F1) S.put_e(t, s[t][E].d1, d1_sum<R>(vh[t]));
+        }
+      });
+      static_for<PER>([&](auto tc) BHAH_INLINE {
+        constexpr int t = decltype(tc)::value, tt = b * PER + t;
+        if constexpr (tt < N) {
+          constexpr bool full = tt >= F0 && tt < F1;
+          double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, w[2 * R + 1];
+          if constexpr (full) S.e_along_0(t, w);
+          s[t][0] = axis_sums<R>(v0[t]);
+          pin<ADV>(s[t][0], tt >= F0 && tt < F2, full);
+          if constexpr (full) {
+            dd[sy(0, E)] = d1_sum<R>(w);
+            pin(dd[sy(0, E)]);
+          }
+          s[t][PD] = axis_sums_two_planes<R>(v0[t][H], o[t]);
 #pragma unroll
-          for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
-          fn(tt, s, dd);
+          for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[t][k].d2;
+          fn(tt, s[t], dd, v0[t][H]);
         }
       });
     });
   } else {
-    constexpr int PB = SS_::PG::MAIN;  // the phi planes' place in the stage
-    // Loads run one gridfunction ahead of their use. At 8th order, where a
-    // gridfunction has four pairs of phi planes, one pair and then the next
-    // main patch: more in flight spills (3-D production step 6.0 instead of
-    // 5.2 ms); at 4th order deeper prefetch measures the same.
-    constexpr int PS = H == 3 ? 2 : 1;
-    typename SS_::MainRegs m;
-    typename SS_::PairRegs pr[PS];
+    constexpr bool RAW = PG::RAW;
+    typename Source<H, AX>::MainRegs m;
+    typename Source<H, AX>::HaloRegs h[RAW ? PG::HR : 1];
     double col[2 * H];  // phi offsets -H..-1, 1..H
-    auto issue = [&](auto tc) BHAH_INLINE {
+    // a gridfunction's values at other phi planes are fetched together: they
+    // share cache lines
+    auto issue_phi = [&](auto tc) BHAH_INLINE {
       constexpr int t = decltype(tc)::value;
       if constexpr (t < N) {
-        S.issue_main(list[t], m);
+        constexpr bool full = t >= F0 && t < F1;
+        if constexpr (RAW && full) {
+          S.issue_halo(list[t], 0, h[0]);
+          S.issue_halo(list[t], 1, h[PG::HR - 1]);
+        }
 #pragma unroll
-        for (int o = 1; o <= H; o++)
-          if (o == H ? ADV : !(t >= F0 && t < F1)) {
+        for (int o = 1; o <= (ADV ? H : R); o++)
+          if (o == H || !(RAW && full)) {
             col[H - o] = S.column(list[t], -o);
             col[H + o - 1] = S.column(list[t], o);
           }
+        if constexpr (!RAW && full) S.issue_halo(list[t], 0, h[0]);
       }
     };
-    issue(std::integral_constant<int, 0>{});
-    if constexpr (F0 == 0) {
-#pragma unroll
-      for (int j = 1; j <= PS; j++) S.issue_pair(list[0], j, pr[j - 1]);
-    }
+    S.issue_main(list[0], m);
+    issue_phi(std::integral_constant<int, 0>{});
     static_for<N>([&](auto tc) BHAH_INLINE {
       constexpr int t = decltype(tc)::value;
       constexpr bool full = t >= F0 && t < F1;
@@ -478,142 +550,89 @@ __device__ __forceinline__ void run_stencils(const StagedSrc<H>& S, const int (&
       vP[0] = vP[2 * H] = 0.0;
       S.commit_main(m, 0);
 #pragma unroll
-      for (int o = 1; o <= H; o++)
-        if (o == H ? ADV : !full) {
+      for (int o = 1; o <= (ADV ? H : R); o++)
+        if (o == H || !(RAW && full)) {
           vP[H - o] = col[H - o];
           vP[H + o] = col[H + o - 1];
         }
-      if constexpr (H == 3 || !full) issue(std::integral_constant<int, t + 1>{});
-      // the first pairs: a gridfunction early, at 8th order with their own main patch
-      if constexpr (H == 3 ? t + 1 == F0 : full && t > 0) {
+      double dP[4];  // D_phi of the lane's pairs (4th order)
+      if constexpr (RAW && full) {
+        S.commit_raw(h[0]);
 #pragma unroll
-        for (int j = 1; j <= PS; j++) S.issue_pair(list[H == 3 ? F0 : t], j, pr[j - 1]);
+        for (int r = 0; r < 2; r++) {
+          dP[2 * r] = d1_sum<R>(h[r].lo);
+          dP[2 * r + 1] = d1_sum<R>(h[r].hi);
+          pin(dP[2 * r]);
+          pin(dP[2 * r + 1]);
+        }
       }
+      // two rounds of halo loads (8th order): the first, the rows, now
+      if constexpr (!RAW && full && PG::HR == 2) {
+        S.commit_halo(h[0], 0);
+        S.issue_halo(list[t], 1, h[0]);
+      }
+      if constexpr (t + 1 < N) S.issue_main(list[t + 1], m);
+      if constexpr (RAW) issue_phi(std::integral_constant<int, t + 1>{});
       BHAH_PHASE_BARRIER();
       AxisSums s[3];
-      double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, c;
-      in_plane(0, full, t >= F0 && t < F2, s, dd, c);
-      vP[H] = c;
+      double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, v0[2 * H + 1], vE[2 * H + 1];
+      constexpr bool first = t >= F0 && t < F2;
+      S.cross(0, v0, vE);
+      vP[H] = v0[H];
+      if constexpr (RAW && full) S.raw_column(vP);
+      auto sum = [&](int k, const double(&v)[2 * H + 1]) BHAH_INLINE {
+        s[k] = axis_sums<R>(v);
+        pin<ADV>(s[k], first, full);
+      };
+      auto mixed = [&](int kl, const double(&v)[2 * R + 1]) BHAH_INLINE {
+        dd[kl] = d1_sum<R>(v);
+        pin(dd[kl]);
+      };
+      sum(PD, vP);
       if constexpr (full) {
-        double a0 = 0.0, aE = 0.0;
-        static_for<R>([&](auto jc) BHAH_INLINE {
-          constexpr int j = decltype(jc)::value + 1;
-          S.commit_pair(pr[(j - 1) % PS], PB);
-          if constexpr (j + PS <= R) S.issue_pair(list[t], j + PS, pr[(j - 1) % PS]);
-          else if constexpr (H == 3 && t + 1 < F1) S.issue_pair(list[t + 1], j + PS - R, pr[(j - 1) % PS]);
-          if constexpr (H == 5 && j == R) issue(std::integral_constant<int, t + 1>{});
+        double vh[2 * R + 1], w[3][2 * R + 1];
+        S.halo_column(0, vh);
+        if constexpr (RAW) {
+          S.put_halo(0, dP[0], dP[1]);
+          S.put_halo(1, dP[2], dP[3]);
+        } else {
+          S.put_p(s[PD].d1);
+          S.commit_halo(h[0], PG::HR - 1);
+        }
+        sum(E, vE);
+        S.put_e(0, s[E].d1, d1_sum<R>(vh));
+        if constexpr (!RAW) issue_phi(std::integral_constant<int, t + 1>{});
+        // at 4th order the reads of the derivative patches are under way
+        // during the sums along i0; at 8th there are no registers for that
+        if constexpr (H != 3) sum(0, v0);
+        BHAH_PHASE_BARRIER();
+        S.p_along_0(w[0]);
+        if constexpr (H != 3) mixed(sy(0, PD), w[0]);
+        S.p_along_e(w[1]);
+        if constexpr (H != 3) {
+          mixed(sy(E, PD), w[1]);
           BHAH_PHASE_BARRIER();
-          double e0[2], eE[2];
-#pragma unroll
-          for (int side = 0; side < 2; side++) {
-            double r0[2 * R + 1], rE[2 * R + 1];
-            r0[R] = rE[R] = 0.0;
-#pragma unroll
-            for (int n = -R; n <= R; n++)
-              if (n != 0) {
-                r0[R + n] = S.pair_at(PB, side, n, 0);
-                rE[R + n] = S.pair_at(PB, side, 0, n);
-              }
-            e0[side] = d1_sum<R>(r0);
-            eE[side] = d1_sum<R>(rE);
-            vP[side ? H - j : H + j] = S.pair_at(PB, side, 0, 0);
-          }
-          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
-          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
-          pin(a0);
-          pin(aE);
-          BHAH_PHASE_BARRIER();
-        });
-        dd[sy(0, PD)] = a0;
-        dd[sy(E, PD)] = aE;
+        }
+        S.e_along_0(0, w[2]);
+        if constexpr (H == 3) {
+          sum(0, v0);
+          mixed(sy(0, PD), w[0]);
+          mixed(sy(E, PD), w[1]);
+        }
+        mixed(sy(0, E), w[2]);
+      } else {
+        if constexpr (!RAW) issue_phi(std::integral_constant<int, t + 1>{});
+        sum(E, vE);
+        sum(0, v0);
       }
-      s[PD] = axis_sums<R>(vP);
-      pin<ADV>(s[PD], t >= F0 && t < F2, full);
 #pragma unroll
       for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
-      fn(t, s, dd);
+      fn(t, s, dd, v0[H]);
     });
   }
 }
 
-template <int C, bool AX, int H, int F0, int F1, int F2, bool ADV, int N, class FN>
-__device__ __forceinline__ void run_stencils(const GatherSrc<H>& S, const int (&list)[N], const FN& fn) {
-  constexpr int PD = C == BHAH_SINH_CYLINDRICAL ? 1 : 2, E = 3 - PD, R = H - 1;
-  static_for<N>([&](auto tc) BHAH_INLINE {
-    constexpr int t = decltype(tc)::value;
-    const int g = list[t];
-    double v0[2 * H + 1], vE[2 * H + 1], vP[2 * H + 1];
-#pragma unroll
-    for (int m = -H; m <= H; m++) {
-      v0[H + m] = S.at(g, m, 0, 0);
-      vE[H + m] = m == 0 ? v0[H] : S.at(g, 0, m, 0);
-      if constexpr (!AX) vP[H + m] = m == 0 ? v0[H] : S.at(g, 0, 0, m);
-    }
-    if constexpr (AX) vP[H + 1] = S.at(g, 0, 0, 1);
-    AxisSums s[3];
-    double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (t >= F0 && t < F1) {
-      double x[4 * R * R];  // f at (n, m) along (i0, e)
-#pragma unroll
-      for (int m = -R; m <= R; m++)
-#pragma unroll
-        for (int n = -R; n <= R; n++)
-          if (m != 0 && n != 0) x[2 * R * xo<R>(m) + xo<R>(n)] = S.at(g, n, m, 0);
-      BHAH_PHASE_BARRIER();
-      double e[2 * R + 1];
-      e[R] = 0.0;
-#pragma unroll
-      for (int m = -R; m <= R; m++)
-        if (m != 0) {
-          double r[2 * R + 1];
-          r[R] = 0.0;
-#pragma unroll
-          for (int n = -R; n <= R; n++)
-            if (n != 0) r[R + n] = x[2 * R * xo<R>(m) + xo<R>(n)];
-          e[R + m] = d1_sum<R>(r);
-        }
-      dd[sy(0, E)] = d1_sum<R>(e);
-      pin(dd[sy(0, E)]);
-      if constexpr (!AX) {
-        double a0 = 0.0, aE = 0.0;
-#pragma unroll
-        for (int j = 1; j <= R; j++) {
-          double e0[2], eE[2];
-#pragma unroll
-          for (int side = 0; side < 2; side++) {
-            double r0[2 * R + 1], rE[2 * R + 1];
-            r0[R] = rE[R] = 0.0;
-#pragma unroll
-            for (int n = -R; n <= R; n++)
-              if (n != 0) {
-                r0[R + n] = S.at(g, n, 0, side ? -j : j);
-                rE[R + n] = S.at(g, 0, n, side ? -j : j);
-              }
-            e0[side] = d1_sum<R>(r0);
-            eE[side] = d1_sum<R>(rE);
-          }
-          a0 = acc_pair<R>(j, a0, e0[0], e0[1]);
-          aE = acc_pair<R>(j, aE, eE[0], eE[1]);
-          pin(a0);
-          pin(aE);
-        }
-        dd[sy(0, PD)] = a0;
-        dd[sy(E, PD)] = aE;
-      }
-    }
-    BHAH_PHASE_BARRIER();
-    s[0] = axis_sums<R>(v0);
-    s[E] = axis_sums<R>(vE);
-    if constexpr (AX) s[PD] = axis_sums_two_planes<R>(v0[H], vP[H + 1]);
-    else s[PD] = axis_sums<R>(vP);
-#pragma unroll
-    for (int k = 0; k < 3; k++) dd[sy(k, k)] = s[k].d2;
-    fn(t, s, dd);
-    BHAH_PHASE_BARRIER();
-  });
-}
-
-// the number of a staged tile as the pushed ghosts are grouped (PushDev)
+// the number of a tile as the pushed ghosts are grouped (PushDev)
 template <int C, int H>
 __device__ __forceinline__ int patch_number(const PushDev& P, int t0, int t1, int t2) {
   const int x = (t0 - H) >> TLX;
@@ -628,18 +647,11 @@ struct TilePoint {
   bool live;
 };
 
-template <class SRC, int C, bool AX, int H>
-__device__ __forceinline__ SRC make_source(const double* y, const GridDev& G, const TilePoint& p, int lane,
-                                           double* lds) {
-  constexpr bool cyl = C == BHAH_SINH_CYLINDRICAL;
-  if constexpr (SRC::STG) {
-    SRC S;
-    if (cyl) S.init(y, G, 1, p.t0, p.t2, p.i0, p.i2, p.t1, lane, lds, AX);
-    else S.init(y, G, 2, p.t0, p.t1, p.i0, p.i1, p.t2, lane, lds, AX);
-    return S;
-  } else {
-    return SRC{PtT<H>(y, G, C, p.i0, p.i1, p.i2), cyl ? 1 : 2};
-  }
+template <int C, bool AX, int H>
+__device__ __forceinline__ Source<H, AX> make_source(const double* y, const GridDev& G, const TilePoint& p, int lane,
+                                                     double* lds) {
+  if constexpr (C == BHAH_SINH_CYLINDRICAL) return Source<H, AX>(y, G, 1, p.t0, p.t2, p.t1, lane, lds);
+  else return Source<H, AX>(y, G, 2, p.t0, p.t1, p.t2, lane, lds);
 }
 
 }  // namespace bhah
