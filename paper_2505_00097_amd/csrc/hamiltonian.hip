@@ -80,12 +80,14 @@ __device__ __forceinline__ void constraints_tile(const GridDev& G, const TileMap
     for (int l = k; l < 3; l++) wg[sy(k, l)] = gd[sy(k, l)] * c.sc(k, l);
 
   if (wave == 0) {
-    double L6[6];
+    double L6[6], h[6];
 #pragma unroll
     for (int a = 0; a < 6; a++) L6[a] = 0.0;
     constexpr int list[6] = {G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
     run_stencils<C, AX, H, 0, 6, 6, false>(
-        S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
+        S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6], double c0) BHAH_INLINE {
+          h[a] = c0;
+          pin(h[a]);
 #pragma unroll
           for (int k = 0; k < 3; k++)
             if (!(AX && k == PD)) put(CS::HK + 6 * k + a, c.s1[k] * s[k].d1);
@@ -94,10 +96,9 @@ __device__ __forceinline__ void constraints_tile(const GridDev& G, const TileMap
           pin(L6[a]);
         });
     BHAH_PHASE_BARRIER();
-    double h[6], hk[3][6], D[3][6], Rc[6], DU[3], Del[3][6];
+    double hk[3][6], D[3][6], Rc[6], DU[3], Del[3][6];
 #pragma unroll
     for (int a = 0; a < 6; a++) {
-      h[a] = at(G_HDD00 + a);
 #pragma unroll
       for (int k = 0; k < 3; k++) hk[k][a] = AX && k == PD ? 0.0 : get(CS::HK + 6 * k + a);
     }

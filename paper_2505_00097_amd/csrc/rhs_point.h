@@ -19,7 +19,7 @@
 // xs[v * 64 + l]). One wave per tile and SIMD with the algebra in coordinate
 // components took 19.2 us for a right-hand side on the 128 x 2 x 256 head-on
 // grid, 954 us on a 256 x 128 x 64 one and 2.44 ms there at 8th order with
-// dissipation; this form takes 13.3 us, 685 us and 1.33 ms.
+// dissipation; this form takes 13.2 us, 642 us and 1.30 ms.
 #pragma once
 
 #include "rhs_stencil.h"
@@ -38,6 +38,7 @@ enum {
   X_Y = 45,    // 6  second-derivative terms of alpha and W in Eq. 8
   X_U = 51,    // 3  2 alpha phi_k + alpha_k
   X_A = 54,    // 6  advection (and dissipation) of a_ij
+  X_LATE = 72,   // 8  a_ij, K, alpha: in the gauge wave's stencil stage, after its stencils
   X_PARK = 60,   // the metric wave's park during its stencils, below the gauge wave's stencil stage
   X_SLOTS = 80,
   // results (12 per wave) take slots that neither wave reads any more
@@ -52,7 +53,7 @@ struct Stage : StageSize<AX, H> {
   using StageSize<AX, H>::SL;
   static constexpr int GAUGE = X_SLOTS - SL, LOW = X_V - SL;
   static constexpr int CAP = LOW + GAUGE - X_PARK;  // park slots
-  static_assert(LOW >= 0 && GAUGE >= X_PARK, "stages");
+  static_assert(LOW >= 0 && GAUGE >= X_PARK && GAUGE <= X_LATE, "stages");
   static constexpr int park(int i) { return i < LOW ? SL + i : X_PARK + i - LOW; }
 };
 
@@ -204,7 +205,9 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
   auto at = [&](int g) { return gf_ld(y, G.sgf, g, p.q * 8u, 0); };
   const auto S = make_source<C, AX, H>(y, G, p, lane, xs0);
   using ST = Stage<AX, H>;
-  double gU[6], Pc[6], ck[6], late[24];  // late: what the park cannot take
+  // values at the point itself come from the stencil stage where the wave takes
+  // the gridfunction through it, others are read once (late: what the park cannot take)
+  double gU[6], Pc[6], ck[6], h[6], v[3], late[24];
   auto keep = [&](int i, double x) {
     if (i < ST::CAP) put(ST::park(i), x);
     else late[i] = x;
@@ -214,7 +217,6 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
     Coefs<H> c;
     double w[6], gd[6];
     {
-      double h[6], v[3];
 #pragma unroll
       for (int a = 0; a < 6; a++) h[a] = at(G_HDD00 + a);
 #pragma unroll
@@ -232,7 +234,10 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
     for (int a = 0; a < 6; a++) { Pc[a] = 0.0; ck[a] = 0.0; }
     constexpr int list[6] = {G_HDD00, G_HDD00 + 1, G_HDD00 + 2, G_HDD00 + 3, G_HDD00 + 4, G_HDD00 + 5};
     //   Pc_ij = gammabar^kl h_ij,kl,  ck_kl = gammabar^ab h_ab,kl (unscaled)
-    run_stencils<C, AX, H, 0, 6, 6, true>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
+    run_stencils<C, AX, H, 0, 6, 6, true>(S, list, [&](int a, const AxisSums(&s)[3], const double(&dd)[6],
+                                                       double c0) BHAH_INLINE {
+      h[a] = c0;
+      pin(h[a]);
 #pragma unroll
       for (int k = 0; k < 3; k++)
         if (!(AX && k == PD)) keep(3 * a + k, c.s1[k] * s[k].d1);
@@ -251,27 +256,20 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
       for (int l = k; l < 3; l++) ck[sy(k, l)] *= c.sc(k, l);
   }
   BHAH_PHASE_BARRIER();
-  double h[6], v[3], adv[6], hk[3][6];
+  double adv[6], hk[3][6];
 #pragma unroll
   for (int a = 0; a < 6; a++) {
-    h[a] = at(G_HDD00 + a);
     adv[a] = kept(18 + a);
 #pragma unroll
     for (int k = 0; k < 3; k++) hk[k][a] = AX && k == PD ? 0.0 : kept(3 * a + k);
   }
-#pragma unroll
-  for (int i = 0; i < 3; i++) v[i] = at(G_VETU0 + i);
   const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
   // for the last phase: fetched there, they would wait behind the loads and
-  // stores of the other waves' epilogues (that phase took 6900 cycles, 14600
-  // in a Runge-Kutta stage, of 30000 and 47000; the gauge wave's, no shorter,
-  // 1700)
-  double a6[6], lam[3];
-#pragma unroll
-  for (int c = 0; c < 6; c++) a6[c] = at(G_ADD00 + c);
+  // stores of the other waves' epilogues
+  double lam[3];
 #pragma unroll
   for (int i = 0; i < 3; i++) lam[i] = at(G_LAMU0 + i);
-  const double alpha = at(G_ALPHA), W = at(G_CF), K = at(G_TRK);
+  const double W = at(G_CF);
   BHAH_PHASE_BARRIER();
   // psi = 1/2 ln det(gammabar/gammahat): psi_m = 1/2 gammabar^ab h_ab,m and
   // v^m psi_km = 1/2 (v^m gammabar^ab h_ab,km - (gammabar^-1 v^m h_m gammabar^-1)^ab h_ab,k)
@@ -362,6 +360,10 @@ __device__ __forceinline__ void metric_wave(const GridDev& G, const Gauge& ga, c
       aux[(6 + k) * G.sgf + p.q] = v[k] * F.iS[k] * dl[k] + get(X_Q + k) / F.iS[k];
   }
   BHAH_PHASE_BARRIER();
+  double a6[6];
+#pragma unroll
+  for (int c = 0; c < 6; c++) a6[c] = get(X_LATE + c);
+  const double K = get(X_LATE + 6), alpha = get(X_LATE + 7);
   double X[6], L[3][3], Dv[3][3], div = 0.0;
 #pragma unroll
   for (int c = 0; c < 6; c++) X[c] = fma(alpha, Rc[c], get(X_Y + c));
@@ -433,6 +435,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
   const auto S = make_source<C, AX, H>(y, G, p, lane, xs0 + Stage<AX, H>::GAUGE * 64);
   double gU[6], Y[6], Za = 0.0, Bv[3], Bd[3], ak[3], phi[3], Kk[3];
   double advW = 0.0, advAl = 0.0, advK = 0.0, advV[3], advL[3], advB[3], koL[3];
+  double v[3], lam[3], bet[3], a6[6], K = 0.0;  // values at the point, from the stencil stage
 #pragma unroll
   for (int i = 0; i < 3; i++) { Bv[i] = 0.0; Bd[i] = 0.0; koL[i] = 0.0; }
   const double alpha = at(G_ALPHA), W = at(G_CF);
@@ -440,7 +443,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
     Coefs<H> c;
     double w[6];
     {
-      double h[6], v[3];
+      double h[6];
 #pragma unroll
       for (int a = 0; a < 6; a++) h[a] = at(G_HDD00 + a);
 #pragma unroll
@@ -455,20 +458,26 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
 #pragma unroll
       for (int l = k; l < 3; l++) w[sy(k, l)] *= c.sc(k, l);
     const double iW = 1.0 / W, aW = alpha * iW;
-    // the gridfunctions with second derivatives come while few results wait in registers
-    constexpr int list[18] = {0, 1, 2, 3, 4, 5, G_VETU0, G_VETU0 + 1, G_VETU0 + 2, G_CF, G_ALPHA,
-                              G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2, G_TRK, G_BETU0, G_BETU0 + 1, G_BETU0 + 2};
-    run_stencils<C, AX, H, 6, 11, 15, true>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6], double) BHAH_INLINE {
-      const bool gauge = (t >= 6 && t < 9) || t == 10 || t >= 15;
+    // the gridfunctions with second derivatives come while few results wait in
+    // registers, those whose values wait as well last
+    constexpr int list[18] = {G_VETU0, G_VETU0 + 1, G_VETU0 + 2, G_CF, G_ALPHA, G_LAMU0, G_LAMU0 + 1, G_LAMU0 + 2,
+                              G_TRK, G_BETU0, G_BETU0 + 1, G_BETU0 + 2, 0, 1, 2, 3, 4, 5};
+    run_stencils<C, AX, H, 0, 5, 9, true>(S, list, [&](int t, const AxisSums(&s)[3], const double(&dd)[6],
+                                                       double c0) BHAH_INLINE {
+      const bool gauge = t < 3 || t == 4 || (t >= 9 && t < 12);
       const double adv = gauge ? advect<H>(s, c.ch, c.qg) : advect<H>(s, c.ch, c.q);
       double d[3];
 #pragma unroll
       for (int k = 0; k < 3; k++) d[k] = AX && k == PD ? 0.0 : c.s1[k] * s[k].d1;
-      if (t < 6) {  // a_ij
-        put(X_A + t, adv);
-      } else if (t < 9) {  // vet^i
-        const int i = t - 6;
+      if (t >= 12) {  // a_ij
+        put(X_A + t - 12, adv);
+        a6[t - 12] = c0;
+        pin(a6[t - 12]);
+      } else if (t < 3) {  // vet^i
+        const int i = t;
         advV[i] = adv;
+        v[i] = c0;
+        pin(v[i]);
 #pragma unroll
         for (int k = 0; k < 3; k++)
           if (!(AX && k == PD)) put(X_V + 3 * k + i, d[k]);
@@ -480,7 +489,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
         pin(advV[i]);
         pin(Bd[0]);
         pin(Bd[3 - PD]);
-      } else if (t == 9) {  // W
+      } else if (t == 3) {  // W
         advW = adv;
 #pragma unroll
         for (int k = 0; k < 3; k++) phi[k] = (-0.5 * iW) * d[k];
@@ -490,7 +499,7 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
           if (!zero_pair<AX, PD>(kl)) pin(Y[kl]);
         }
         pin(advW);
-      } else if (t == 10) {  // alpha
+      } else if (t == 4) {  // alpha
         advAl = adv;
 #pragma unroll
         for (int k = 0; k < 3; k++) {
@@ -505,9 +514,11 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
         }
         pin(Za);
         pin(advAl);
-      } else if (t < 14) {  // lambda^i
-        const int i = t - 11;
+      } else if (t < 8) {  // lambda^i
+        const int i = t - 5;
         advL[i] = adv;
+        lam[i] = c0;
+        pin(lam[i]);
 #pragma unroll
         for (int k = 0; k < 3; k++)
           if (!(AX && k == PD)) put(X_L + 3 * k + i, d[k]);
@@ -519,26 +530,26 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
           pin(koL[i]);
         }
         pin(advL[i]);
-      } else if (t == 14) {  // K
+      } else if (t == 8) {  // K
         advK = adv;
+        K = c0;
+        pin(K);
 #pragma unroll
         for (int k = 0; k < 3; k++) Kk[k] = d[k];
         pin(advK);
       } else {  // B^i
-        advB[t - 15] = adv;
-        pin(advB[t - 15]);
+        advB[t - 9] = adv;
+        pin(advB[t - 9]);
+        bet[t - 9] = c0;
+        pin(bet[t - 9]);
       }
     });
   }
   BHAH_PHASE_BARRIER();
-  double v[3], lam[3], bet[3];
 #pragma unroll
-  for (int i = 0; i < 3; i++) {
-    v[i] = at(G_VETU0 + i);
-    lam[i] = at(G_LAMU0 + i);
-    bet[i] = at(G_BETU0 + i);
-  }
-  const double K = at(G_TRK);
+  for (int c = 0; c < 6; c++) put(X_LATE + c, a6[c]);
+  put(X_LATE + 6, K);
+  put(X_LATE + 7, alpha);
   const Frame F = load_frame<C>(G, p.i0, p.i1, p.i2);
   BHAH_PHASE_BARRIER();
   {
@@ -557,9 +568,6 @@ __device__ __forceinline__ void gauge_wave(const GridDev& G, const Gauge& ga, co
 #pragma unroll
       for (int j = i; j < 3; j++) put(X_Y + sy(i, j), fma(2.0, fma(ak[i], phi[j], ak[j] * phi[i]), Y[sy(i, j)]));
   }
-  double a6[6];
-#pragma unroll
-  for (int c = 0; c < 6; c++) a6[c] = at(G_ADD00 + c);
   // gammabar^jk Dhat_j Dhat_k beta^i
   double vk[3][3], Dv[3][3];
 #pragma unroll
