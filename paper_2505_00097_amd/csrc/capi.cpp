@@ -113,6 +113,7 @@ static hipError_t upload_ghosts(const std::vector<int>& dst, const std::vector<i
 // stage's other ghosts.
 static hipError_t upload_push(bhah_grid* g) {
   const HostPush& P = g->push;
+  if (P.start.empty()) return hipSuccess;
   // records first: they are read as 16-byte words
   std::vector<int> packed(P.rec);
   packed.insert(packed.end(), P.terms.begin(), P.terms.end());

@@ -118,21 +118,23 @@ HostPush build_push(const bhah_grid* g, const std::vector<int>& dst, const std::
   P.nx = (c.N[0] + PATCH_X - 1) / PATCH_X;
   P.ne = (c.N[ed] + PATCH_E - 1) / PATCH_E;
   // patch and lane of an interior point (patch -1 for any other)
-  auto place = [&](int q, int& lane) {
-    const int i[3] = {q % c.n[0] - c.ng, (q / c.n[0]) % c.n[1] - c.ng, q / (c.n[0] * c.n[1]) - c.ng};
+  auto place = [&](int q, unsigned char& lane) {
+    const int row = q / c.n[0], plane = row / c.n[1];
+    const unsigned i[3] = {(unsigned)(q - row * c.n[0] - c.ng), (unsigned)(row - plane * c.n[1] - c.ng),
+                           (unsigned)(plane - c.ng)};
     for (int d = 0; d < 3; d++)
-      if (i[d] < 0 || i[d] >= c.N[d]) return -1;
-    lane = i[0] % PATCH_X + PATCH_X * (i[ed] % PATCH_E);
-    return (i[pd] * P.ne + i[ed] / PATCH_E) * P.nx + i[0] / PATCH_X;
+      if (i[d] >= (unsigned)c.N[d]) return -1;
+    lane = (unsigned char)(i[0] % PATCH_X + PATCH_X * (i[ed] % PATCH_E));
+    return (int)((i[pd] * P.ne + i[ed] / PATCH_E) * P.nx + i[0] / PATCH_X);
   };
   const size_t n = dst.size();
   std::vector<int> patch(n);
+  std::vector<unsigned char> lanes(src.size());  // of the sources of pushed ghosts
   P.start.assign((size_t)P.nx * P.ne * c.N[pd] + 1, 0);
   for (size_t t = 0; t < n; t++) {
-    int lane;
-    patch[t] = place(src[start[t]], lane);
+    patch[t] = place(src[start[t]], lanes[start[t]]);
     for (int k = start[t] + 1; k < start[t + 1] && patch[t] >= 0; k++)
-      if (place(src[k], lane) != patch[t]) patch[t] = -1;
+      if (place(src[k], lanes[k]) != patch[t]) patch[t] = -1;
     if (patch[t] >= 0) {
       P.start[patch[t] + 1]++;
     } else {
@@ -159,18 +161,14 @@ HostPush build_push(const bhah_grid* g, const std::vector<int>& dst, const std::
     if (small) {
       r[1] = par[t] | m << 3;
       for (int k = 0; k < m; k++) {
-        int lane = 0;
-        place(src[start[t] + k], lane);
-        r[2] |= lane << (6 * k);
+        r[2] |= lanes[start[t] + k] << (6 * k);
         r[3] |= ((int)w[start[t] + k] & 0xff) << (8 * k);
       }
     } else {
       r[1] = par[t] | 32 | m << 8;
       r[2] = (int)(P.terms.size() / 2);
       for (int k = start[t]; k < start[t + 1]; k++) {
-        int lane = 0;
-        place(src[k], lane);
-        P.terms.push_back(lane);
+        P.terms.push_back(lanes[k]);
         P.terms.push_back((int)w[k]);
       }
     }
@@ -440,7 +438,8 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
     for (HostGhosts* L : {&g->inner_full, &g->inner_stage}) L->start.push_back((int)L->src.size());
   }
 
-  // ---- stage ghosts written by the right-hand-side kernel ------------------
+  // ---- stage ghosts written by the right-hand-side kernel, where it does (rhs_pushes)
+  if (p->N[dphi] != 2 && ng != NG) return BHAH_OK;
   if (p->bc_kind != BHAH_BC_RADIATION) {
     g->push = build_push(g, g->r_dst, g->r_start, g->r_par, g->r_src, g->r_w);
     return BHAH_OK;
@@ -450,6 +449,7 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
   // what is left copies outer points: grouped by its source for the radiation kernel
   HostGhosts& left = g->push.left;
   std::unordered_map<int, int> outer;
+  outer.reserve(g->rad_q.size());
   for (size_t t = 0; t < g->rad_q.size(); t++) outer[g->rad_q[t]] = (int)t;
   std::vector<int>& cs = g->rad_copy_start;
   cs.assign(g->rad_q.size() + 1, 0);
