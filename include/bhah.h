@@ -378,8 +378,9 @@ int bhah_batch_set_integrator(bhah_batch* b, int integrator);
 /* Launch shape of the right-hand-side kernel: blocks_per_cu > 0 runs that
  * many persistent two-wave blocks per compute unit striding over the work
  * list (default 4: two waves per SIMD); 0 launches one block per tile, as do
- * lists of more than about 8 tiles per block whatever the setting (results
- * do not depend on it).                                                     */
+ * lists of more than 8 tiles per block whatever the setting (results do not
+ * depend on it). What counts is the current job set's list of each kernel
+ * variant, not what the batch held before.                                  */
 int bhah_batch_set_blocks_per_cu(bhah_batch* b, int blocks_per_cu);
 
 typedef struct {
@@ -387,7 +388,7 @@ typedef struct {
   int n_tiles;           /* (job, tile) entries, 64 points each              */
   int n_chunks;          /* (job, 256 ghost points) entries                  */
   int graph_steps;       /* RK4 steps per captured graph                     */
-  int rhs_blocks;        /* blocks of the right-hand-side kernel             */
+  int rhs_blocks;        /* blocks of the largest right-hand-side launch     */
   int n_classes_tuned;   /* size classes with a tile choice                  */
   double tune_seconds;   /* wall time spent timing tile candidates           */
   int blocks_per_cu;     /* persistent RHS blocks per CU (0: one per tile)   */

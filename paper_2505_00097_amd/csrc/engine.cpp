@@ -88,19 +88,42 @@ int Engine::set_jobs(const std::vector<EngineJob>& jobs) {
   return BHAH_OK;
 }
 
-// Blocks of the right-hand-side kernel: blocks_per_cu_ per compute unit
-// (blocks of two waves, two waves per SIMD, so 4 fill a CU) striding over the work
-// list, or with blocks_per_cu_ == 0 one block per tile of the current
-// capacity; always a multiple of the XCD count. A list of more than 8 tiles
-// per block (the capacity is 1.5 times the list) runs one block per tile as
+Engine::ListSizes Engine::list_sizes() const {
+  ListSizes n;
+  for (int j = 0; j < (int)jobs_.size(); j++) {
+    const GridDev& G = jobs_[j].g->dev;
+    n.tiles[rhs_variant(G.coord, G.N1, G.N2, G.ng)] += make_tilemap(G, 1).ntiles;
+    n.rad += lists_of(j).rad.n;
+  }
+  return n;
+}
+
+// Blocks of the right-hand-side kernel for one variant whose jobs have `list`
+// tiles, to run `tiles` of them: blocks_per_cu_ per compute unit (blocks of two
+// waves, two waves per SIMD, so 4 fill a CU) striding over the work list, or
+// with blocks_per_cu_ == 0 one block per tile; always a multiple of the XCD
+// count. A list of more than 8 tiles per block runs one block per tile as
 // well: blocks that stride drift apart, and the planes that their tiles share
 // leave the L2s. One 1008 x 168 x 336 job: 171 ms a step striding, 105 with
 // one block per tile; 256 x 128 x 64 (32 tiles per block) 3.56, 3.25; 16
 // head-on jobs (13) 1.154, 1.135; four 96 x 32 x 32 jobs (6) 0.651, 0.686.
-int Engine::rhs_grid() const {
+// One block per tile is rounded up in steps of 1/64 to 1/32 of the tiles, so
+// that job sets of nearly one size share a captured graph.
+int Engine::rhs_grid(long long list, long long tiles) const {
+  if (tiles <= 0) return 0;
   const long long stride = (long long)blocks_per_cu_ * n_cus_;
-  const long long want = stride > 0 && cap_tiles_ <= 12 * stride ? stride : (long long)cap_tiles_;
-  return (int)std::max<long long>(BHAH_NXCD, (want + BHAH_NXCD - 1) / BHAH_NXCD * BHAH_NXCD);
+  if (stride > 0 && list <= 8 * stride) return (int)((stride + BHAH_NXCD - 1) / BHAH_NXCD * BHAH_NXCD);
+  long long step = BHAH_NXCD;
+  while (64 * step <= tiles) step *= 2;
+  return (int)((tiles + step - 1) / step * step);
+}
+
+Engine::LaunchShape Engine::launch_shape() const {
+  const ListSizes n = list_sizes();
+  LaunchShape l{};
+  for (int v = 0; v < NVAR; v++) l[v] = rhs_grid(n.tiles[v], n.tiles[v]);
+  l[NVAR] = n.rad > 0 ? 1 : 0;
+  return l;
 }
 
 int Engine::ensure_device(hipStream_t s) {
@@ -129,7 +152,6 @@ int Engine::ensure_device(hipStream_t s) {
 void Engine::drop_graphs() {
   for (auto& kv : graphs_) (void)hipGraphExecDestroy(kv.second);
   graphs_.clear();
-  for (int f = 0; f <= NVAR; f++) fam_in_graphs_[f] = false;
 }
 
 // Fill the host blob: header, job table (all jobs) and work lists of the
@@ -216,7 +238,6 @@ void Engine::build_blob(const std::vector<TileCfg>& cfg, const std::vector<int>&
         for (int t = 0; t < maps[j].ntiles; t++) tiles[pos++] = int2{j, t};
       }
     hdr->n_tiles[f] = pos - hdr->tile_off[f];
-    fam_present_[f] = hdr->n_tiles[f] > 0 || fam_present_[f];
   }
   int cpos = 0;
   for (int w = 0; w < 3; w++) {
@@ -229,7 +250,6 @@ void Engine::build_blob(const std::vector<TileCfg>& cfg, const std::vector<int>&
     }
     hdr->n_chunks[w] = cpos - hdr->chunk_off[w];
   }
-  fam_present_[NVAR] = hdr->n_chunks[2] > 0 || fam_present_[NVAR];
   n_tiles_ = pos;
   n_chunks_ = cpos;
   blob_bytes_ = (size_t)(L.chunks + sizeof(int2) * (size_t)cpos);
@@ -282,23 +302,25 @@ int Engine::time_class(const SizeClass& c, const TileCfg& cfg, hipStream_t s, do
   const BatchHdr* dh = (const BatchHdr*)d_blob_;
   const int2* dt = (const int2*)(d_blob_ + L.tiles);
   // the kernel variants of the class's jobs (4th- and 8th-order grids of one
-  // shape share the class)
-  bool used[NVAR] = {};
+  // shape share the class), launched in the form that the whole job set gets
+  const ListSizes all = list_sizes();
+  long long own[NVAR] = {};
   for (int j : only) {
     const GridDev& G = jobs_[j].g->dev;
-    used[rhs_variant(G.coord, G.N1, G.N2, G.ng)] = true;
+    own[rhs_variant(G.coord, G.N1, G.N2, G.ng)] += (long long)repeat * make_tilemap(G, cfg.band).ntiles;
   }
+  int blocks[NVAR];
+  for (int v = 0; v < NVAR; v++) blocks[v] = rhs_grid(all.tiles[v], own[v]);
   hipEvent_t e0, e1;
   if ((rc = check_hip(hipEventCreate(&e0), "hipEventCreate"))) return rc;
   if ((rc = check_hip(hipEventCreate(&e1), "hipEventCreate"))) { (void)hipEventDestroy(e0); return rc; }
   const int reps = 3;
-  const int blocks = rhs_grid();
   for (int v = 0; v < NVAR; v++)
-    if (used[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), blocks, s);
+    if (blocks[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), blocks[v], s);
   (void)hipEventRecord(e0, s);
   for (int r = 0; r < reps; r++)
     for (int v = 0; v < NVAR; v++)
-      if (used[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), blocks, s);
+      if (blocks[v]) launch_rhs_batch(v, dj, dh, dt, 4, nullptr, 0, gauge_of(gp_), blocks[v], s);
   (void)hipEventRecord(e1, s);
   rc = check_hip(hipEventSynchronize(e1), "tile timing");
   float ms = 0.f;
@@ -336,15 +358,13 @@ int Engine::tune_missing(hipStream_t s) {
   return BHAH_OK;
 }
 
-int Engine::capture(int nsteps, hipStream_t s, hipGraphExec_t* out) {
-  (void)s;
+int Engine::capture(int nsteps, const LaunchShape& shape, hipGraphExec_t* out) {
   const Layout L = layout(cap_jobs_, cap_tiles_, cap_chunks_);
   const BatchJob* dj = (const BatchJob*)(d_blob_ + L.jobs);
   const BatchHdr* dh = (const BatchHdr*)d_blob_;
   const int2* dt = (const int2*)(d_blob_ + L.tiles);
   const int2* dc = (const int2*)(d_blob_ + L.chunks);
   const int* dn = (const int*)(d_blob_ + L.counts);
-  rhs_blocks_ = rhs_grid();
   int rc = check_hip(hipStreamBeginCapture(cap_stream_, hipStreamCaptureModeThreadLocal), "graph capture");
   if (rc) return rc;
   // Step k of the graph runs the jobs with more than k active steps in this
@@ -356,10 +376,9 @@ int Engine::capture(int nsteps, hipStream_t s, hipGraphExec_t* out) {
   for (int k = 0; k < nsteps; k++)
     for (int stage = 0; stage < nst; stage++) {
       for (int f = 0; f < NVAR; f++)
-        if (fam_present_[f])
-          launch_rhs_batch(f, dj, dh, dt, stage, dn, k, gauge_of(gp_), rhs_blocks_, cap_stream_);
+        if (shape[f]) launch_rhs_batch(f, dj, dh, dt, stage, dn, k, gauge_of(gp_), shape[f], cap_stream_);
       // outer points of radiation-boundary jobs, before their inner ghosts are copied
-      if (fam_present_[NVAR]) launch_radiation_batch(dj, dh, dc, stage, dn, k, ghost_blocks_, cap_stream_);
+      if (shape[NVAR]) launch_radiation_batch(dj, dh, dc, stage, dn, k, ghost_blocks_, cap_stream_);
       launch_ghosts_batch(dj, dh, dc, stage, dn, k, stage == nst - 1, ghost_blocks_, cap_stream_);
     }
   hipGraph_t graph = nullptr;
@@ -372,8 +391,27 @@ int Engine::capture(int nsteps, hipStream_t s, hipGraphExec_t* out) {
   }
   rc = check_hip(hipGraphInstantiate(out, graph, nullptr, nullptr, 0), "hipGraphInstantiate");
   (void)hipGraphDestroy(graph);
-  for (int f = 0; f <= NVAR; f++) fam_in_graphs_[f] = fam_present_[f];
   return rc;
+}
+
+// the graph of nsteps steps of the current job set, captured if no kept one
+// launches the same kernels
+int Engine::graph_for(int nsteps, hipStream_t s, hipGraphExec_t* out) {
+  const LaunchShape shape = launch_shape();
+  rhs_blocks_ = *std::max_element(shape.begin(), shape.begin() + NVAR);
+  const GraphKey key{nsteps, integrator_, shape};
+  const auto it = graphs_.find(key);
+  if (it != graphs_.end()) {
+    *out = it->second;
+    return BHAH_OK;
+  }
+  if (graphs_.size() >= kMaxGraphs) {
+    if (int rc = check_hip(hipStreamSynchronize(s), "batch graphs")) return rc;  // none of them still runs
+    drop_graphs();
+  }
+  if (int rc = capture(nsteps, shape, out)) return rc;
+  graphs_.emplace(key, *out);
+  return BHAH_OK;
 }
 
 int Engine::step(int nsteps, hipStream_t s) {
@@ -390,8 +428,6 @@ int Engine::step(int nsteps, hipStream_t s) {
     dirty_ = false;
   }
   if (tune_launch_ && (rc = tune_launch(s))) return rc;
-  for (int f = 0; f <= NVAR; f++)
-    if (fam_present_[f] && !fam_in_graphs_[f]) drop_graphs();
   // jobs that take fewer steps than the call idle through the rest: launch
   // graphs only while some job still has steps to take
   long long most = 0;
@@ -399,14 +435,10 @@ int Engine::step(int nsteps, hipStream_t s) {
   long long first = 0;
   while (first < most) {
     const int k = (int)std::min<long long>(most - first, graph_steps_);
-    auto it = graphs_.find(k);
-    if (it == graphs_.end()) {
-      hipGraphExec_t ex = nullptr;
-      if ((rc = capture(k, s, &ex))) return rc;
-      it = graphs_.emplace(k, ex).first;
-    }
+    hipGraphExec_t ex = nullptr;
+    if ((rc = graph_for(k, s, &ex))) return rc;
     if ((rc = upload_counts(first, k, s))) return rc;
-    if ((rc = check_hip(hipGraphLaunch(it->second, s), "hipGraphLaunch"))) return rc;
+    if ((rc = check_hip(hipGraphLaunch(ex, s), "hipGraphLaunch"))) return rc;
     first += k;
   }
   return BHAH_OK;
@@ -436,7 +468,6 @@ int Engine::tune_launch(hipStream_t s) {
     if (hit->second.first != graph_steps_ || hit->second.second != blocks_per_cu_) {
       set_graph_steps(hit->second.first);
       set_blocks_per_cu(hit->second.second);
-      drop_graphs();
     }
     last_tune_.graph_steps = graph_steps_;
     last_tune_.blocks_per_cu = blocks_per_cu_;
@@ -482,10 +513,8 @@ int Engine::tune_launch(hipStream_t s) {
     for (int b = 0; b < 4 && !rc; b++) {
       set_graph_steps(steps_c[a]);
       set_blocks_per_cu(bpc_c[b]);
-      drop_graphs();
       hipGraphExec_t ex = nullptr;
-      if ((rc = capture(graph_steps_, s, &ex))) break;
-      graphs_.emplace(graph_steps_, ex);
+      if ((rc = graph_for(graph_steps_, s, &ex))) break;
       if ((rc = upload_counts(0, graph_steps_, s))) break;
       (void)hipGraphLaunch(ex, s);  // warm-up
       (void)hipEventRecord(e0, s);

@@ -2,14 +2,16 @@
 //
 // The engine owns a device work description (job table + per-variant (job,
 // tile) lists + (job, ghost chunk) list, uploaded as one blob) and a cache of
-// instantiated hipGraphs, one per step count, each replaying
+// instantiated hipGraphs, one per step count and launch, each replaying
 // steps x 4 stages x [batched RHS kernel per kernel variant, batched ghost
 // kernel]. The graphs read the blob at run time, so a changed job set only
-// needs a new upload, not a new graph. Tile shapes are chosen per size class
+// needs a new upload, and another graph where its lists take another launch
+// (blocks per kernel variant). Tile shapes are chosen per size class
 // (coordinate family + interior extents) by timing candidates on the jobs
 // themselves; choices persist in a small JSON cache file.
 #pragma once
 
+#include <array>
 #include <initializer_list>
 #include <map>
 #include <string>
@@ -56,17 +58,13 @@ class Engine {
   void set_graph_steps(int S) { graph_steps_ = S < 1 ? 1 : S; }
   // BHAH_RK4 or BHAH_SSPRK3 (the stage arguments and graphs are rebuilt)
   void set_integrator(int k) {
-    if (k != integrator_) {
-      drop_graphs();
-      dirty_ = true;
-    }
+    if (k != integrator_) dirty_ = true;
     integrator_ = k;
   }
   int integrator() const { return integrator_; }
   // persistent blocks of the right-hand-side kernel per compute unit;
   // 0 launches one block per tile instead
   void set_blocks_per_cu(int n) {
-    if (n != blocks_per_cu_) drop_graphs();
     blocks_per_cu_ = n < 0 ? 0 : n;
     rhs_blocks_ = 0;
   }
@@ -98,6 +96,10 @@ class Engine {
   TileCfg tile_of_class(const SizeClass& c) const;
 
  private:
+  // the kernels a graph launches per stage: blocks of the right-hand-side
+  // kernel per variant (0: not launched); entry NVAR: 1 with radiation points
+  using LaunchShape = std::array<int, NVAR + 1>;
+
   int ensure_device(hipStream_t s);
   int tune_missing(hipStream_t s);
   int time_class(const SizeClass& c, const TileCfg& cfg, hipStream_t s, double* us);
@@ -108,7 +110,7 @@ class Engine {
   // per-job active step counts of one graph launch covering steps
   // [first, first + k) of a step() call, copied to the device blob
   int upload_counts(long long first, int k, hipStream_t s);
-  int capture(int nsteps, hipStream_t s, hipGraphExec_t* out);
+  int capture(int nsteps, const LaunchShape& shape, hipGraphExec_t* out);
   void drop_graphs();
   void load_cache();
   void save_cache();
@@ -140,9 +142,15 @@ class Engine {
   hipEvent_t counts_done_[kRing] = {};
   int counts_slot_ = 0;
   int n_tiles_ = 0, n_chunks_ = 0;
-  // kernel variants with tiles in some blob (entry NVAR: radiation points)
-  bool fam_present_[NVAR + 1] = {};
-  bool fam_in_graphs_[NVAR + 1] = {};  // ... and in the captured graphs
+  // tiles per kernel variant of the whole job set (they do not depend on the
+  // band), and its radiation points
+  struct ListSizes {
+    long long tiles[NVAR] = {};
+    long long rad = 0;
+  };
+  ListSizes list_sizes() const;
+  int rhs_grid(long long list, long long tiles) const;
+  LaunchShape launch_shape() const;
   // the ghost lists refilled after a stage (gh[0]: ghosts with an interior
   // phi index, gh[1]: all) and the radiation points of job j: a
   // radiation-boundary grid refills only its inner ghosts (one-hop copies)
@@ -160,10 +168,14 @@ class Engine {
   int rhs_blocks_ = 0, ghost_blocks_ = 0;
   int blocks_per_cu_ = 4;
   int n_cus_ = 0;
-  int rhs_grid() const;
   int graph_steps_ = 10;
   int integrator_ = BHAH_RK4;
-  std::map<int, hipGraphExec_t> graphs_;
+  // captured graphs by (steps, integrator, launch), so that a job set that
+  // comes and goes finds its graph again; at most kMaxGraphs are kept
+  using GraphKey = std::tuple<int, int, LaunchShape>;
+  static constexpr size_t kMaxGraphs = 128;
+  std::map<GraphKey, hipGraphExec_t> graphs_;
+  int graph_for(int nsteps, hipStream_t s, hipGraphExec_t* out);
   hipStream_t cap_stream_ = nullptr;
 };
 
