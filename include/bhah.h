@@ -404,12 +404,14 @@ int bhah_batch_get_info(const bhah_batch* b, bhah_batch_info* info);
 
 /* Launch tuning (off by default): with on != 0, the first bhah_batch_step
  * on a job set not seen before times every pair of graph steps {4, 10, 25}
- * and persistent blocks per CU {2, 4, 8, one per tile} on device copies of
- * the jobs' states (the caller's states are untouched; the results are the
- * same bit for bit whatever the pair), keeps the fastest (the default
- * (10, 4) unless another is more than 2% faster) and stores it per job-set
- * signature (the multiset of grid shapes, numerics and the integrator) in
- * the tile cache file. The copies need one state per job of device memory
+ * and persistent blocks per CU {2, 4, 8, one per tile} (each launch that
+ * several pairs come to once) on device copies of the jobs' states (the
+ * caller's states are untouched; the results are the same bit for bit
+ * whatever the pair), keeps the fastest (the default (10, 4) unless another
+ * is more than 2% faster) and stores it per job-set signature (the multiset
+ * of grid shapes, numerics and the integrator) in the tile cache file, with
+ * its blocks: a stored choice that comes to another launch is timed again.
+ * The copies need one state per job of device memory
  * for the duration of the tuning (BHAH_ENOMEM otherwise).                   */
 int bhah_batch_set_launch_tuning(bhah_batch* b, int on);
 

@@ -398,7 +398,7 @@ int Engine::capture(int nsteps, const LaunchShape& shape, hipGraphExec_t* out) {
 // launches the same kernels
 int Engine::graph_for(int nsteps, hipStream_t s, hipGraphExec_t* out) {
   const LaunchShape shape = launch_shape();
-  rhs_blocks_ = *std::max_element(shape.begin(), shape.begin() + NVAR);
+  rhs_blocks_ = most_blocks(shape);
   const GraphKey key{nsteps, integrator_, shape};
   const auto it = graphs_.find(key);
   if (it != graphs_.end()) {
@@ -463,18 +463,26 @@ std::string Engine::launch_signature() const {
 
 int Engine::tune_launch(hipStream_t s) {
   const std::string sig = launch_signature();
-  auto hit = launch_cache_.find(sig);
+  const auto hit = launch_cache_.find(sig);
   if (hit != launch_cache_.end()) {
-    if (hit->second.first != graph_steps_ || hit->second.second != blocks_per_cu_) {
-      set_graph_steps(hit->second.first);
-      set_blocks_per_cu(hit->second.second);
+    // a choice stands for the launch that was timed: where its blocks per CU
+    // come to another one here, the job set is timed again
+    const LaunchChoice& c = hit->second;
+    const int bpc = blocks_per_cu_;
+    blocks_per_cu_ = c.blocks_per_cu;
+    const bool same = c.blocks == 0 || c.blocks == most_blocks(launch_shape());
+    blocks_per_cu_ = bpc;
+    if (same) {
+      if (c.graph_steps != graph_steps_ || c.blocks_per_cu != blocks_per_cu_) {
+        set_graph_steps(c.graph_steps);
+        set_blocks_per_cu(c.blocks_per_cu);
+      }
+      last_tune_.graph_steps = graph_steps_;
+      last_tune_.blocks_per_cu = blocks_per_cu_;
+      last_tune_.from_cache = true;
+      last_tune_.us_per_step = c.us;
+      return BHAH_OK;
     }
-    last_tune_.graph_steps = graph_steps_;
-    last_tune_.blocks_per_cu = blocks_per_cu_;
-    last_tune_.from_cache = true;
-    auto u = launch_us_.find(sig);
-    last_tune_.us_per_step = u == launch_us_.end() ? 0.0 : u->second;
-    return BHAH_OK;
   }
   const double t0 = now_s();
   // copies of the states: the candidates run real steps
@@ -505,14 +513,17 @@ int Engine::tune_launch(hipStream_t s) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (!rc) rc = check_hip(hipEventCreate(&e0), "hipEventCreate");
   if (!rc) rc = check_hip(hipEventCreate(&e1), "hipEventCreate");
-  const int steps_c[3] = {4, 10, 25}, bpc_c[4] = {2, 4, 8, 0};
+  // lists of more than 8 tiles per block come to one launch whatever the
+  // blocks per CU: each launch is timed once, under the first of its names
+  const int steps_c[3] = {4, 10, 25}, bpc_c[4] = {4, 2, 8, 0};
   int best_s = 10, best_b = 4;
   double best = 1e300, def = 0.0;
-  int n_cand = 0;
+  std::set<std::pair<int, LaunchShape>> timed;
   for (int a = 0; a < 3 && !rc; a++)
     for (int b = 0; b < 4 && !rc; b++) {
       set_graph_steps(steps_c[a]);
       set_blocks_per_cu(bpc_c[b]);
+      if (!timed.insert({graph_steps_, launch_shape()}).second) continue;
       hipGraphExec_t ex = nullptr;
       if ((rc = graph_for(graph_steps_, s, &ex))) break;
       if ((rc = upload_counts(0, graph_steps_, s))) break;
@@ -524,7 +535,6 @@ int Engine::tune_launch(hipStream_t s) {
       float ms = 0.f;
       (void)hipEventElapsedTime(&ms, e0, e1);
       const double us = 1e3 * ms / (2.0 * graph_steps_);
-      n_cand++;
       if (steps_c[a] == 10 && bpc_c[b] == 4) def = us;
       if (us < best) {
         best = us;
@@ -551,9 +561,8 @@ int Engine::tune_launch(hipStream_t s) {
   build_blob(cfg, {});
   if ((rc = upload(s))) return rc;
   dirty_ = false;
-  launch_cache_[sig] = {best_s, best_b};
-  launch_us_[sig] = best;
-  last_tune_ = LaunchTune{best_s, best_b, best, def, now_s() - t0, n_cand, false};
+  launch_cache_[sig] = LaunchChoice{best_s, best_b, most_blocks(launch_shape()), best};
+  last_tune_ = LaunchTune{best_s, best_b, best, def, now_s() - t0, (int)timed.size(), false};
   save_cache();
   return BHAH_OK;
 }
@@ -572,13 +581,12 @@ void Engine::load_cache() {
     if (!p) continue;
     {  // a launch-configuration entry
       char sig[96];
-      int S, bpc;
-      if (std::sscanf(p, "{\"arch\": \"%63[^\"]\", \"launch\": \"%95[^\"]\", \"S\": %d, \"bpc\": %d, \"us\": %lf}",
-                      arch, sig, &S, &bpc, &us) == 5) {
-        if (arch_ == arch && S >= 1 && bpc >= 0) {
-          launch_cache_[sig] = {S, bpc};
-          launch_us_[sig] = us;
-        }
+      int S, bpc, blocks = 0;
+      if (std::sscanf(p,
+                      "{\"arch\": \"%63[^\"]\", \"launch\": \"%95[^\"]\", \"S\": %d, \"bpc\": %d, \"us\": %lf, "
+                      "\"blocks\": %d}",
+                      arch, sig, &S, &bpc, &us, &blocks) >= 5) {
+        if (arch_ == arch && S >= 1 && bpc >= 0) launch_cache_[sig] = LaunchChoice{S, bpc, std::max(blocks, 0), us};
         continue;
       }
     }
@@ -633,10 +641,11 @@ void Engine::save_cache() {
     first = false;
   }
   for (const auto& kv : launch_cache_) {
-    const auto u = launch_us_.find(kv.first);
-    std::fprintf(f, "%s{\"arch\": \"%s\", \"launch\": \"%s\", \"S\": %d, \"bpc\": %d, \"us\": %.3f}",
-                 first ? "" : ",\n", arch_.c_str(), kv.first.c_str(), kv.second.first, kv.second.second,
-                 u == launch_us_.end() ? 0.0 : u->second);
+    const LaunchChoice& c = kv.second;
+    std::fprintf(f,
+                 "%s{\"arch\": \"%s\", \"launch\": \"%s\", \"S\": %d, \"bpc\": %d, \"us\": %.3f, "
+                 "\"blocks\": %d}",
+                 first ? "" : ",\n", arch_.c_str(), kv.first.c_str(), c.graph_steps, c.blocks_per_cu, c.us, c.blocks);
     first = false;
   }
   std::fprintf(f, "\n]}\n");

@@ -11,6 +11,7 @@
 // themselves; choices persist in a small JSON cache file.
 #pragma once
 
+#include <algorithm>
 #include <array>
 #include <initializer_list>
 #include <map>
@@ -73,9 +74,10 @@ class Engine {
   // per CU of the right-hand-side kernel. Off by default; when on, the
   // first step() on a job set not seen before times every candidate pair
   // on copies of the jobs' states (the caller's states are not touched; the
-  // results do not depend on either choice) and keeps the fastest, ties
-  // within 2% going to the default (10, 4). Choices persist per job-set
-  // signature (the multiset of size classes) in the tile cache file.
+  // results do not depend on either choice), each launch that several pairs
+  // come to once, and keeps the fastest, ties within 2% going to the default
+  // (10, 4). Choices persist per job-set signature (the multiset of size
+  // classes) in the tile cache file.
   void set_launch_tuning(bool on) { tune_launch_ = on; }
   struct LaunchTune {
     int graph_steps = 0, blocks_per_cu = 0;
@@ -125,8 +127,13 @@ class Engine {
   double tune_seconds_ = 0.0;
   bool tune_launch_ = false;
   LaunchTune last_tune_{};
-  std::map<std::string, std::pair<int, int>> launch_cache_;  // signature -> (graph steps, blocks per CU)
-  std::map<std::string, double> launch_us_;
+  // a tuned launch: the choice, the blocks of its largest right-hand-side
+  // launch (0: not known, from a file without them) and its time per step
+  struct LaunchChoice {
+    int graph_steps, blocks_per_cu, blocks;
+    double us;
+  };
+  std::map<std::string, LaunchChoice> launch_cache_;  // by job-set signature
 
   // host blob (pinned) and its device copy
   char* h_blob_ = nullptr;
@@ -151,6 +158,8 @@ class Engine {
   ListSizes list_sizes() const;
   int rhs_grid(long long list, long long tiles) const;
   LaunchShape launch_shape() const;
+  // blocks of the largest right-hand-side launch
+  static int most_blocks(const LaunchShape& l) { return *std::max_element(l.begin(), l.begin() + NVAR); }
   // the ghost lists refilled after a stage (gh[0]: ghosts with an interior
   // phi index, gh[1]: all) and the radiation points of job j: a
   // radiation-boundary grid refills only its inner ghosts (one-hop copies)

@@ -76,3 +76,34 @@ def test_blocks_per_cu_sets_the_launch(size, bpc):
     else:
         assert n <= blocks <= n + n // 32 + 8
     capi.batch_destroy(b)
+
+
+def _tuned(grids, ys, wss, cache):
+    import torch
+    from paper_2505_00097_amd import capi
+    b = capi.batch_create([g.h for g in grids], tune_cache_path=cache)
+    capi.batch_set_launch_tuning(b, True)
+    capi.batch_step(b, ys, wss, [g.dt for g in grids], nsteps=1)
+    torch.cuda.synchronize()
+    info = capi.batch_get_info(b)
+    capi.batch_destroy(b)
+    return info
+
+
+@pytest.mark.parametrize("sizes,launches", [([LONG, SHORT], 3), ([LONG], 6), ([SHORT], 12)])
+def test_launch_tuning_times_each_launch_once(tmp_path, sizes, launches):
+    """Of the blocks per CU {2, 4, 8, one per tile}, those that come to one
+    launch are one candidate (each at three graph lengths); a stored choice is
+    taken where it comes to the launch that was timed, and timed again where
+    not."""
+    print("launch tuning:", sizes, flush=True)
+    jobs = _jobs(sizes)
+    path = tmp_path / "tiles.json"
+    first = _tuned(*jobs, str(path))
+    assert first.launch_candidates == launches and not first.launch_from_cache
+    again = _tuned(*jobs, str(path))
+    assert again.launch_from_cache and again.rhs_blocks == first.rhs_blocks
+    stored = f'"blocks": {first.rhs_blocks}}}'
+    assert path.read_text().count(stored) == 1
+    path.write_text(path.read_text().replace(stored, f'"blocks": {first.rhs_blocks + 8}}}'))
+    assert not _tuned(*jobs, str(path)).launch_from_cache
