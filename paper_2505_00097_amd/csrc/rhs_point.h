@@ -67,11 +67,24 @@ struct Stage : StageSize<AX, H> {
 // points of one row, lane l takes points 2p and 2p+1, p = l mod 32, of
 // gridfunction list[2 i + l / 32], one 16-byte access for two gridfunctions
 // and two points: half the vector memory instructions of the per-lane form.
-typedef double bhah_d2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef double bhah_d2 __attribute__((ext_vector_type(2)));
+
+// a value of V from and to the caller's arrays, which are aligned to 8 bytes
+// (an alignment given to a type is lost where the type is a template argument,
+// so it stands at the access)
+typedef double bhah_d2_8 __attribute__((ext_vector_type(2), aligned(8)));
+template <class V>
+__device__ __forceinline__ V load_v(const double* p) {
+  if constexpr (std::is_same_v<V, double>) return *p;
+  else return *(const bhah_d2_8*)p;
+}
+__device__ __forceinline__ void store_v(double* p, double v) { *p = v; }
+__device__ __forceinline__ void store_v(double* p, bhah_d2 v) { *(bhah_d2_8*)p = v; }
 
 // V: double (per lane, twelve results) or bhah_d2 (row pairs, six); e(i) is
-// the element of result i, res(i) its place in the park. With keep the stored
-// values replace the results there.
+// the element of result i, res(i) its place in the park (for row pairs an even
+// one: aligned to 16 bytes). With keep the stored values replace the results
+// there.
 template <class V, int N, class E, class RES>
 __device__ __forceinline__ void store_stage(const StageArgs& st, bool keep, const E& e, const RES& res) {
   auto each = [](const V& k, auto f) {
@@ -84,12 +97,12 @@ __device__ __forceinline__ void store_stage(const StageArgs& st, bool keep, cons
   };
   auto ld = [&](const double* b, V(&x)[N]) {
 #pragma unroll
-    for (int i = 0; i < N; i++) x[i] = *(const V*)(b + e(i));
+    for (int i = 0; i < N; i++) x[i] = load_v<V>(b + e(i));
   };
   auto k = [&](int i) -> V& { return *(V*)res(i); };
   if (st.rhs) {
 #pragma unroll
-    for (int i = 0; i < N; i++) *(V*)(st.rhs + e(i)) = k(i);
+    for (int i = 0; i < N; i++) store_v(st.rhs + e(i), k(i));
     return;
   }
   V b1[N], o[N];
@@ -118,7 +131,7 @@ __device__ __forceinline__ void store_stage(const StageArgs& st, bool keep, cons
     for (int i = 0; i < N; i++) o[i] = each(k(i), [&](double x, int h) { return combine_plain(st, x, el(b1[i], h)); });
   }
 #pragma unroll
-  for (int i = 0; i < N; i++) *(V*)(st.out + e(i)) = o[i];
+  for (int i = 0; i < N; i++) store_v(st.out + e(i), o[i]);
   if (keep) {
 #pragma unroll
     for (int i = 0; i < N; i++) k(i) = o[i];
