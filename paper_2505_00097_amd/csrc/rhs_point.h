@@ -192,6 +192,7 @@ __device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs
     g1 = P.start[n + 1];
   }
   const bool push = g0 < g1;
+  wave_fence();  // the row pairs take other lanes' results
   const int p2 = 2 * (lane & 31), gs = lane >> 5;
   const unsigned qa = (unsigned)__shfl((int)q, p2), qb = (unsigned)__shfl((int)q, p2 + 1);
   if (__all(live && qb == qa + 1u)) {
@@ -203,7 +204,10 @@ __device__ __forceinline__ void stage_epilogue(const GridDev& G, const StageArgs
   } else if (live) {
     store_stage<double, 12>(st, push, [&](int i) { return list[i] * G.sgf + q; }, [&](int i) { return park + i * 64; });
   }
-  if (push) push_ghosts(G, P, g0, g1, st.out, list, park - lane, lane);
+  if (push) {
+    wave_fence();
+    push_ghosts(G, P, g0, g1, st.out, list, park - lane, lane);
+  }
 }
 
 // ---- metric wave ---------------------------------------------------------------

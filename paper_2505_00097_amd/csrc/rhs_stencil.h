@@ -19,6 +19,17 @@ namespace bhah {
 // values of a mixed pair). No instruction is emitted.
 __device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
 
+// Between LDS accesses of a wave where one lane reads or overwrites what another
+// lane of the wave stored or reads. The LDS serves a wave's accesses in the order
+// of their issue, so no instruction is emitted; this holds the compiler to that
+// order, which otherwise would rest on its not telling the addresses apart. The
+// 72 x 12 x 24 RK4 step takes 63.5 us with it, 63.3 without.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Upwinded advection beta^k d_k f (Sec. 3: the centred stencil shifted one
 // point upwind) as its antisymmetric and symmetric parts. With
 // D_j = f_j - f_-j and S_j = (f_j - f_0) + (f_-j - f_0), for either sign of
@@ -471,6 +482,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
     static_for<NB>([&](auto bc) BHAH_INLINE {
       constexpr int b = decltype(bc)::value;
       double o[PER];
+      if constexpr (b > 0) wave_fence();  // the last batch's reads, before its patches are overwritten
 #pragma unroll
       for (int t = 0; t < PER; t++)
         if (b * PER + t < N) {
@@ -479,6 +491,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
         }
       if constexpr (b + 1 < NB) issue(b + 1);
       BHAH_PHASE_BARRIER();
+      wave_fence();
       // every read of the batch's main patches, then its D_e patches, so that
       // one gridfunction's reads are under way while another's are waited for
       double v0[PER][2 * H + 1], vE[PER][2 * H + 1], vh[PER][2 * R + 1];
@@ -498,6 +511,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
           if constexpr (tt >= F0 && tt < F1) S.put_e(t, s[t][E].d1, d1_sum<R>(vh[t]));
         }
       });
+      if constexpr (b * PER < F1 && (b + 1) * PER > F0) wave_fence();
       static_for<PER>([&](auto tc) BHAH_INLINE {
         constexpr int t = decltype(tc)::value, tt = b * PER + t;
         if constexpr (tt < N) {
@@ -548,6 +562,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
       constexpr bool full = t >= F0 && t < F1;
       double vP[2 * H + 1];
       vP[0] = vP[2 * H] = 0.0;
+      if constexpr (t > 0) wave_fence();  // the last gridfunction's reads, before its patches are overwritten
       S.commit_main(m, 0);
 #pragma unroll
       for (int o = 1; o <= (ADV ? H : R); o++)
@@ -574,6 +589,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
       if constexpr (t + 1 < N) S.issue_main(list[t + 1], m);
       if constexpr (RAW) issue_phi(std::integral_constant<int, t + 1>{});
       BHAH_PHASE_BARRIER();
+      wave_fence();
       AxisSums s[3];
       double dd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, v0[2 * H + 1], vE[2 * H + 1];
       constexpr bool first = t >= F0 && t < F2;
@@ -593,6 +609,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
         double vh[2 * R + 1], w[3][2 * R + 1];
         S.halo_column(0, vh);
         if constexpr (RAW) {
+          wave_fence();  // the derivative patches lie over the raw one
           S.put_halo(0, dP[0], dP[1]);
           S.put_halo(1, dP[2], dP[3]);
         } else {
@@ -606,6 +623,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
         // during the sums along i0; at 8th there are no registers for that
         if constexpr (H != 3) sum(0, v0);
         BHAH_PHASE_BARRIER();
+        wave_fence();
         S.p_along_0(w[0]);
         if constexpr (H != 3) mixed(sy(0, PD), w[0]);
         S.p_along_e(w[1]);
@@ -630,6 +648,7 @@ __device__ __forceinline__ void run_stencils(const Source<H, AX>& S, const int (
       fn(t, s, dd, v0[H]);
     });
   }
+  wave_fence();  // the caller may use the stage's slots
 }
 
 // the number of a tile as the pushed ghosts are grouped (PushDev)
