@@ -295,25 +295,12 @@ struct bhah_grid {
   bhah::HostGhosts inner_full, inner_stage;
   bhah::RadDev rad{};
   bhah::GhostDev ghost_inner{}, ghost_inner_stage{};
-  int* d_rad_i = nullptr;     // q | shift | copy_start | copy
-  double* d_rad_c = nullptr;
-  int* d_inner_ints[2] = {nullptr, nullptr};
-  double* d_inner_w[2] = {nullptr, nullptr};
-  // device allocations
-  double* d_tab[3];
-  int* d_ints;      // dst | start | parity | src packed
-  double* d_w;
-  int* d_rints;     // the same for the stage ghost list
-  double* d_rw;
   // stage ghosts written by the right-hand-side kernel, and the list of the
   // others (on radiation grids without those that the radiation kernel copies)
   bhah::HostPush push;
   bhah::PushDev push_dev{};
   bhah::GhostDev ghost_left{};
-  int* d_push = nullptr;      // start | rec | terms
-  int* d_left_ints = nullptr;
-  double* d_left_w = nullptr;
-  long long n_int_block;
+  void* d_mem = nullptr;  // the device copies of all tables and lists
 };
 
 namespace bhah {

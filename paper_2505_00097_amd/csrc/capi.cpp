@@ -75,84 +75,88 @@ void ssprk3_stages(double dt, double* y, double* ws, long long n, StageArgs st[3
   gdst[0] = A; gdst[1] = B; gdst[2] = y;
 }
 
-static void free_device(bhah_grid* g) {
-  for (int d = 0; d < 3; d++)
-    if (g->d_tab[d]) (void)hipFree(g->d_tab[d]);
-  for (void* p : {(void*)g->d_ints, (void*)g->d_w, (void*)g->d_rints, (void*)g->d_rw, (void*)g->d_rad_i,
-                  (void*)g->d_rad_c, (void*)g->d_inner_ints[0], (void*)g->d_inner_w[0], (void*)g->d_inner_ints[1],
-                  (void*)g->d_inner_w[1], (void*)g->d_push, (void*)g->d_left_ints, (void*)g->d_left_w})
-    if (p) (void)hipFree(p);
-}
+// The device copies of a grid's tables and lists: one allocation, one copy for
+// all small arrays together and one for each large one (a grid has up to 40
+// arrays; an allocation and a copy for every few of them took a third of the
+// creation of a small grid, gathering the large ones on the host first as much
+// of that of a large one).
+struct DeviceImage {
+  static constexpr size_t kSmall = 1 << 16;
+  struct Item {
+    const void* host;
+    size_t bytes;
+    const void** slot;  // receives the device address
+  };
+  std::vector<Item> items;
+  template <class T>
+  void put(const std::vector<T>& v, const T** slot) {
+    items.push_back({v.data(), v.size() * sizeof(T), (const void**)slot});
+  }
+  void put(const std::vector<int>& dst, const std::vector<int>& start, const std::vector<int>& par,
+           const std::vector<int>& src, const std::vector<double>& w, GhostDev* out) {
+    out->n_ghost = (int)dst.size();
+    put(dst, &out->dst);
+    put(start, &out->start);
+    put(par, &out->parity);
+    put(src, &out->src);
+    put(w, &out->w);
+  }
+  void put(const HostGhosts& h, GhostDev* out) { put(h.dst, h.start, h.par, h.src, h.w, out); }
+  hipError_t upload(void** mem) {
+    auto small = [](const Item& i) { return i.bytes <= kSmall; };
+    std::stable_partition(items.begin(), items.end(), small);
+    std::vector<size_t> at;
+    size_t total = 0, head = 0;
+    for (const Item& i : items) {
+      at.push_back(total);
+      total += (i.bytes + 255) / 256 * 256;
+      if (small(i)) head = total;
+    }
+    std::vector<char> pack(head);
+    hipError_t e = hipMalloc(mem, total + 256);
+    for (size_t k = 0; k < items.size() && e == hipSuccess; k++) {
+      const Item& i = items[k];
+      *i.slot = (char*)*mem + at[k];
+      if (!small(i)) e = hipMemcpy((char*)*mem + at[k], i.host, i.bytes, hipMemcpyHostToDevice);
+      else if (i.bytes) std::memcpy(pack.data() + at[k], i.host, i.bytes);
+    }
+    if (e == hipSuccess && head) e = hipMemcpy(*mem, pack.data(), head, hipMemcpyHostToDevice);
+    return e;
+  }
+};
 
-// Upload one ghost list (dst | start | parity | src packed as ints, weights
-// separately) and return its device view.
-static hipError_t upload_ghosts(const std::vector<int>& dst, const std::vector<int>& start,
-                                const std::vector<int>& par, const std::vector<int>& src,
-                                const std::vector<double>& w, int** d_ints, double** d_w, GhostDev* out) {
-  const size_t ng = dst.size(), nt = src.size();
-  std::vector<int> packed;
-  packed.reserve(3 * ng + 1 + nt);
-  packed.insert(packed.end(), dst.begin(), dst.end());
-  packed.insert(packed.end(), start.begin(), start.end());
-  packed.insert(packed.end(), par.begin(), par.end());
-  packed.insert(packed.end(), src.begin(), src.end());
-  hipError_t e = hipMalloc((void**)d_ints, packed.size() * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc((void**)d_w, (nt ? nt : 1) * sizeof(double));
-  if (e == hipSuccess) e = hipMemcpy(*d_ints, packed.data(), packed.size() * sizeof(int), hipMemcpyHostToDevice);
-  if (e == hipSuccess && nt) e = hipMemcpy(*d_w, w.data(), nt * sizeof(double), hipMemcpyHostToDevice);
-  out->n_ghost = (int)ng;
-  out->dst = *d_ints;
-  out->start = *d_ints + ng;
-  out->parity = *d_ints + 2 * ng + 1;
-  out->src = *d_ints + 3 * ng + 1;
-  out->w = *d_w;
-  return e;
-}
-
-// Upload the ghosts that the right-hand-side kernel writes and the list of the
-// stage's other ghosts.
-static hipError_t upload_push(bhah_grid* g) {
+// Everything of a grid that its kernels read.
+static hipError_t upload_grid(bhah_grid* g) {
+  DeviceImage im;
+  const double** tab[3] = {&g->dev.tab0, &g->dev.tab1, &g->dev.tab2};
+  for (int d = 0; d < 3; d++) im.put(g->tab[d], tab[d]);
+  im.put(g->g_dst, g->g_start, g->g_par, g->g_src, g->g_w, &g->ghost);
+  im.put(g->r_dst, g->r_start, g->r_par, g->r_src, g->r_w, &g->ghost_stage);
+  // the ghosts that the right-hand-side kernel writes (the records, read as
+  // 16-byte words, begin on a multiple of 256) and the stage's other ghosts
   const HostPush& P = g->push;
-  if (P.start.empty()) return hipSuccess;
-  // records first: they are read as 16-byte words
-  std::vector<int> packed(P.rec);
-  packed.insert(packed.end(), P.terms.begin(), P.terms.end());
-  packed.insert(packed.end(), P.start.begin(), P.start.end());
-  hipError_t e = hipMalloc((void**)&g->d_push, packed.size() * sizeof(int));
-  if (e == hipSuccess) e = hipMemcpy(g->d_push, packed.data(), packed.size() * sizeof(int), hipMemcpyHostToDevice);
-  const int* terms = g->d_push + P.rec.size();
-  g->push_dev = PushDev{terms + P.terms.size(), g->d_push, terms, P.nx, P.ne};
-  if (e == hipSuccess)
-    e = upload_ghosts(P.left.dst, P.left.start, P.left.par, P.left.src, P.left.w, &g->d_left_ints, &g->d_left_w,
-                      &g->ghost_left);
-  return e;
-}
-
-// Upload the radiation lists: the outer points (q | shift packed, 3
-// coefficients each, their copies) and the two inner-copy lists.
-static hipError_t upload_radiation(bhah_grid* g) {
-  const size_t n = g->rad_q.size();
-  std::vector<int> packed(g->rad_q);
-  packed.insert(packed.end(), g->rad_shift.begin(), g->rad_shift.end());
-  packed.insert(packed.end(), g->rad_copy_start.begin(), g->rad_copy_start.end());
-  packed.insert(packed.end(), g->rad_copy.begin(), g->rad_copy.end());
-  // coefficients [n][3], then the stencil weight table
-  const size_t nw = g->rad_w.size();
-  std::vector<double> coef(g->rad_coef);
-  coef.insert(coef.end(), g->rad_w.begin(), g->rad_w.end());
-  hipError_t e = hipMalloc((void**)&g->d_rad_i, packed.size() * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc((void**)&g->d_rad_c, (3 * n + nw) * sizeof(double));
-  if (e == hipSuccess)
-    e = hipMemcpy(g->d_rad_i, packed.data(), packed.size() * sizeof(int), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g->d_rad_c, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice);
-  g->rad = RadDev{(int)n, g->d_rad_i, g->d_rad_i + n, g->d_rad_c, g->params.nghosts - 1, g->d_rad_c + 3 * n,
-                  g->d_rad_i + 2 * n, g->d_rad_i + 3 * n + 1};
-  const HostGhosts* L[2] = {&g->inner_full, &g->inner_stage};
-  GhostDev* D[2] = {&g->ghost_inner, &g->ghost_inner_stage};
-  for (int k = 0; k < 2 && e == hipSuccess; k++)
-    e = upload_ghosts(L[k]->dst, L[k]->start, L[k]->par, L[k]->src, L[k]->w, &g->d_inner_ints[k],
-                      &g->d_inner_w[k], D[k]);
-  return e;
+  if (!P.start.empty()) {
+    g->push_dev.nx = P.nx;
+    g->push_dev.ne = P.ne;
+    im.put(P.start, &g->push_dev.start);
+    im.put(P.rec, &g->push_dev.rec);
+    im.put(P.terms, &g->push_dev.terms);
+    im.put(P.left, &g->ghost_left);
+  }
+  // the evolved outer points, their copies, the two inner-copy lists
+  if (g->params.bc_kind == BHAH_BC_RADIATION) {
+    g->rad.n = (int)g->rad_q.size();
+    g->rad.R = g->params.nghosts - 1;
+    im.put(g->rad_q, &g->rad.q);
+    im.put(g->rad_shift, &g->rad.shift);
+    im.put(g->rad_coef, &g->rad.coef);
+    im.put(g->rad_w, &g->rad.w);
+    im.put(g->rad_copy_start, &g->rad.copy_start);
+    im.put(g->rad_copy, &g->rad.copy);
+    im.put(g->inner_full, &g->ghost_inner);
+    im.put(g->inner_stage, &g->ghost_inner_stage);
+  }
+  return im.upload(&g->d_mem);
 }
 
 // One stage of a time integrator: the interior right-hand side combined as in
@@ -185,30 +189,16 @@ int bhah_grid_create(const bhah_grid_params* params, bhah_grid** out) {
   if (!params || !out) return fail(BHAH_EINVAL, "bhah_grid_create: NULL argument");
   bhah_grid* g = new (std::nothrow) bhah_grid();
   if (!g) return fail(BHAH_ENOMEM, "bhah_grid_create: host allocation failed");
-  for (int d = 0; d < 3; d++) g->d_tab[d] = nullptr;
-  g->d_ints = g->d_rints = nullptr;
-  g->d_w = g->d_rw = nullptr;
   int rc = build_grid_host(params, g);
   if (rc) { delete g; return rc; }
   if ((rc = check_hip(hipGetDevice(&g->device), "hipGetDevice"))) { delete g; return rc; }
 
   const bhah_grid_info& I = g->info;
-  hipError_t e = hipSuccess;
-  for (int d = 0; d < 3 && e == hipSuccess; d++) {
-    e = hipMalloc((void**)&g->d_tab[d], g->tab[d].size() * sizeof(double));
-    if (e == hipSuccess)
-      e = hipMemcpy(g->d_tab[d], g->tab[d].data(), g->tab[d].size() * sizeof(double), hipMemcpyHostToDevice);
-  }
-  if (e == hipSuccess)
-    e = upload_ghosts(g->g_dst, g->g_start, g->g_par, g->g_src, g->g_w, &g->d_ints, &g->d_w, &g->ghost);
-  if (e == hipSuccess)
-    e = upload_ghosts(g->r_dst, g->r_start, g->r_par, g->r_src, g->r_w, &g->d_rints, &g->d_rw, &g->ghost_stage);
-  if (e == hipSuccess) e = upload_push(g);
-  if (e == hipSuccess && params->bc_kind == BHAH_BC_RADIATION) e = upload_radiation(g);
+  const hipError_t e = upload_grid(g);
   if (e != hipSuccess) {
     const int code = e == hipErrorOutOfMemory ? BHAH_ENOMEM : BHAH_EDEVICE;
     fail(code, std::string("bhah_grid_create: ") + hipGetErrorString(e));
-    free_device(g);
+    if (g->d_mem) (void)hipFree(g->d_mem);
     delete g;
     return code;
   }
@@ -222,14 +212,13 @@ int bhah_grid_create(const bhah_grid_params* params, bhah_grid** out) {
   D.s2 = D.n0 * D.n1;
   D.sgf = I.n_points;
   for (int d = 0; d < 3; d++) D.inv_dx[d] = 1.0 / I.dxx[d];
-  D.tab0 = g->d_tab[0]; D.tab1 = g->d_tab[1]; D.tab2 = g->d_tab[2];
   *out = g;
   return BHAH_OK;
 }
 
 void bhah_grid_destroy(bhah_grid* g) {
   if (!g) return;
-  free_device(g);
+  if (g->d_mem) (void)hipFree(g->d_mem);
   delete g;
 }
 

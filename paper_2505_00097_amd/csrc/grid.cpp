@@ -23,7 +23,6 @@
 // ghosts. Inner ghosts whose source is an outer ghost take that combination.
 #include <algorithm>
 #include <cmath>
-#include <map>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -66,7 +65,14 @@ void map_row(bool linear, double A, double w, double x, double* out) {
   out[3] = A * ch / (w * w * w * s);
 }
 
-using Comb = std::map<int, long long>;  // interior flat index -> integer weight
+// interior flat index -> integer weight, sorted by index (three terms, mostly)
+struct Comb : std::vector<std::pair<int, long long>> {
+  void add(int q, long long w) {
+    const auto it = std::lower_bound(begin(), end(), q, [](const value_type& t, int k) { return t.first < k; });
+    if (it != end() && it->first == q) it->second += w;
+    else insert(it, {q, w});
+  }
+};
 
 // d/dx at 0 of the polynomial interpolating f at the integer nodes s..s+2R:
 // weights w_j = L_j'(0) of the Lagrange basis, summed in exact rational
@@ -237,9 +243,10 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
   }
 
   // ---- CFL time step: cfl * min over interior points of min_i S_i dxx^i ----
+  // (no S_i depends on phi)
   double dsmin = INFINITY;
-  for (int i2 = ng; i2 < ng + p->N[2]; i2++)
-    for (int i1 = ng; i1 < ng + p->N[1]; i1++)
+  for (int i2 = ng; i2 < ng + (dphi == 2 ? 1 : p->N[2]); i2++)
+    for (int i1 = ng; i1 < ng + (dphi == 1 ? 1 : p->N[1]); i1++)
       for (int i0 = ng; i0 < ng + p->N[0]; i0++) {
         const double* t0 = &g->tab[0][(size_t)i0 * TAB_W];
         double S[3];
@@ -302,14 +309,15 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
                 const int s = (int)(q + t * step);
                 const int ks = kind_of(s);
                 if (ks == 0) {
-                  c[s] += w3[t - 1];
+                  c.add(s, w3[t - 1]);
                 } else if (ks == 1 && !comb_of(s).empty()) {
-                  for (auto& kv : comb_of(s)) c[kv.first] += w3[t - 1] * kv.second;
+                  for (auto& kv : comb_of(s)) c.add(kv.first, w3[t - 1] * kv.second);
                 } else {
                   return fail(BHAH_EINVAL, "extrapolation reads a point not yet filled");
                 }
               }
-              for (auto it = c.begin(); it != c.end();) it = it->second == 0 ? c.erase(it) : std::next(it);
+              c.erase(std::remove_if(c.begin(), c.end(), [](const Comb::value_type& t) { return t.second == 0; }),
+                      c.end());
               comb[q] = std::move(c);
             }
       }
@@ -318,20 +326,27 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
     }
   }
 
-  // ---- ghost list --------------------------------------------------------
+  // ---- ghost lists: all, and those needed by the stencils during the RK stages
+  // (phi ghost planes are skipped there: reads wrap phi onto the interior)
   const long long n_ghosts = np - I.n_interior;
   g->g_dst.clear(); g->g_start.clear(); g->g_par.clear(); g->g_src.clear(); g->g_w.clear();
   g->g_dst.reserve(n_ghosts); g->g_start.reserve(n_ghosts + 1); g->g_par.reserve(n_ghosts);
   g->g_src.reserve(n_ghosts); g->g_w.reserve(n_ghosts);
+  const long long n_stage = n_ghosts / n[dphi] * p->N[dphi];
+  g->r_dst.clear(); g->r_start.clear(); g->r_par.clear(); g->r_src.clear(); g->r_w.clear();
+  g->r_dst.reserve(n_stage); g->r_start.reserve(n_stage + 1); g->r_par.reserve(n_stage);
+  g->r_src.reserve(n_stage); g->r_w.reserve(n_stage);
   g->max_terms = 0;
   long long n_outer = 0, n_inner = 0;
-  std::vector<std::pair<int, long long>> single(1);
   for (int i2 = 0; i2 < n[2]; i2++)
     for (int i1 = 0; i1 < n[1]; i1++)
       for (int i0 = 0; i0 < n[0]; i0++) {
         int src, par;
         const int k = classify(i0, i1, i2, src, par);
-        if (k == 0) continue;
+        if (k == 0) {  // the interior of this row
+          i0 += p->N[0] - 1;
+          continue;
+        }
         const int q = flat(i0, i1, i2);
         const Comb* c = nullptr;
         bool one = false;
@@ -358,28 +373,19 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
           for (auto& kv : *c) { g->g_src.push_back(kv.first); g->g_w.push_back((double)kv.second); }
           g->max_terms = std::max(g->max_terms, (int)c->size());
         }
+        const int idx = dphi == 1 ? i1 : i2;
+        if (idx < ng || idx >= ng + p->N[dphi]) continue;
+        g->r_dst.push_back(q);
+        g->r_start.push_back((int)g->r_src.size());
+        g->r_par.push_back(par);
+        for (size_t k = g->g_start.back(); k < g->g_src.size(); k++) {
+          g->r_src.push_back(g->g_src[k]);
+          g->r_w.push_back(g->g_w[k]);
+        }
       }
   g->g_start.push_back((int)g->g_src.size());
-
-  // ---- ghosts needed by the stencils during the RK stages ---------------
-  // (phi ghost planes are skipped: reads wrap phi onto the interior)
-  const int pd = coord == BHAH_SINH_CYLINDRICAL ? 1 : 2;
-  g->r_dst.clear(); g->r_start.clear(); g->r_par.clear(); g->r_src.clear(); g->r_w.clear();
-  g->r_dst.reserve(g->g_dst.size()); g->r_start.reserve(g->g_dst.size() + 1); g->r_par.reserve(g->g_dst.size());
-  g->r_src.reserve(g->g_src.size()); g->r_w.reserve(g->g_src.size());
-  for (size_t t = 0; t < g->g_dst.size(); t++) {
-    const int q = g->g_dst[t];
-    const int idx = pd == 1 ? (q / n[0]) % n[1] : q / (n[0] * n[1]);
-    if (idx < ng || idx >= ng + p->N[pd]) continue;
-    g->r_dst.push_back(q);
-    g->r_start.push_back((int)g->r_src.size());
-    g->r_par.push_back(g->g_par[t]);
-    for (int k = g->g_start[t]; k < g->g_start[t + 1]; k++) {
-      g->r_src.push_back(g->g_src[k]);
-      g->r_w.push_back(g->g_w[k]);
-    }
-  }
   g->r_start.push_back((int)g->r_src.size());
+
   I.n_pure_outer = n_outer;
   I.n_inner = n_inner;
 
@@ -399,7 +405,10 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
         for (int i0 = 0; i0 < n[0]; i0++) {
           int src, par;
           const int k = classify(i0, i1, i2, src, par);
-          if (k == 0) continue;
+          if (k == 0) {  // the interior of this row
+            i0 += p->N[0] - 1;
+            continue;
+          }
           const int q = flat(i0, i1, i2);
           if (k == 1) {
             // rhat . grad xx^k from the radial maps: r = r(xx0) on the
@@ -424,9 +433,9 @@ int build_grid_host(const bhah_grid_params* p, bhah_grid* g) {
             g->rad_coef.push_back(a0 / I.dxx[0]);
             g->rad_coef.push_back(a2 / I.dxx[2]);
           } else {
-            const int idx = pd == 1 ? i1 : i2;
+            const int idx = dphi == 1 ? i1 : i2;
             for (HostGhosts* L : {&g->inner_full, &g->inner_stage}) {
-              if (L == &g->inner_stage && (idx < ng || idx >= ng + p->N[pd])) continue;
+              if (L == &g->inner_stage && (idx < ng || idx >= ng + p->N[dphi])) continue;
               L->dst.push_back(q);
               L->start.push_back((int)L->src.size());
               L->par.push_back(par);
