@@ -189,12 +189,21 @@ int bhah_grid_create(const bhah_grid_params* params, bhah_grid** out) {
   if (!params || !out) return fail(BHAH_EINVAL, "bhah_grid_create: NULL argument");
   bhah_grid* g = new (std::nothrow) bhah_grid();
   if (!g) return fail(BHAH_ENOMEM, "bhah_grid_create: host allocation failed");
-  int rc = build_grid_host(params, g);
-  if (rc) { delete g; return rc; }
-  if ((rc = check_hip(hipGetDevice(&g->device), "hipGetDevice"))) { delete g; return rc; }
-
+  int rc = BHAH_OK;
+  hipError_t e = hipSuccess;
+  try {
+    rc = build_grid_host(params, g);
+    if (!rc) rc = check_hip(hipGetDevice(&g->device), "hipGetDevice");
+    if (!rc) e = upload_grid(g);
+  } catch (const std::bad_alloc&) {
+    rc = fail(BHAH_ENOMEM, "bhah_grid_create: host allocation failed");
+  }
+  if (rc) {
+    if (g->d_mem) (void)hipFree(g->d_mem);
+    delete g;
+    return rc;
+  }
   const bhah_grid_info& I = g->info;
-  const hipError_t e = upload_grid(g);
   if (e != hipSuccess) {
     const int code = e == hipErrorOutOfMemory ? BHAH_ENOMEM : BHAH_EDEVICE;
     fail(code, std::string("bhah_grid_create: ") + hipGetErrorString(e));
