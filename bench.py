@@ -29,16 +29,16 @@ PEAK_HBM = 8.0e12           # bytes/s
 
 # FP64 operations per interior point for one right-hand-side evaluation, per
 # (coordinate family, two phi planes): the fadd/fsub/fmul/fdiv count (an FMA
-# counts 2) of the optimised per-point code, as
-# paper_2505_00097_amd/count_flops.py prints it (a CPU test keeps the two in
-# step). On grids with two phi planes the kernel variant drops the phi
+# counts 2) of the optimised per-point code without the derivatives that
+# neighbouring tiles form too, as paper_2505_00097_amd/count_flops.py prints it
+# (a CPU test keeps the two in step). On grids with two phi planes the kernel variant drops the phi
 # derivatives that vanish identically there, and its own count applies.
-F_ALG = {(0, False): 4663, (0, True): 3575, (1, False): 4444, (1, True): 3336, (2, False): 4644,
-         (2, True): 3556}
+F_ALG = {(0, False): 4443, (0, True): 3531, (1, False): 4224, (1, True): 3292, (2, False): 4424,
+         (2, True): 3512}
 # the same for the 8th-order kernels (five ghost layers), with Kreiss-Oliger
 # dissipation as the production head-on numerics run them
-F_ALG8_KO = {(0, False): 6938, (0, True): 4861, (1, False): 6719, (1, True): 4622, (2, False): 6919,
-             (2, True): 4842}
+F_ALG8_KO = {(0, False): 6333, (0, True): 4740, (1, False): 6114, (1, True): 4501, (2, False): 6314,
+             (2, True): 4721}
 
 
 def two_planes(coord, N):

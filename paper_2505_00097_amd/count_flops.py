@@ -10,12 +10,13 @@ instructions (an fma or fmuladd call counts 2) of the basic blocks that store
 nothing to global memory (plain or buffer stores), less those whose results
 only feed such stores (the stage combination the compiler computes ahead of
 its store) and the terms of the ghost sums (whose weights are converted
-integers): that is the per-point arithmetic of Eqs. 7-15 after
-common-subexpression elimination, with a lane's share of the derivatives at
-the halo points of its patch (for each of eleven gridfunctions 20 operations at
-4th order and 55 at 8th, 5 and 11 with two phi planes), without the RK stage
-combination that follows. The result is the FLOP figure the benchmark
-divides by the measured launch time.
+integers), less a lane's share of the derivatives at the halo points of its
+patch (HALO_SHARE: neighbouring patches form them too, a finer tiling would
+form more of them): that is the per-point arithmetic of Eqs. 7-15 after
+common-subexpression elimination, without the RK stage combination that
+follows. What both waves of a tile form for themselves (the inverse metric, the
+connection terms of the shift) counts in each. The result is the FLOP figure
+the benchmark divides by the measured launch time.
 
     python paper_2505_00097_amd/count_flops.py
 """
@@ -27,6 +28,12 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, HERE)
+
+# operations of one lane at halo points, by (ghost layers, two phi planes): the
+# sums along e at the halo columns and along phi at the lane's pairs of the phi
+# halo (5 and 11 operations each, at 4th order one less by a weight of -1), for
+# each of the eleven gridfunctions with mixed derivatives
+HALO_SHARE = {(3, False): 11 * 20, (3, True): 11 * 4, (5, False): 11 * 55, (5, True): 11 * 11}
 
 COORD_NAMES = {0: "SinhSpherical", 1: "SinhCylindrical", 2: "Spherical"}
 
@@ -83,7 +90,7 @@ def count(ir, kernel_prefix="_ZN4bhah11k_rhs_fusedILi", dissipation=False, nghos
                 if us and all(stores[bi] or (r is not None and r in dead) for bi, r in us):
                     dead.add(v)
                     changed = True
-        res[c] = sum(w for v, w in ops.items() if v not in dead)
+        res[c] = sum(w for v, w in ops.items() if v not in dead) - HALO_SHARE[(nghosts, c[1])]
     return res
 
 
@@ -95,7 +102,8 @@ def main():
             for (c, ax), n in sorted(count(ir, dissipation=ko, nghosts=ng).items()):
                 st = f" (with stage ghosts: {staged[(c, ax)]})" if (c, ax) in staged else ""
                 print(f"order {2 * (ng - 1)}: {COORD_NAMES[c]}{' (two phi planes)' if ax else ''}"
-                      f"{' + dissipation' if ko else ''}: {n} FP64 operations per point{st}")
+                      f"{' + dissipation' if ko else ''}: {n} FP64 operations per point{st}, "
+                      f"{HALO_SHARE[(ng, ax)]} more at halo points")
 
 
 if __name__ == "__main__":
