@@ -129,9 +129,9 @@ constexpr bool AX = VARIANT % 2 == 1;
 
 // what 0: right-hand side into out, with aux; 1: the stage out = base + c k with
 // the pushed ghosts (those left to the ghost kernel are not written); 2: the
-// seven constraints into out. Returns 0, or 1 where lanes of a wave or the waves
+// seven constraints into out. Tiles are walked in bands of `band`. Returns 0, or 1 where lanes of a wave or the waves
 // come to different synchronisations.
-extern "C" int run_tiles(const bhah_grid_params* par, const bhah_gauge_params* gp, int what, int order, const double* y,
+extern "C" int run_tiles(const bhah_grid_params* par, const bhah_gauge_params* gp, int what, int order, int band, const double* y,
                          const double* base, double c, double* out, double* aux) {
   std::unique_ptr<bhah_grid> g(new bhah_grid());
   if (int rc = build_grid_host(par, g.get())) return rc;
@@ -147,7 +147,7 @@ extern "C" int run_tiles(const bhah_grid_params* par, const bhah_gauge_params* g
   T.ty = (G.N1 + (1 << T.ly) - 1) >> T.ly;
   T.tz = C == BHAH_SINH_CYLINDRICAL ? (G.N2 + TEE - 1) / TEE : G.N2;
   T.ntiles = T.tx * T.ty * T.tz;
-  T.band = std::min(T.ty, 4);
+  T.band = std::min(T.ty, band);
   const HostPush& P = g->push;
   const PushDev push = what == 1 && !P.start.empty()
                            ? PushDev{P.start.data(), P.rec.data(), P.terms.data(), P.nx, P.ne}
