@@ -12,14 +12,15 @@
 //     It stores the other twelve.
 // What bounds it: the latency of a wave's own loads, LDS reads and arithmetic,
 // so the aim is two waves per SIMD, each within 256 registers and half of
-// 40 KB of LDS (four blocks, eight waves, per CU); on large grids it is the
-// rate of line requests to the L2s (rhs_stencil.h). The split
-// keeps about 60 values per point in each wave; what the waves exchange and
-// the stencil stages share 80 LDS slots per point (slot v of lane l at
-// xs[v * 64 + l]). One wave per tile and SIMD with the algebra in coordinate
-// components took 19.2 us for a right-hand side on the 128 x 2 x 256 head-on
-// grid, 954 us on a 256 x 128 x 64 one and 2.44 ms there at 8th order with
-// dissipation; this form takes 13.2 us, 642 us and 1.30 ms.
+// 40 KB of LDS (four blocks, eight waves, per CU). On large grids loads queue
+// for the L2s as well (rhs_stencil.h): on the 256 x 128 x 64 grid a wave issues
+// vector arithmetic in 18% of its cycles and waits for memory or LDS in 35%, at
+// 8th order in 12% and 44%. The split keeps about 60 values per point in each
+// wave; what the waves exchange and the stencil stages share 80 LDS slots per
+// point (slot v of lane l at xs[v * 64 + l]). One wave per tile and SIMD with
+// the algebra in coordinate components took 19.2 us for a right-hand side on the
+// 128 x 2 x 256 head-on grid, 954 us on a 256 x 128 x 64 one and 2.44 ms there
+// at 8th order with dissipation; this form takes 13.0 us, 641 us and 1.29 ms.
 #pragma once
 
 #include "rhs_stencil.h"

@@ -160,11 +160,12 @@ struct Patch {
   // The phi planes at offsets -R..R, in pairs of points. 4th order (RAW): the
   // patch's rows with their halo along i0, then the rows of the halo along e,
   // D_phi of each formed in registers; the point's own values come from the
-  // same loads through LDS (a raw patch of the four planes). What bounds 3-D
-  // grids is the rate of line requests from the CUs to the L2s (115 per ns),
-  // so no line is asked for twice: with the halo alone in pairs and the
-  // point's own column loaded apart the 256 x 128 x 64 right-hand side makes
-  // 92 instead of 83 million requests, 716 instead of 687 us. At 8th order
+  // same loads through LDS (a raw patch of the four planes). Line requests from
+  // the CUs to the L2s cost time on 3-D grids: the 256 x 128 x 64 right-hand side
+  // took 716, 684 and 642 us with 92, 84 and 74 million of them, about 4 us per
+  // million (and some 345 us that do not follow them), so no line is asked for
+  // twice: with the halo alone in pairs and the point's own column loaded apart
+  // it makes 92 instead of 83 million, 716 instead of 687 us. At 8th order
   // LDS has no room for the raw patch: halo (rows along e, then columns) and
   // own column there.
   static constexpr bool RAW = !AX && H == 3;
@@ -364,17 +365,19 @@ struct Source {
   __device__ __forceinline__ double column(int g, int m) const { return gf_ld(y, sgf, g, vlane, sw[H + m]); }
 };
 
-// Tiles: 64 points, 2^lx along i0 times 2^ly along i1 times 64 >> (lx + ly)
-// along i2; the tile grid is walked in bands of `band` tile rows of i1, and
-// within a band by i2, then i1, then i0 (fastest), so that tiles that share
-// cache lines along i0 run at the same time. The hardware hands consecutive
-// workgroup ids to the XCDs in turn; block ids are remapped so that every XCD
-// works through one contiguous range of the walk (its L2 then holds a compact
-// part of the grid). The lines matter more than the bytes: in columns of 64
-// points the 3-D RK4 stage reads 2.4 GB instead of 4.2 GB through the L2s, but
-// every column edge leaves lines that two tiles complete far apart in time
-// (1.16x the write requests), and the step takes 3.90 ms instead of 3.66 ms
-// (head-on 0.934 instead of 0.902 ms per 10 steps).
+// Tiles: patches of 2^lx points along i0 times 2^ly along i1 times
+// 64 >> (lx + ly) along i2 (16 along i0, 4 along e); the tile grid is walked in
+// bands of `band` tile rows of i1, and within a band by i2, then i1, then i0
+// (fastest), so that tiles that share cache lines along i0 run at the same time.
+// The hardware hands consecutive workgroup ids to the XCDs in turn; block ids
+// are remapped so that every XCD works through one contiguous range of the walk
+// (its L2 then holds a compact part of the grid). Bands of 16, 4 and 1: a
+// 256 x 128 x 64 RK4 step takes 3.33, 3.10 and 3.27 ms, an SSPRK3 step there at
+// 8th order with dissipation 5.22, 4.23 and 4.59, a 1008 x 168 x 336 RK4 step
+// 113.5, 103.9 and 102.6. Neither the bytes past the L2s nor the requests to
+// them tell which is best: a right-hand side on the first grid makes 74.6
+// million requests at every band, with 28, 28 and 12 million misses, in 664, 641
+// and 683 us.
 // (t0, t1, t2) is the tile's first point; (i0, i1, i2) the lane's, moved onto
 // the grid where the tile runs past it (false is returned for such lanes).
 template <int H>
