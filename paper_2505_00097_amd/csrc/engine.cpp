@@ -44,9 +44,9 @@ double now_s() {
 std::vector<TileCfg> tile_candidates(const SizeClass& c) {
   const int N1 = std::get<2>(c), ty = std::get<0>(c) == BHAH_SINH_CYLINDRICAL ? N1 : (N1 + PATCH_E - 1) / PATCH_E;
   std::vector<TileCfg> out;
-  // bands of 4 and 16 tile rows: tiles that run at the same time share
-  // stencil planes in the XCD's L2. Wider bands first: near-ties go to the
-  // walk with the better L2 reuse
+  // bands of 16, 4 and 1 tile rows: which planes tiles that run at the same
+  // time share (times of each beside the walk, rhs_stencil.h). A grid's tuner
+  // gives near-ties to the first, a batch takes the fastest
   if (ty > 8) out.push_back(TileCfg{6, 0, 16});
   if (ty > 1) out.push_back(TileCfg{6, 0, 4});
   out.push_back(TileCfg{6, 0, 1});
